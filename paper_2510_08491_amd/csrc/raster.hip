@@ -349,6 +349,43 @@ __device__ __forceinline__ float alpha_of(float ahat, float alpha_max) {
   return fminf(al, alpha_max);
 }
 
+// bit j: the rectangle of staged instance j meets this wave's pixels.  Lane j
+// tests instance j, so a batch costs one test instead of one per instance
+// (at 200k primitives 40% of a tile's instances miss a given 8 x 8 block).
+template <int N, int B, typename PB>
+__device__ __forceinline__ unsigned long long meets_wave(const Stage<N, B>& S, const PB& pb, int nb) {
+  static_assert(B <= 64, "one lane per instance");
+  const int lane = (int)(threadIdx.x & 63);
+  bool meets = false;
+  if (lane < nb) {
+    const int4 rc = S.rect[lane];
+    meets = !(rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1);
+  }
+  return __ballot(meets);
+}
+
+// sum over the hidden units of W2 cos(phase) sinc(half-width) for PPL pixels
+// of a lane (a miss has e' = 0 and stays finite)
+template <int N, int PPL>
+__device__ __forceinline__ void unit_sum(const float4* tab, const PairGeom (&g)[PPL], float (&Q)[PPL]) {
+  const float* tabf = reinterpret_cast<const float*>(tab);
+#pragma unroll
+  for (int q = 0; q < PPL; ++q) Q[q] = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < N; ++k) {
+    const float4 w = tab[k];
+    const float w2 = tabf[4 * N + k];
+#pragma unroll
+    for (int q = 0; q < PPL; ++q) {
+      const float ph = __builtin_fmaf(w.x, g[q].p0, __builtin_fmaf(w.y, g[q].p1, __builtin_fmaf(w.z, g[q].p2, w.w)));
+      const float hv = __builtin_fmaf(w.x, g[q].e0, __builtin_fmaf(w.y, g[q].e1, w.z * g[q].e2));
+      const float c = cos_rev(ph);
+      const float sn = sinc_rev(sin_rev(hv), hv);
+      Q[q] = __builtin_fmaf(w2 * c, sn, Q[q]);
+    }
+  }
+}
+
 // adds the wave's total of v to *slot (one atomic per wave)
 __device__ __forceinline__ void count_tile_pairs(uint32_t* slot, uint32_t v) {
   for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
@@ -403,9 +440,8 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
       else
         stage_batch<N, NT, FB>(S, a, v, b0, nb);
 #pragma unroll 1
-      for (int j = 0; j < nb; ++j) {
-        const int4 rc = S.rect[j];
-        if (rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1) continue;  // wave-uniform
+      for (unsigned long long m = meets_wave(S, pb, nb); m; m &= m - 1) {
+        const int j = __builtin_ctzll(m);
         const float4 r0 = S.rec[j][0], r1 = S.rec[j][1], r2 = S.rec[j][2];
         const float4 r3 = S.rec[j][3], r4 = S.rec[j][4], r5 = S.rec[j][5];
         const double* dqj = disc_coef_of(S, a, v, j);
@@ -419,26 +455,12 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
           const bool gh = pair_geom(r0, r1, r2, r3, r4, r5, pb.pxc[q], pb.pyc[q], g[q], dqj);
           hit[q] = !done[q] && gh;
           any |= hit[q];
-          Q[q] = 0.f;
           if (COUNT) tpairs += hit[q] ? 1u : 0u;
         }
         if (__ballot(any) == 0) continue;  // wave-uniform skip
-        const float* tabf = reinterpret_cast<const float*>(S.tab[j]);
         // all lanes run the unit loop; misses are masked after it
-#pragma unroll 4
-        for (int k = 0; k < N; ++k) {
-          const float4 w = S.tab[j][k];
-          const float w2 = tabf[4 * N + k];
-#pragma unroll
-          for (int q = 0; q < PPL; ++q) {
-            const float ph = __builtin_fmaf(w.x, g[q].p0, __builtin_fmaf(w.y, g[q].p1, __builtin_fmaf(w.z, g[q].p2, w.w)));
-            const float hv = __builtin_fmaf(w.x, g[q].e0, __builtin_fmaf(w.y, g[q].e1, w.z * g[q].e2));
-            const float c = cos_rev(ph);
-            const float sn = sinc_rev(sin_rev(hv), hv);
-            Q[q] = __builtin_fmaf(w2 * c, sn, Q[q]);
-          }
-        }
-        const float b2 = tabf[5 * N];
+        unit_sum<N, PPL>(S.tab[j], g, Q);
+        const float b2 = reinterpret_cast<const float*>(S.tab[j])[5 * N];
         float ahat[PPL];
 #pragma unroll
         for (int q = 0; q < PPL; ++q) ahat[q] = 2.f * pb.L[q] * g[q].H * (Q[q] + b2);
@@ -639,46 +661,6 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_gauss_kernel(RasterA
 // ---------------------------------------------------------------------------
 // backward
 // ---------------------------------------------------------------------------
-// sum over each row of 16 lanes; every lane of the row ends with its row's sum
-__device__ __forceinline__ float dpp_row_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));  // row_half_mirror
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false));  // row_mirror
-  return v;
-}
-
-// adds the wave's sum of v into an LDS accumulator: row sums, then one LDS
-// atomic per row (4 lanes)
-__device__ __forceinline__ void wave_accumulate(float* slot, float v, int lane) {
-  v = dpp_row_sum(v);
-  if ((lane & 15) == 0) atomicAdd(slot, v);
-}
-
-// five sums at once (interleaved, so the DPP steps of one value fill the
-// hazard slots of the others): a[0..3] += (x, y, z, w), b[0] += u
-__device__ __forceinline__ void wave_accumulate5(float* a, float* b, float x, float y, float z, float w, float u,
-                                                 int lane) {
-#define SNP_DPP_STEP(CTRL)                                                                          \
-  x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false)); \
-  y += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(y), CTRL, 0xF, 0xF, false)); \
-  z += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(z), CTRL, 0xF, 0xF, false)); \
-  w += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(w), CTRL, 0xF, 0xF, false)); \
-  u += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u), CTRL, 0xF, 0xF, false));
-  SNP_DPP_STEP(0xB1)
-  SNP_DPP_STEP(0x4E)
-  SNP_DPP_STEP(0x141)
-  SNP_DPP_STEP(0x140)
-#undef SNP_DPP_STEP
-  if ((lane & 15) == 0) {
-    atomicAdd(a + 0, x);
-    atomicAdd(a + 1, y);
-    atomicAdd(a + 2, z);
-    atomicAdd(a + 3, w);
-    atomicAdd(b, u);
-  }
-}
-
 // Transposed butterfly over the 16 lanes of a row.  One level combines two
 // registers a, b across partner lanes: a lane whose selector bit is set keeps
 // b and sends a, its partner keeps a and sends b, and each adds what it
@@ -731,6 +713,64 @@ __device__ __forceinline__ float cross_rows_pair(float a, float b) {
   const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(w), __float_as_uint(w), false, false);
   return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
+
+// The two row levels whose selector is a bank of four lanes: the DPP add
+// writes only the banks that keep its operand, so combining two registers
+// takes two adds and no selects (a select costs 1.5 adds).  Level 1 has the
+// partners lane ^ 7 (row_half_mirror) and keeps the first register in banks 0
+// and 2, level 2 the partners lane ^ 8 (row_ror:8) and banks 0 and 1.  The
+// instructions write part of their destination, which the compiler's DPP
+// builtins cannot express for an add; the waits before the first DPP read are
+// the two states the hardware asks for after a VALU write.
+#define SNP_HM(a, b)                                                             \
+  "v_add_f32_dpp " a ", " a ", " a " row_half_mirror row_mask:0xf bank_mask:0x5\n\t" \
+  "v_add_f32_dpp " a ", " b ", " b " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+#define SNP_R8(a, b)                                                      \
+  "v_add_f32_dpp " a ", " a ", " a " row_ror:8 row_mask:0xf bank_mask:0x3\n\t" \
+  "v_add_f32_dpp " a ", " b ", " b " row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+
+// v8: the terms (0, 0', 1, 1', 2, 2', 3, 3') of a unit pair, v2 its sW2 terms;
+// both levels of the former (into v8[0]: terms 0 and 1, v8[4]: terms 2 and 3),
+// the first of the latter (into v2[0])
+__device__ __forceinline__ void row_levels_pair(float (&v8)[8], float (&v2)[2]) {
+  asm("s_nop 1\n\t"  //
+      SNP_HM("%0", "%5") SNP_HM("%1", "%6") SNP_HM("%2", "%7") SNP_HM("%3", "%8") SNP_HM("%4", "%9")
+      SNP_R8("%0", "%1") SNP_R8("%2", "%3") "s_nop 0"
+      : "+v"(v8[0]), "+v"(v8[2]), "+v"(v8[4]), "+v"(v8[6]), "+v"(v2[0])
+      : "v"(v8[1]), "v"(v8[3]), "v"(v8[5]), "v"(v8[7]), "v"(v2[1]));
+}
+
+// both levels of 16 values: R[4 i] ends with the sums of R[4 i .. 4 i + 3]
+__device__ __forceinline__ void row_levels_16(float* R) {
+  asm("s_nop 1\n\t"  //
+      SNP_HM("%0", "%8") SNP_HM("%1", "%9") SNP_HM("%2", "%10") SNP_HM("%3", "%11")
+      SNP_HM("%4", "%12") SNP_HM("%5", "%13") SNP_HM("%6", "%14") SNP_HM("%7", "%15")
+      SNP_R8("%0", "%1") SNP_R8("%2", "%3") SNP_R8("%4", "%5") SNP_R8("%6", "%7") "s_nop 1"
+      : "+v"(R[0]), "+v"(R[2]), "+v"(R[4]), "+v"(R[6]), "+v"(R[8]), "+v"(R[10]), "+v"(R[12]), "+v"(R[14])
+      : "v"(R[1]), "v"(R[3]), "v"(R[5]), "v"(R[7]), "v"(R[9]), "v"(R[11]), "v"(R[13]), "v"(R[15]));
+}
+
+// both levels of a, b, c: banks 0, 1 end with a, b, banks 2, 3 with c
+__device__ __forceinline__ float row_levels_3(float a, float b, float c) {
+  asm("s_nop 1\n\t"  //
+      "v_add_f32_dpp %1, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      SNP_HM("%0", "%2")
+      "s_nop 1\n\t"
+      SNP_R8("%0", "%1") "s_nop 1"
+      : "+v"(a), "+v"(c)
+      : "v"(b));
+  return a;
+}
+
+__device__ __forceinline__ float row_level_ror8(float a, float b) {
+  asm("s_nop 1\n\t"  //
+      SNP_R8("%0", "%1") "s_nop 1"
+      : "+v"(a)
+      : "v"(b));
+  return a;
+}
+#undef SNP_HM
+#undef SNP_R8
 
 // d/dh of sin(2 pi h)/h near h = 0 is -(2 pi)^3 h / 3 + (2 pi)^5 h^3 / 30
 // (the next term, (2 pi)^7 h^5 / 840, is below float rounding for
@@ -876,13 +916,27 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // unclamped ("live", it carries gradient) is appended to the instance's list
 // in LDS with its pixel, d loss / d Q and d loss / d H.
 //
-// Phase 2 (one live pair per lane): the waves take chunks of 64 list entries
-// (instance by instance, round robin over the waves), recompute the pair's
-// geometry -- with the float64 discriminant near the silhouette -- and the
-// per-unit terms, and sum the gradients of the table entries and of the
-// record coefficients over the wave into LDS accumulators, flushed to HBM
-// once per batch.  Every lane of phase 2 carries gradient, and each wave
-// reduction covers 64 live pairs.
+// Phase 2 (one live pair per lane): the waves take chunks of four rows of 16
+// list entries (round robin over the waves; a row belongs to one instance),
+// recompute the pair's geometry -- with the float64 discriminant near the
+// silhouette -- and the per-unit terms, and sum the gradients of the table
+// entries and of the record coefficients over the rows into LDS accumulators,
+// flushed to HBM once per batch.
+//
+// What bounds it: the vector ALU (its instructions' own issue times add up to
+// the kernel's time), so phase 2 counts instructions: rows rather than whole
+// waves per instance fill the lanes (an instance has 60 live pairs in a 16 x
+// 16 tile at 200k primitives and 800 x 800 pixels, 18 at 3k primitives and
+// 200 x 117), and the row levels of the sums take DPP adds without selects.
+// With one instance per chunk the sums are finished across the rows: four
+// rows adding to one LDS address took 60.4 ms where this takes 47.4.  Against
+// one instance per 64-lane chunk and select-based levels: 48.4 -> 46.0 ms (4
+// mixed views, 200k primitives, N = 16), 4.55 -> 4.10 ms (800 x 800, 100k,
+// N = 8), 0.61 -> 0.44 ms (3 small views, 3001 primitives, N = 16).
+//
+// Waves per SIMD: 5 at N >= 16 (46.0 against 48.3 ms with 4, although 16
+// registers spill at 5); 4 at N <= 8, where the spilled part is a larger share
+// of a chunk (4.10 against 4.30 ms).
 //
 // With the per-ray colour network (CD > 0, colour mode 4) phase 1 evaluates
 // each pair's colour, lists every pair that blends (alpha > 0) with its
@@ -892,10 +946,13 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // record gradient, and the entry point's and direction's gradients into the
 // geometry chain.
 template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0>
-__global__ void __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(CD > 0 ? 4 : 5)))
+__global__ void __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 ? 4 : 5)))
 render_bwd_kernel(RasterArgs a) {
   constexpr int NT = TW * TH;
   constexpr int NW = NT / 64;
+  // chunks of phase 2 take rows of different instances (the per-ray colour
+  // network's sums go to global memory once per chunk, so it takes one instance)
+  constexpr bool PACK = CD == 0;
   constexpr int TS = 5 * N + 4;
   constexpr int ACC = TS + kGViewFloats;  // per instance: table grads, then record grads
   __shared__ Stage<N, NB> S;
@@ -910,7 +967,7 @@ render_bwd_kernel(RasterArgs a) {
   __shared__ ColourStage<(CD > 0 ? CD : 1), (CD > 0 ? NB : 1)> CS;
   __shared__ float s_wt[CD > 0 ? NB : 1][CD > 0 ? NT : 1];  // alpha T of each listed pair
   __shared__ int s_item;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // selector bits and value index of the transposed row reductions
   const bool sel1 = lane & 4, sel2 = lane & 1, sel3 = lane & 2, sel4 = lane & 8;
   const int idx16 = 8 * ((lane >> 3) & 1) + 4 * ((lane >> 1) & 1) + 2 * (lane & 1) + ((lane >> 2) & 1);
@@ -953,47 +1010,11 @@ render_bwd_kernel(RasterArgs a) {
       else
         stage_batch<N, NT, NB>(S, a, v, b0, nb);
       // ---------------- phase 1: pixels ----------------
-      // One instance for this thread's pixel.  `cached`: the integral comes
-      // from the forward's store (ahc) instead of the density MLP.
-      auto pixel_step = [&](const int j, const bool cached, const float ahc) {
-        const int4 rc = S.rect[j];
-        if (rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1) return;  // wave-uniform
-        const float4 r0 = S.rec[j][0], r1 = S.rec[j][1], r2 = S.rec[j][2];
-        const float4 r3 = S.rec[j][3], r4 = S.rec[j][4], r5 = S.rec[j][5];
-        PairGeom g;
-        const bool gh = pair_geom(r0, r1, r2, r3, r4, r5, pb.pxc[0], pb.pyc[0], g, disc_coef_of(S, a, v, j));
-        const bool hit = !done && gh;
-        if (__ballot(hit) == 0) return;  // wave-uniform
-        float ahat, QB = 0.f;  // QB = Q + b2 (recomputed path only)
-        if (cached) {
-          ahat = ahc;
-        } else {
-          const float* tabf = reinterpret_cast<const float*>(S.tab[j]);
-          float Q = 0.f;
-#pragma unroll 4
-          for (int k = 0; k < N; ++k) {
-            const float4 w = S.tab[j][k];
-            const float w2 = tabf[4 * N + k];
-            const float ph = __builtin_fmaf(w.x, g.p0, __builtin_fmaf(w.y, g.p1, __builtin_fmaf(w.z, g.p2, w.w)));
-            const float hv = __builtin_fmaf(w.x, g.e0, __builtin_fmaf(w.y, g.e1, w.z * g.e2));
-            const float c = cos_rev(ph);
-            const float sn = sinc_rev(sin_rev(hv), hv);
-            Q = __builtin_fmaf(w2 * c, sn, Q);
-          }
-          QB = Q + tabf[5 * N];
-          ahat = 2.f * pb.L[0] * g.H * QB;
-        }
-        // the pair's colour (the per-ray network's, as in the forward)
-        float c0 = r2.w, c1 = r3.w, c2 = r4.w;
-        if constexpr (CD > 0) {
-          float sg[3];
-          const float iL = fast_rcp(pb.L[0]);
-          ray_colour<CD>(reinterpret_cast<const float*>(CS.t[j]), reinterpret_cast<const float*>(CS.b[j]),
-                         g.p0 - g.e0, g.p1 - g.e1, g.p2 - g.e2, g.d0 * iL, g.d1 * iL, g.d2 * iL, sg);
-          c0 += sg[0];
-          c1 += sg[1];
-          c2 += sg[2];
-        }
+      // Blends instance j into this thread's pixel: T, the behind colour, the
+      // colour gradient, and the pair's entry in the live list.  c: the pair's
+      // colour; cached: the integral was read back, else QB = Q + b2 is given.
+      auto pixel_blend = [&](const int j, const bool hit, const float ahat, const float H, const bool cached,
+                             const float QB, const float c0, const float c1, const float c2) {
         // Without branches: a lane whose pixel does not blend this pair (a
         // miss, a terminated pixel, an alpha_min skip) takes alpha = 0, which
         // leaves T, the behind colour and every sum exactly as they were
@@ -1010,22 +1031,21 @@ render_bwd_kernel(RasterArgs a) {
         // live: positive, unclamped integral
         const bool gl = blend && ahat > 0.f && al < a.alpha_max;
         const float G = G0 * (c0 * ta - B0) + G1 * (c1 * ta - B1) + G2 * (c2 * ta - B2);
-        const float wq = gl ? G * 2.f * pb.L[0] * g.H : 0.f;  // d loss / d Q
+        const float wq = gl ? G * 2.f * pb.L[0] * H : 0.f;  // d loss / d Q
         // d loss / d H (direct) = G 2 L (Q + b2); from the stored integral
         // alpha-hat = 2 L H (Q + b2) when cached (H > 0 for a hit)
-        const float gH = gl ? (cached ? G * ahat * fast_rcp(g.H) : G * 2.f * pb.L[0] * QB) : 0.f;
+        const float gH = gl ? (cached ? G * ahat * fast_rcp(H) : G * 2.f * pb.L[0] * QB) : 0.f;
         // with the per-ray colour every blending pair is listed: its colour
         // gradient is G_c alpha T
         const bool live = (CD > 0 && al > 0.f) || wq != 0.f || gH != 0.f;
         T = ta;
         done = done || T < a.t_eps;
-        // colour gradient: one transposed reduction of the three sums (with
-        // the per-ray colour, phase 2 sums it)
+        // colour gradient: one transposed reduction of the three sums, finished
+        // across the rows (four lanes adding to one LDS address cost more than
+        // the two swaps; with the per-ray colour, phase 2 sums it)
         if constexpr (CD == 0) {
-          const float z = nb_level<kDppRor8>(nb_level<kDppXor2>(
-              tb_level<kDppXor1>(tb_level<kDppHalfMirror>(gc0, gc1, sel1), tb_level<kDppHalfMirror>(gc2, 0.f, sel1), sel2)));
-          const int i4 = idx16 & 3;
-          if (!sel3 && !sel4 && i4 < 3) atomicAdd(s_acc[j] + TS + 18 + i4, z);
+          const float z = cross_rows_sum(nb_level<kDppXor2>(nb_level<kDppXor1>(row_levels_3(gc0, gc1, gc2))));
+          if (lane < 12 && (lane & 3) == 0) atomicAdd(s_acc[j] + TS + 18 + (lane >> 2), z);
         }
         // each wave appends to its own 64 slots of the instance's list (a
         // wave meets an instance once per batch), so no atomic is needed
@@ -1043,40 +1063,104 @@ render_bwd_kernel(RasterArgs a) {
           if (lane == 0) s_cnt[j][wave] = (uint32_t)__popcll(lm);
         }
       };
-      if (a.ahat_cache && (int64_t)(b0 + nb) <= a.cache_instances) {
+      // One instance for this thread's pixel.  `cached`: the integral comes
+      // from the forward's store (ahc) instead of the density MLP.
+      auto pixel_step = [&](const int j, const bool cached, const float ahc) {
+        const float4 r0 = S.rec[j][0], r1 = S.rec[j][1], r2 = S.rec[j][2];
+        const float4 r3 = S.rec[j][3], r4 = S.rec[j][4], r5 = S.rec[j][5];
+        PairGeom g[1];
+        const bool gh = pair_geom(r0, r1, r2, r3, r4, r5, pb.pxc[0], pb.pyc[0], g[0], disc_coef_of(S, a, v, j));
+        const bool hit = !done && gh;
+        if (__ballot(hit) == 0) return;  // wave-uniform
+        float ahat, QB = 0.f;  // QB = Q + b2 (recomputed path only)
+        if (cached) {
+          ahat = ahc;
+        } else {
+          float Q[1];
+          unit_sum<N, 1>(S.tab[j], g, Q);
+          QB = Q[0] + reinterpret_cast<const float*>(S.tab[j])[5 * N];
+          ahat = 2.f * pb.L[0] * g[0].H * QB;
+        }
+        // the pair's colour (the per-ray network's, as in the forward)
+        float c0 = r2.w, c1 = r3.w, c2 = r4.w;
+        if constexpr (CD > 0) {
+          float sg[3];
+          const float iL = fast_rcp(pb.L[0]);
+          ray_colour<CD>(reinterpret_cast<const float*>(CS.t[j]), reinterpret_cast<const float*>(CS.b[j]),
+                         g[0].p0 - g[0].e0, g[0].p1 - g[0].e1, g[0].p2 - g[0].e2, g[0].d0 * iL, g[0].d1 * iL,
+                         g[0].d2 * iL, sg);
+          c0 += sg[0];
+          c1 += sg[1];
+          c2 += sg[2];
+        }
+        pixel_blend(j, hit, ahat, g[0].H, cached, QB, c0, c1, c2);
+      };
+      // the batch's integrals come from the forward's store
+      const bool cached = a.ahat_cache && (int64_t)(b0 + nb) <= a.cache_instances;
+      const float* cp = a.ahat_cache + (int64_t)b0 * NT + pb.loc[0];
+      if (cached) {
         // the forward's integrals of this batch, fetched together (only for
         // instances whose rectangle meets this wave's pixels)
         float pre[NB];
-        const float* cp = a.ahat_cache + (int64_t)b0 * NT + pb.loc[0];
-        const bool wave_live = __ballot(!done) != 0;
+        const uint32_t m = __ballot(!done) != 0 ? (uint32_t)meets_wave(S, pb, nb) : 0u;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) pre[j] = (m >> j) & 1u ? cp[(int64_t)j * NT] : 0.f;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
-          pre[j] = 0.f;
-          if (j < nb && wave_live) {
-            const int4 rc = S.rect[j];
-            if (!(rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1)) pre[j] = cp[(int64_t)j * NT];
-          }
+          // a pair without a positive integral changes nothing (alpha 0, no
+          // gradient), so an instance without one in the wave is left out
+          // before its geometry (the store keeps stale values where the
+          // forward's wave met nothing, which then fail the hit test)
+          if (((m >> j) & 1u) && __ballot(pre[j] > 0.f && !done) != 0) pixel_step(j, true, pre[j]);
         }
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-          if (j < nb) pixel_step(j, true, pre[j]);
       } else {
-        for (int j = 0; j < nb; ++j) pixel_step(j, false, 0.f);
+        for (uint32_t m = (uint32_t)meets_wave(S, pb, nb); m; m &= m - 1) pixel_step(__builtin_ctz(m), false, 0.f);
       }
       __syncthreads();
       // ---------------- phase 2: live pairs ----------------
-      int it = 0;
-      for (int j = 0; j < nb; ++j) {
-        // the list is the waves' regions in order: entry e lies in region w
-        // with wstart[w] <= e < wstart[w + 1], at slot 64 w + e - wstart[w]
-        uint32_t wstart[NW + 1];
-        wstart[0] = 0;
+      // rows: 16 pairs of one instance; the batch's rows are numbered instance
+      // by instance (rend[j]: rows of instances 0..j), four to a chunk
+      uint32_t rows = 0;
+      if (lane < NB) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) wstart[w + 1] = wstart[w] + s_cnt[j][w];
-        const uint32_t cnt = wstart[NW];
-        for (uint32_t c0 = 0; c0 < cnt; c0 += 64, ++it) {
-          if (it % NW != wave) continue;  // wave-uniform
-          const uint32_t e = c0 + lane;
+        for (int w = 0; w < NW; ++w) rows += s_cnt[lane][w];
+        rows = PACK ? (rows + 15) / 16 : (rows + 63) / 64 * 4;
+      }
+      uint32_t rsum = rows;
+#pragma unroll
+      for (int o = 1; o < NB; o <<= 1) {
+        const uint32_t y = __shfl_up(rsum, o);
+        if (lane >= o) rsum += y;
+      }
+      // (lanes past the last instance repeat its end)
+      const uint32_t total = __builtin_amdgcn_readlane(rsum, NB - 1);
+      for (uint32_t q0 = 4 * wave; q0 < total; q0 += 4 * NW) {
+        {
+          // this row's instance: the number of instances that end at or before
+          // it, counted over the lanes for each of the chunk's rows (rows past
+          // the last one repeat it, without pairs)
+          const int myrow = PACK ? lane >> 4 : 0;
+          int j = 0;
+          uint32_t rbase = 0;
+#pragma unroll
+          for (int r = 0; r < (PACK ? 4 : 1); ++r) {
+            const uint32_t row = q0 + r < total ? q0 + r : total - 1;
+            const int jr = __builtin_popcountll(__ballot(lane < NB && rsum <= row));
+            const uint32_t br = jr > 0 ? __builtin_amdgcn_readlane(rsum, jr - 1) : 0u;
+            j = myrow >= r ? jr : j;
+            rbase = myrow >= r ? br : rbase;
+          }
+          const uint32_t row = q0 + myrow;
+          const uint32_t e = 16 * (row - rbase) + (PACK ? lane & 15 : lane);
+          // one instance in the whole chunk: its sums are finished across the rows
+          const bool same = !PACK || __builtin_amdgcn_readfirstlane(j) == __builtin_amdgcn_readlane(j, 63);
+          // the list is the waves' regions in order: entry e lies in region w
+          // with wstart[w] <= e < wstart[w + 1], at slot 64 w + e - wstart[w]
+          uint32_t wstart[NW + 1];
+          wstart[0] = 0;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) wstart[w + 1] = wstart[w] + s_cnt[j][w];
+          const uint32_t cnt = wstart[NW];
           const bool act = e < cnt;
           uint32_t slot = e;
 #pragma unroll
@@ -1091,7 +1175,7 @@ render_bwd_kernel(RasterArgs a) {
           const float4 r0 = S.rec[j][0], r1 = S.rec[j][1], r2 = S.rec[j][2];
           const float4 r3 = S.rec[j][3], r4 = S.rec[j][4], r5 = S.rec[j][5];
           PairGeom G;
-          const double* dqj = disc_coef_of(S, a, v, j);
+          const double* dqj = a.disc_coef + ((int64_t)v * a.P + S.id[j]) * 6;
           const bool gh = pair_geom<true>(r0, r1, r2, r3, r4, r5, pxc, pyc, G, dqj);
           if (!gh) {  // float64 discriminant says the ray misses: no gradient
             wq = 0.f;
@@ -1105,17 +1189,19 @@ render_bwd_kernel(RasterArgs a) {
           float* acc = s_acc[j];
           float gp0 = 0.f, gp1 = 0.f, gp2 = 0.f, ge0 = 0.f, ge1 = 0.f, ge2 = 0.f;
           // Units in groups of eight (four when N = 4), one unit pair per
-          // iteration.  A pair's eight terms (sWx, sWy, sWz, gph of both units)
-          // take three transposed row levels and its two sW2 terms one; the
-          // second pair of four units completes a 16-value row reduction
-          // (lane: term 2 b1 + b0 of unit 2 b3 + b2), and the last pair of a
-          // group finishes the sums across the rows with the row swaps, after
-          // which each LDS address receives exactly one lane's sum.  y_prev,
+          // iteration.  A pair's ten terms (sWx, sWy, sWz, gph and sW2 of both
+          // units) take the row levels one by one as values to combine arrive:
+          // lane bit 2 the unit of the pair, bit 3 the term's low bit, bit 0 its
+          // high bit, bit 1 the unit pair of four units (sW2: bit 3 the pair of
+          // four, bit 0 the four of eight).  With one instance in the chunk the
+          // row swaps finish the sums across the rows, so that each LDS address
+          // receives one lane's sum; otherwise each row adds its own.  y_prev,
           // s_prev carry the previous pair, z_prev, q_prev the previous four units.
           constexpr int GU = N >= 8 ? 8 : 4;
-          const int tl = 2 * ((lane >> 1) & 1) + (lane & 1);         // term of this lane
-          const int ul = 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);  // unit in its group of four
-          float y_prev = 0.f, s_prev = 0.f, z_prev = 0.f, q_prev = 0.f;
+          const int tl = 2 * (lane & 1) + ((lane >> 3) & 1);         // term of this lane
+          const int ul = 2 * ((lane >> 1) & 1) + ((lane >> 2) & 1);  // unit in its group of four
+          const int sl = 4 * (lane & 1) + 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);  // sW2's unit of eight
+          float y_prev, s_prev, z_prev, q_prev;  // each set before its first use (pi 0, then 1)
 #pragma unroll 1
           for (int k0 = 0; k0 < N; k0 += 2) {
             float v8[8], v2[2];
@@ -1150,36 +1236,42 @@ render_bwd_kernel(RasterArgs a) {
               ge1 = __builtin_fmaf(ghv, w.y, ge1);
               ge2 = __builtin_fmaf(ghv, w.z, ge2);
             }
-            const float x0 = tb_level<kDppXor1>(tb_level<kDppHalfMirror>(v8[0], v8[1], sel1),
-                                                tb_level<kDppHalfMirror>(v8[2], v8[3], sel1), sel2);
-            const float x1 = tb_level<kDppXor1>(tb_level<kDppHalfMirror>(v8[4], v8[5], sel1),
-                                                tb_level<kDppHalfMirror>(v8[6], v8[7], sel1), sel2);
-            const float y = tb_level<kDppXor2>(x0, x1, sel3);
-            const float s2 = tb_level<kDppHalfMirror>(v2[0], v2[1], sel1);
+            row_levels_pair(v8, v2);  // v8[0]: terms 0, 1; v8[4]: terms 2, 3; v2[0]: sW2
+            const float y = tb_level<kDppXor1>(v8[0], v8[4], sel2);
+            const float s2 = v2[0];
             const int pi = (k0 >> 1) & (GU / 2 - 1);  // pair within the group (wave-uniform)
             if ((pi & 1) == 0) {
               y_prev = y;
               s_prev = s2;
               continue;
             }
-            const float z = tb_level<kDppRor8>(y_prev, y, sel4);
-            const float q = tb_level<kDppXor1>(s_prev, s2, sel2);  // unit 2 b0 + b2 of the four
-            const int g = k0 & ~(GU - 1);
-            if (GU == 8 && pi == 1) {
-              z_prev = z;
-              q_prev = q;
-              continue;
-            }
-            if (GU == 8) {
-              const float zz = cross_rows_pair(z_prev, z);  // rows 0, 1: first four units; rows 2, 3: second
-              if ((lane & 16) == 0) atomicAdd(acc + 4 * (g + 4 * (lane >> 5) + ul) + tl, zz);
-              const float q8 = cross_rows_sum(nb_level<kDppRor8>(tb_level<kDppXor2>(q_prev, q, sel3)));
-              if (lane < 8) atomicAdd(acc + 4 * N + g + (idx16 & 7), q8);
-            } else {
+            const float z = tb_level<kDppXor2>(y_prev, y, sel3);
+            const float q = row_level_ror8(s_prev, s2);
+            const int g = k0 & ~3;  // first of these four units
+            if (!same) {
+              atomicAdd(acc + 4 * (g + ul) + tl, z);
+              if (GU == 4) {
+                const float q4 = nb_level<kDppXor2>(nb_level<kDppXor1>(q));
+                if ((lane & 3) == 0) atomicAdd(acc + 4 * N + g + sl, q4);
+              } else if (pi == 1) {
+                q_prev = q;
+              } else {
+                const float q8 = nb_level<kDppXor2>(tb_level<kDppXor1>(q_prev, q, sel2));
+                if ((lane & 2) == 0) atomicAdd(acc + 4 * N + g - 4 + sl, q8);
+              }
+            } else if (GU == 4) {
               const float zz = cross_rows_sum(z);
               if (lane < 16) atomicAdd(acc + 4 * (g + ul) + tl, zz);
-              const float q4 = cross_rows_sum(nb_level<kDppRor8>(nb_level<kDppXor2>(q)));
-              if (lane < 8 && !sel3) atomicAdd(acc + 4 * N + g + (idx16 & 3), q4);
+              const float q4 = cross_rows_sum(nb_level<kDppXor2>(nb_level<kDppXor1>(q)));
+              if (lane < 16 && (lane & 3) == 0) atomicAdd(acc + 4 * N + g + sl, q4);
+            } else if (pi == 1) {
+              z_prev = z;
+              q_prev = q;
+            } else {
+              const float zz = cross_rows_pair(z_prev, z);  // rows 0, 1: first four units; rows 2, 3: second
+              if ((lane & 16) == 0) atomicAdd(acc + 4 * (g - 4 + 4 * (lane >> 5) + ul) + tl, zz);
+              const float q8 = cross_rows_sum(nb_level<kDppXor2>(tb_level<kDppXor1>(q_prev, q, sel2)));
+              if (lane < 16 && (lane & 2) == 0) atomicAdd(acc + 4 * N + g - 4 + sl, q8);
             }
           }
           // The colour network's adjoint (per-ray colour) comes first, while
@@ -1237,15 +1329,15 @@ render_bwd_kernel(RasterArgs a) {
             ge2 -= gu[2];
           }
           float R[18];
-#pragma unroll
-          for (int r = 0; r < 18; ++r) R[r] = 0.f;
-          if (wq != 0.f || gHd != 0.f || wtp != 0.f) {
+          {
             const float gHt = gHd + ge0 * G.d0 + ge1 * G.d1 + ge2 * G.d2;
             float gd0 = __builtin_fmaf(gn[0], iLp, ge0 * G.H), gd1 = __builtin_fmaf(gn[1], iLp, ge1 * G.H),
                   gd2 = __builtin_fmaf(gn[2], iLp, ge2 * G.H);
             const float gX0 = gp0 * G.rA, gX1 = gp1 * G.rA, gX2 = gp2 * G.rA;
             const float gA_p = -(gp0 * G.p0 + gp1 * G.p1 + gp2 * G.p2) * G.rA;
-            const float gdisc = gHt * G.rA * 0.5f * fast_rcp(G.sq);
+            // a lane without a pair, or a miss, has zero gradients everywhere and
+            // sqrt(disc) = 0: its reciprocal is left out, so that 0 stays 0
+            const float gdisc = gHt * G.rA * 0.5f * (G.sq > 0.f ? fast_rcp(G.sq) : 0.f);
             const float gA = gdisc - gHt * G.H * G.rA + gA_p;
             const float gM = -gdisc;
             gd0 += 2.f * gA * G.d0 + (G.m1 * gX2 - G.m2 * gX1);
@@ -1274,21 +1366,23 @@ render_bwd_kernel(RasterArgs a) {
             R[17] = gm2 * G.dy;
           }
           {
-            // record coefficients 0..15: one full transposed reduction
-            float x4[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              x4[q] = tb_level<kDppXor1>(tb_level<kDppHalfMirror>(R[4 * q], R[4 * q + 1], sel1),
-                                         tb_level<kDppHalfMirror>(R[4 * q + 2], R[4 * q + 3], sel1), sel2);
-            const float z = cross_rows_sum(tb_level<kDppRor8>(tb_level<kDppXor2>(x4[0], x4[1], sel3),
-                                                              tb_level<kDppXor2>(x4[2], x4[3], sel3), sel4));
-            if (lane < 16) atomicAdd(acc + TS + idx16, z);
-            // coefficients 16, 17 and the b2 gradient (sum of d loss / d Q)
-            const float t4 = cross_rows_sum(nb_level<kDppRor8>(nb_level<kDppXor2>(
-                tb_level<kDppXor1>(tb_level<kDppHalfMirror>(R[16], R[17], sel1),
-                                   tb_level<kDppHalfMirror>(wq, 0.f, sel1), sel2))));
-            const int i4 = idx16 & 3;
-            if (lane < 8 && !sel3 && i4 < 3) atomicAdd(i4 == 2 ? acc + 5 * N : acc + TS + 16 + i4, t4);
+            // record coefficients 0..15: one full transposed reduction over the
+            // row (lane: coefficient 8 b1 + 4 b0 + 2 b3 + b2); then 16, 17 and
+            // the b2 gradient (the sum of d loss / d Q)
+            row_levels_16(R);  // R[0], R[4], R[8], R[12]: four sums each
+            float z = tb_level<kDppXor2>(tb_level<kDppXor1>(R[0], R[4], sel2),
+                                         tb_level<kDppXor1>(R[8], R[12], sel2), sel3);
+            float t4 = nb_level<kDppXor2>(nb_level<kDppXor1>(row_levels_3(R[16], R[17], wq)));
+            const int zl = 8 * ((lane >> 1) & 1) + 4 * (lane & 1) + 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);
+            const int i4 = (lane >> 2) & 3;  // 0, 1: coefficients 16, 17; 2: b2
+            if (same) {
+              z = cross_rows_sum(z);
+              t4 = cross_rows_sum(t4);
+            }
+            if (!same || lane < 16) {
+              atomicAdd(acc + TS + zl, z);
+              if ((lane & 3) == 0 && i4 < 3) atomicAdd(i4 == 2 ? acc + 5 * N : acc + TS + 16 + i4, t4);
+            }
           }
         }
       }
