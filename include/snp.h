@@ -141,9 +141,9 @@ typedef struct {
  *             give the same arrays bit for bit.  1 = the (view, primitive)
  *             pairs are sorted by depth first, instances are emitted in that
  *             order and sorted by their tile bits only (fewer passes over
- *             the instances, a few more launches); 2 = instances emitted in
- *             primitive order and sorted by the whole key; 0 = 1 when
- *             V * P >= 2^16, else 2.
+ *             the instances); 2 = instances emitted in primitive order and
+ *             sorted by the whole key; 0 = as 1, but when V * P < 2^16 with
+ *             the workspace size and counters of 2.
  *  time       xi_t in [0, 1] of the dynamic-scene application: with
  *             prims.wt the phase of hidden unit k is omega0 (W1_k x + b1_k) +
  *             time * wt_k (the time term added unscaled, as the paper prints

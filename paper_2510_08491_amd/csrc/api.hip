@@ -16,14 +16,18 @@ struct Plan {
   snp_layout L;
   size_t scan_scratch, sort_scratch, loss_partials, cams_bytes;
   size_t keys_alt, values_alt;
-  size_t dkeys[2], dvals[2], counts_sorted;  // depth sort of the (view, primitive) pairs
-  size_t tkeys[2], tvals[2], tile_n;          // persistent launches: tile order by instance count
+  // depth order of the (view, primitive) pairs: scratch keys and indices, the
+  // order and the tile counts in it
+  size_t dkeys[2], dvals, order, counts_sorted;
+  size_t tile_order, tile_steps;  // persistent launches: tiles by instance count
+  int inst_rounds, pair_rounds;   // block sizes of the radix passes over instances and pairs
+  int64_t depth_reported;         // pairs the depth sort reports in its counter
   std::vector<int32_t> tile_base;
   std::vector<int64_t> pix_base;
   int64_t total_pixels;
   int tile_bits;  // significant bits of the global tile id
-  bool depth_first;  // depth sort of the pairs, then the instances by tile bits only
   bool tile_order_on;  // persistent launches take the tiles by instance count, descending
+  bool depth_first;  // depth sort of the pairs, then the instances by tile bits only
   // colour mode 4: the colour network's table and biases, their gradients,
   // and the rotation / scale gradients handed to the preprocess adjoint
   size_t ctab, cbias, gctab, gcbias, extra_rs;
@@ -100,10 +104,12 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   int tb = 1;
   while (((int64_t)1 << tb) < tiles) ++tb;
   pl->tile_bits = tb;
-  // the heaviest-first order pays for its sort where tiles are expensive (neural
-  // primitives); the Gaussians' cheap tiles do not need it
-  pl->tile_order_on = cfg->persistent != 0 && cfg->primitive == 0;
-  pl->depth_first = cfg->bin_order == 1 || (cfg->bin_order == 0 && (int64_t)V * P >= ((int64_t)1 << 16));
+  // bin_order 0: with few pairs the depth order takes no buffers of its own
+  // (and is not reported); the arrays it leads to are those of bin_order 2
+  const bool few = (int64_t)V * P < ((int64_t)1 << 16);
+  const bool own_buffers = cfg->bin_order == 1 || (cfg->bin_order == 0 && !few);
+  pl->depth_first = cfg->bin_order != 2;
+  pl->depth_reported = own_buffers ? (int64_t)V * P : 0;
   // Gaussians have no density table, float64 discriminants, backward arrays
   // or pair cache
   const bool gs = gaussian(cfg);
@@ -128,30 +134,47 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   L.depth_bits = take(sizeof(uint32_t) * (size_t)VP);
   L.tile_counts = take(sizeof(uint32_t) * (size_t)VP);
   L.offsets = take(sizeof(uint32_t) * (size_t)VP);
-  pl->scan_scratch = take(scan_scratch_bytes(VP));
-  const size_t dn = pl->depth_first ? (size_t)VP : 0;
-  for (int k = 0; k < 2; ++k) {
-    pl->dkeys[k] = take(sizeof(unsigned long long) * dn);
-    pl->dvals[k] = take(sizeof(uint32_t) * dn);
-  }
-  pl->counts_sorted = take(sizeof(uint32_t) * dn);
+  auto take_pairs = [&] {
+    const size_t dn = pl->depth_first ? (size_t)VP : 0, kn = order_small(VP) ? 0 : dn;
+    for (int k = 0; k < 2; ++k) pl->dkeys[k] = take(sizeof(uint32_t) * kn);
+    pl->dvals = take(sizeof(uint32_t) * kn);
+    pl->order = take(sizeof(uint32_t) * dn);
+    pl->counts_sorted = take(sizeof(uint32_t) * dn);
+  };
+  if (own_buffers) take_pairs();
   L.keys = take(sizeof(unsigned long long) * (size_t)cap);
   pl->keys_alt = take(sizeof(unsigned long long) * (size_t)cap);
   L.values = take(sizeof(uint32_t) * (size_t)cap);
   pl->values_alt = take(sizeof(uint32_t) * (size_t)cap);
-  int64_t sort_n = pl->depth_first && VP > cap ? VP : cap;
-  if (pl->tile_order_on && tiles > sort_n) sort_n = tiles;
-  pl->sort_scratch = take(sort_scratch_bytes(sort_n));
   L.ranges = take(sizeof(uint32_t) * 2 * (size_t)tiles);
   L.tile_pairs = take(sizeof(uint32_t) * (size_t)tiles);
-  const size_t tn = pl->tile_order_on ? (size_t)tiles : 0;
-  for (int k = 0; k < 2; ++k) {
-    pl->tkeys[k] = take(sizeof(unsigned long long) * tn);
-    pl->tvals[k] = take(sizeof(uint32_t) * tn);
-  }
-  pl->tile_n = take(sizeof(unsigned long long));
+  // the heaviest-first order pays for its sort where tiles are expensive (neural
+  // primitives); the Gaussians' cheap tiles do not need it
+  pl->tile_order_on = cfg->persistent != 0 && cfg->primitive == 0;
+  pl->tile_order = take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
   L.gview = take(gs ? 0 : sizeof(float) * (size_t)VP * kGViewFloats);
   L.gtable = take(sizeof(float) * (size_t)P * TS);
+  {
+    // what only binning and sorting use lies under the backward's gradient
+    // records and table, which the backward clears before it uses them
+    const size_t end = off, room = gs ? 0 : end;
+    if (!gs) off = L.gview;
+    if (!own_buffers) take_pairs();
+    pl->scan_scratch = take(scan_scratch_bytes(VP));
+    pl->tile_steps = take(pl->tile_order_on ? tile_order_scratch_bytes(tiles) : 0);
+    // smaller blocks take four times the scratch: only where it adds nothing
+    auto rounds_of = [&](int64_t n) {
+      const int r = sort_rounds(n);
+      return r == 16 || gs || off + sort_scratch_bytes(n, r) <= room ? r : 16;
+    };
+    pl->inst_rounds = rounds_of(cap);
+    pl->pair_rounds = rounds_of(VP);
+    size_t sort_bytes = sort_scratch_bytes(cap, pl->inst_rounds);
+    if (pl->depth_first && !order_small(VP))
+      sort_bytes = std::max(sort_bytes, sort_scratch_bytes(VP, pl->pair_rounds));
+    pl->sort_scratch = take(sort_bytes);
+    if (off < end) off = end;
+  }
   {
     const bool rc = cfg->color_mode == 4 && !gs;
     const size_t cts = rc ? (size_t)ray_colour_stride(cfg->cmlp_width, cfg->cmlp_depth) : 0;
@@ -241,7 +264,6 @@ static snp_status do_preprocess(const snp_config* cfg, const snp_prims* pr, int3
   const snp_layout& L = pl.L;
   unsigned long long* counters = wsp<unsigned long long>(ws, L.counters);
   CamDev* cd = wsp<CamDev>(ws, L.cams);
-  SNP_HIP(zero_counters(counters, CNT_COUNT, st));
   for (int v0 = 0; v0 < V; v0 += kMaxCamsPerChunk) {
     CamChunk ch;
     std::memset(&ch, 0, sizeof(ch));
@@ -254,7 +276,7 @@ static snp_status do_preprocess(const snp_config* cfg, const snp_prims* pr, int3
       ch.tile_base[i] = pl.tile_base[v0 + i];
       ch.pix_base[i] = pl.pix_base[v0 + i];
     }
-    SNP_HIP(launch_setup_cams(ch, cd, st));
+    SNP_HIP(launch_setup_cams(ch, cd, counters, st));
   }
   if (!gaussian(cfg))
     SNP_HIP(launch_prim_table(cfg->n_hidden, pr->P, cfg->omega0, cfg->time, *pr, wsp<float>(ws, L.table), counters,
@@ -310,7 +332,6 @@ static snp_status do_preprocess(const snp_config* cfg, const snp_prims* pr, int3
 }
 
 constexpr int kDepthBits = 31;  // positive float32 depth: the sign bit is zero
-constexpr int kTileKeyBits = 16;  // instance count of a tile, saturated, for the work-queue order
 
 // key bits the instance sort orders: the tile bits only when the instances
 // are emitted in depth order, else depth and tile bits
@@ -325,21 +346,23 @@ static snp_status do_bin(const snp_config* cfg, int64_t P, int32_t V, const Plan
   const int64_t VP = (int64_t)V * P;
   const uint32_t* order = nullptr;  // identity: primitive order
   const uint32_t* counts = wsp<uint32_t>(ws, L.tile_counts);
+  uint32_t* offsets = wsp<uint32_t>(ws, L.offsets);
+  unsigned long long* total = counters + CNT_INSTANCES;
   if (pl.depth_first) {
-    unsigned long long* dk0 = wsp<unsigned long long>(ws, pl.dkeys[0]);
-    unsigned long long* dk1 = wsp<unsigned long long>(ws, pl.dkeys[1]);
-    uint32_t* dv0 = wsp<uint32_t>(ws, pl.dvals[0]);
-    uint32_t* dv1 = wsp<uint32_t>(ws, pl.dvals[1]);
-    SNP_HIP(launch_depth_keys(wsp<uint32_t>(ws, L.depth_bits), VP, dk0, dv0, counters + CNT_DEPTH_SORT, st));
-    SNP_HIP(radix_sort(dk0, dv0, dk1, dv1, VP, counters + CNT_DEPTH_SORT, 0, kDepthBits,
-                       wsp<void>(ws, pl.sort_scratch), st));
-    order = radix_passes(kDepthBits) % 2 == 1 ? dv1 : dv0;
     uint32_t* cs = wsp<uint32_t>(ws, pl.counts_sorted);
-    SNP_HIP(launch_gather_counts(order, counts, VP, cs, st));
+    uint32_t* od = wsp<uint32_t>(ws, pl.order);
+    const uint32_t* depth = wsp<uint32_t>(ws, L.depth_bits);
+    if (order_small(VP))
+      SNP_HIP(launch_order_small(depth, counts, VP, od, cs, offsets, total, st));
+    else
+      SNP_HIP(order_pairs(depth, counts, VP, wsp<uint32_t>(ws, pl.dkeys[0]), wsp<uint32_t>(ws, pl.dkeys[1]),
+                          wsp<uint32_t>(ws, pl.dvals), od, cs, pl.pair_rounds, wsp<void>(ws, pl.sort_scratch), st));
+    order = od;
     counts = cs;
   }
-  SNP_HIP(scan_exclusive_u32(counts, wsp<uint32_t>(ws, L.offsets), VP, wsp<void>(ws, pl.scan_scratch),
-                             reinterpret_cast<uint64_t*>(counters + CNT_INSTANCES), st));
+  if (!pl.depth_first || !order_small(VP))
+    SNP_HIP(scan_exclusive_u32(counts, offsets, VP, wsp<void>(ws, pl.scan_scratch),
+                               reinterpret_cast<uint64_t*>(total), st));
   const bool odd = radix_passes(sort_bits(pl)) % 2 == 1;
   EmitArgs ea;
   ea.P = P;
@@ -353,7 +376,9 @@ static snp_status do_bin(const snp_config* cfg, int64_t P, int32_t V, const Plan
   ea.offsets = wsp<uint32_t>(ws, L.offsets);
   ea.keys = wsp<unsigned long long>(ws, odd ? pl.keys_alt : L.keys);
   ea.values = wsp<uint32_t>(ws, odd ? pl.values_alt : L.values);
-  SNP_HIP(launch_emit(ea, counters, st));
+  ea.counters = counters;
+  ea.depth_sorted = pl.depth_reported;
+  SNP_HIP(launch_emit(ea, st));
   (void)cfg;
   return SNP_OK;
 }
@@ -370,21 +395,17 @@ static snp_status do_sort(const Plan& pl, void* ws, hipStream_t st) {
   // passes are stable, which completes the (tile, depth) order
   unsigned long long* n_inst = counters + CNT_INSTANCES;
   void* scr = wsp<void>(ws, pl.sort_scratch);
-  if (odd)
-    SNP_HIP(radix_sort(k_alt, v_alt, k_main, v_main, L.capacity, n_inst, sort_lo(pl), sort_bits(pl), scr, st));
-  else
-    SNP_HIP(radix_sort(k_main, v_main, k_alt, v_alt, L.capacity, n_inst, sort_lo(pl), sort_bits(pl), scr, st));
-  SNP_HIP(launch_ranges(k_main, counters, L.capacity, wsp<uint32_t>(ws, L.ranges), L.total_tiles, st));
-  if (pl.tile_order_on) {
-    // tiles by instance count, descending, for the persistent rasterizers' work queue
-    unsigned long long* tk0 = wsp<unsigned long long>(ws, pl.tkeys[0]);
-    unsigned long long* tk1 = wsp<unsigned long long>(ws, pl.tkeys[1]);
-    uint32_t* tv0 = wsp<uint32_t>(ws, pl.tvals[0]);
-    uint32_t* tv1 = wsp<uint32_t>(ws, pl.tvals[1]);
-    unsigned long long* tn = wsp<unsigned long long>(ws, pl.tile_n);
-    SNP_HIP(launch_tile_keys(wsp<uint32_t>(ws, L.ranges), L.total_tiles, tk0, tv0, tn, st));
-    SNP_HIP(radix_sort(tk0, tv0, tk1, tv1, L.total_tiles, tn, 0, kTileKeyBits, wsp<void>(ws, pl.sort_scratch), st));
+  uint32_t* ranges = wsp<uint32_t>(ws, L.ranges);
+  if (odd) {
+    std::swap(k_main, k_alt);
+    std::swap(v_main, v_alt);
   }
+  SNP_HIP(radix_sort(k_main, v_main, k_alt, v_alt, L.capacity, n_inst, sort_lo(pl), sort_bits(pl),
+                     pl.inst_rounds, scr, ranges, 2 * (int64_t)L.total_tiles, st));
+  SNP_HIP(launch_ranges(wsp<unsigned long long>(ws, L.keys), counters, L.capacity, ranges, st));
+  if (pl.tile_order_on)
+    SNP_HIP(launch_tile_order(ranges, L.total_tiles, wsp<uint32_t>(ws, pl.tile_order),
+                              wsp<uint32_t>(ws, pl.tile_steps), st));
   return SNP_OK;
 }
 
@@ -402,8 +423,7 @@ static RasterArgs raster_args(const snp_config* cfg, int64_t P, int32_t V, const
   a.records = wsp<float>(ws, L.records);
   a.values = wsp<uint32_t>(ws, L.values);
   a.ranges = wsp<uint32_t>(ws, L.ranges);
-  // the sorted tile ids (2 passes over the 16 key bits: back in the first buffer)
-  a.tile_order = pl.tile_order_on ? wsp<uint32_t>(ws, pl.tvals[radix_passes(kTileKeyBits) % 2]) : nullptr;
+  a.tile_order = pl.tile_order_on ? wsp<uint32_t>(ws, pl.tile_order) : nullptr;
   a.rects = wsp<int32_t>(ws, L.rects);
   a.gview = wsp<float>(ws, L.gview);
   a.gtable = wsp<float>(ws, L.gtable);

@@ -68,15 +68,6 @@ hipError_t zero_f32(float* p, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-__global__ void zero_u64_kernel(unsigned long long* p, int n) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0ull;
-}
-
-hipError_t zero_counters(unsigned long long* p, int n, hipStream_t st) {
-  hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(64), 0, st, p, n);
-  return hipGetLastError();
-}
-
 __global__ void zero_one_u64_kernel(unsigned long long* p) { *p = 0ull; }
 
 hipError_t zero_counter(unsigned long long* p, hipStream_t st) {

@@ -34,8 +34,11 @@ namespace snp {
 // ---------------------------------------------------------------------------
 // per-view constants
 // ---------------------------------------------------------------------------
-__global__ void setup_cams_kernel(CamChunk ch, CamDev* out) {
+// (the first chunk also clears the counters)
+__global__ void setup_cams_kernel(CamChunk ch, CamDev* out, unsigned long long* counters) {
   const int i = threadIdx.x;
+  static_assert(CNT_COUNT <= kMaxCamsPerChunk, "one thread per counter");
+  if (ch.first == 0 && i < CNT_COUNT) counters[i] = 0ull;
   if (i >= ch.count) return;
   const snp_camera& c = ch.cam[i];
   CamDev d;
@@ -1027,8 +1030,8 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(PreBwdArgs a) {
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_setup_cams(const CamChunk& ch, CamDev* out, hipStream_t st) {
-  hipLaunchKernelGGL(setup_cams_kernel, dim3(1), dim3(kMaxCamsPerChunk), 0, st, ch, out);
+hipError_t launch_setup_cams(const CamChunk& ch, CamDev* out, unsigned long long* counters, hipStream_t st) {
+  hipLaunchKernelGGL(setup_cams_kernel, dim3(1), dim3(kMaxCamsPerChunk), 0, st, ch, out, counters);
   return hipGetLastError();
 }
 

@@ -242,6 +242,8 @@ struct EmitArgs {
   const uint32_t* offsets;  // first instance of each pair, in depth order
   unsigned long long* keys;
   uint32_t* values;
+  unsigned long long* counters;
+  int64_t depth_sorted;     // reported in counters[CNT_DEPTH_SORT]
 };
 
 struct RasterArgs {
@@ -276,7 +278,7 @@ struct RasterArgs {
 };
 
 // preprocess.hip
-hipError_t launch_setup_cams(const CamChunk& ch, CamDev* out, hipStream_t st);
+hipError_t launch_setup_cams(const CamChunk& ch, CamDev* out, unsigned long long* counters, hipStream_t st);
 hipError_t launch_prim_table(int N, int64_t P, float omega0, float time, const snp_prims& pr, float* table,
                              unsigned long long* counters, hipStream_t st);
 hipError_t launch_preprocess_views(const ViewArgs& a, hipStream_t st);
@@ -298,19 +300,25 @@ hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 size_t scan_scratch_bytes(int64_t n);
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint64_t* total_out,
                               hipStream_t st);
-hipError_t launch_emit(const EmitArgs& a, unsigned long long* counters, hipStream_t st);
-size_t sort_scratch_bytes(int64_t capacity);
+bool order_small(int64_t n);
+hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t n, uint32_t* order,
+                              uint32_t* counts_sorted, uint32_t* offsets, unsigned long long* total_out,
+                              hipStream_t st);
+hipError_t order_pairs(const uint32_t* depth_bits, const uint32_t* counts, int64_t n, uint32_t* ka, uint32_t* kb,
+                       uint32_t* va, uint32_t* order, uint32_t* counts_sorted, int rounds, void* scratch,
+                       hipStream_t st);
+hipError_t launch_emit(const EmitArgs& a, hipStream_t st);
+int sort_rounds(int64_t n);
+size_t sort_scratch_bytes(int64_t n, int rounds);
 hipError_t radix_sort(unsigned long long* k0, uint32_t* v0, unsigned long long* k1, uint32_t* v1, int64_t capacity,
-                      const unsigned long long* count, int lo_bit, int key_bits, void* scratch, hipStream_t st);
-hipError_t launch_depth_keys(const uint32_t* depth_bits, int64_t n, unsigned long long* keys, uint32_t* idx,
-                             unsigned long long* n_out, hipStream_t st);
-hipError_t launch_gather_counts(const uint32_t* order, const uint32_t* counts, int64_t n, uint32_t* out,
-                                hipStream_t st);
+                      const unsigned long long* count, int lo_bit, int key_bits, int rounds, void* scratch,
+                      uint32_t* clear, int64_t n_clear, hipStream_t st);
 int radix_passes(int key_bits);
 hipError_t launch_ranges(const unsigned long long* keys, const unsigned long long* counters, int64_t capacity,
-                         uint32_t* ranges, int64_t n_tiles, hipStream_t st);
-hipError_t launch_tile_keys(const uint32_t* ranges, int64_t n_tiles, unsigned long long* keys, uint32_t* ids,
-                            unsigned long long* n_out, hipStream_t st);
+                         uint32_t* ranges, hipStream_t st);
+size_t tile_order_scratch_bytes(int64_t n_tiles);
+hipError_t launch_tile_order(const uint32_t* ranges, int64_t n_tiles, uint32_t* order, uint32_t* scratch,
+                             hipStream_t st);
 // raster.hip
 int supported_tiles(int32_t* triples, int32_t max);
 bool tile_supported(int tw, int th, int ppl);
@@ -344,7 +352,6 @@ size_t loss_scratch_bytes();
 hipError_t launch_l1(const float* img, const float* tgt, int64_t n, double n_norm, float* grad, double* partials,
                      double* out, hipStream_t st);
 hipError_t zero_f32(float* p, int64_t n, hipStream_t st);
-hipError_t zero_counters(unsigned long long* p, int n, hipStream_t st);
 hipError_t zero_counter(unsigned long long* p, hipStream_t st);
 
 }  // namespace snp
