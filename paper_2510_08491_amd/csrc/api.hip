@@ -19,14 +19,14 @@ struct Plan {
   // depth order of the (view, primitive) pairs: scratch keys and indices, the
   // order and the tile counts in it
   size_t dkeys[2], dvals, order, counts_sorted;
-  size_t tile_order, tile_steps;  // persistent launches: tiles by instance count
+  size_t tile_order, tile_steps;  // tiles by instance count
+  bool tile_order_on;
   int inst_rounds, pair_rounds;   // block sizes of the radix passes over instances and pairs
   int64_t depth_reported;         // pairs the depth sort reports in its counter
   std::vector<int32_t> tile_base;
   std::vector<int64_t> pix_base;
   int64_t total_pixels;
   int tile_bits;  // significant bits of the global tile id
-  bool tile_order_on;  // persistent launches take the tiles by instance count, descending
   bool depth_first;  // depth sort of the pairs, then the instances by tile bits only
   // colour mode 4: the colour network's table and biases, their gradients,
   // and the rotation / scale gradients handed to the preprocess adjoint
@@ -148,10 +148,12 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   pl->values_alt = take(sizeof(uint32_t) * (size_t)cap);
   L.ranges = take(sizeof(uint32_t) * 2 * (size_t)tiles);
   L.tile_pairs = take(sizeof(uint32_t) * (size_t)tiles);
-  // the heaviest-first order pays for its sort where tiles are expensive (neural
-  // primitives); the Gaussians' cheap tiles do not need it
-  pl->tile_order_on = cfg->persistent != 0 && cfg->primitive == 0;
-  pl->tile_order = take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
+  // the tile order lies in the sort's spare keys, which are free once it has
+  // run; with less room than tiles, persistent launches have an array of
+  // their own and the others take the tiles in id order
+  const bool spare = tiles <= 2 * cap;
+  pl->tile_order_on = spare || cfg->persistent;
+  pl->tile_order = spare ? pl->keys_alt : take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
   L.gview = take(gs ? 0 : sizeof(float) * (size_t)VP * kGViewFloats);
   L.gtable = take(sizeof(float) * (size_t)P * TS);
   {
@@ -424,6 +426,10 @@ static RasterArgs raster_args(const snp_config* cfg, int64_t P, int32_t V, const
   a.values = wsp<uint32_t>(ws, L.values);
   a.ranges = wsp<uint32_t>(ws, L.ranges);
   a.tile_order = pl.tile_order_on ? wsp<uint32_t>(ws, pl.tile_order) : nullptr;
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  a.cus = cus > 0 ? cus : 1;
   a.rects = wsp<int32_t>(ws, L.rects);
   a.gview = wsp<float>(ws, L.gview);
   a.gtable = wsp<float>(ws, L.gtable);

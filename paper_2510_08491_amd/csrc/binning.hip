@@ -653,7 +653,7 @@ __global__ void __launch_bounds__(256) ranges_kernel(const unsigned long long* _
   }
 }
 
-// The order in which the persistent rasterizers take the tiles: most instances first, in
+// The order in which the rasterizers take the tiles: most instances first, in
 // steps of 64 instances (tiles of a step in any order -- the order only
 // balances the load).  A counting sort over 1024 steps; one workgroup while a
 // thread has at most a few dozen tiles, else spread over blocks that share

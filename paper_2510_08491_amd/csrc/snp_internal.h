@@ -255,7 +255,8 @@ struct RasterArgs {
   const float* records;
   const uint32_t* values;
   const uint32_t* ranges;
-  const uint32_t* tile_order;  // persistent launches: tiles by instance count, descending (null: in id order)
+  const uint32_t* tile_order;  // tiles by instance count, descending (null: in id order)
+  int32_t cus;                 // compute units of the device
   const int32_t* rects;   // per (view, primitive) pixel rectangle x0, x1, y0, y1
   float* images;          // forward output
   float* final_T;         // forward output
