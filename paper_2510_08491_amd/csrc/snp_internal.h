@@ -200,6 +200,23 @@ struct ShArgs {
   float* g_sh_t;
 };
 
+// Lanes per primitive where a per-primitive kernel goes over the units of its
+// rows (density table, adjoints): a group reads whole runs of a row.
+constexpr int kGroup = 4;
+
+// Sum over aligned groups of four lanes, the same value in every lane of the
+// group (whose lanes are active together).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double group_sum(double x) {
+  x += dpp_f64<0xB1>(x);    // quad_perm 1,0,3,2
+  return x + dpp_f64<0x4E>(x);  // quad_perm 2,3,0,1
+}
+
 struct PreBwdArgs {
   int64_t P;
   int32_t V, N, color_mode;
