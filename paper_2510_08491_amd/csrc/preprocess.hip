@@ -421,7 +421,51 @@ __global__ void __launch_bounds__(256) preprocess_views_kernel(ViewArgs a) {
 template <int WIDTH, int DEPTH, int IN>
 struct CmlpShape {
   static constexpr int K = IN * WIDTH + WIDTH + (DEPTH - 1) * (WIDTH * WIDTH + WIDTH) + WIDTH * 3 + 3;
+  // the copy in LDS: rows of hidden layers WIDTH + 1 apart, so that a column
+  // of 16 units as well as a row of 16 inputs lies in different banks
+  static constexpr int WS = WIDTH + 1;
+  static constexpr int LH = IN * WIDTH + WIDTH;              // first hidden layer
+  static constexpr int LHS = WIDTH * WS + WIDTH;             // one hidden layer
+  static constexpr int LO = LH + (DEPTH - 1) * LHS;          // output layer
+  static constexpr int LDS = (LO + 3 * WIDTH + 3 + 3) / 4 * 4;
 };
+
+// One wave copies a primitive's network to LDS, every load over 64 consecutive
+// floats and all of them in flight together (the operands of the products,
+// read from memory in their own order, touch 16 lines per load).
+template <int WIDTH, int DEPTH, int IN>
+__device__ __forceinline__ void cmlp_stage(const float* __restrict__ Wp, float* sW, int lane) {
+  using Sh = CmlpShape<WIDTH, DEPTH, IN>;
+  constexpr int H = WIDTH * WIDTH, RPL = 64 / WIDTH;  // rows of a hidden layer per load
+  constexpr int NF = (Sh::LH + 63) / 64, NH = H / 64, NO = (3 * WIDTH + 3 + 63) / 64;
+  float f[NF], h[DEPTH > 1 ? DEPTH - 1 : 1][NH + 1], o[NO];
+#pragma unroll
+  for (int u = 0; u < NF; ++u) f[u] = 64 * u + lane < Sh::LH ? Wp[64 * u + lane] : 0.f;
+#pragma unroll
+  for (int l = 0; l < DEPTH - 1; ++l) {
+    const float* w = Wp + Sh::LH + l * (H + WIDTH);
+#pragma unroll
+    for (int u = 0; u < NH; ++u) h[l][u] = w[64 * u + lane];
+    h[l][NH] = lane < WIDTH ? w[H + lane] : 0.f;
+  }
+  const float* wo = Wp + Sh::LH + (DEPTH - 1) * (H + WIDTH);
+#pragma unroll
+  for (int u = 0; u < NO; ++u) o[u] = 64 * u + lane < 3 * WIDTH + 3 ? wo[64 * u + lane] : 0.f;
+#pragma unroll
+  for (int u = 0; u < NF; ++u)
+    if (64 * u + lane < Sh::LH) sW[64 * u + lane] = f[u];
+#pragma unroll
+  for (int l = 0; l < DEPTH - 1; ++l) {
+    float* d = sW + Sh::LH + l * Sh::LHS;
+    const int at = (lane / WIDTH) * Sh::WS + lane % WIDTH;
+#pragma unroll
+    for (int u = 0; u < NH; ++u) d[at + u * RPL * Sh::WS] = h[l][u];
+    if (lane < WIDTH) d[WIDTH * Sh::WS + lane] = h[l][NH];
+  }
+#pragma unroll
+  for (int u = 0; u < NO; ++u)
+    if (64 * u + lane < 3 * WIDTH + 3) sW[Sh::LO + 64 * u + lane] = o[u];
+}
 
 // light direction normalize(l_v - x_B) of the relighting colour
 __device__ __forceinline__ void light_dir(const CmlpArgs& a, int64_t p, const CamDev& cam, float* ld, float* inv_len) {
@@ -466,7 +510,10 @@ __device__ __forceinline__ void cmlp_input(const CmlpArgs& a, int64_t p, int v, 
 // view c in register r.  rows_to_regs then transposes those four registers
 // with the wave's four rows of 16 lanes, so that lane (g, c) holds unit
 // 16 t + 4 s + g of view c in register s: the next layer's operand B as it
-// stands.  Each weight is loaded once per 16 views by exactly one lane.
+// stands.  The weights come from a copy in LDS (cmlp_stage), read from memory
+// once.  Bound by reading them: 1M primitives, 32 x 3, two views: 4.45 -> 1.98
+// ms (5.2 TB/s) against operands read from memory in their own order; 200k,
+// 32 x 2, four views: 0.67 -> 0.32 ms.
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4f rows_to_regs(v4f d) {
@@ -481,18 +528,23 @@ __device__ __forceinline__ v4f rows_to_regs(v4f d) {
 }
 
 template <int WIDTH, int DEPTH, int IN>
-__global__ void __launch_bounds__(256) cmlp_fwd_mfma_kernel(CmlpArgs a) {
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // one wave per primitive
-  if (p >= a.P) return;  // wave-uniform
-  const int lane = (int)(threadIdx.x & 63), g = lane >> 4, c = lane & 15;
-  constexpr int K = CmlpShape<WIDTH, DEPTH, IN>::K;
+__global__ void __launch_bounds__(64) cmlp_fwd_mfma_kernel(CmlpArgs a) {
+  using Sh = CmlpShape<WIDTH, DEPTH, IN>;
+  __shared__ float sW[Sh::LDS];
+  const int64_t p = blockIdx.x;
+  const int lane = (int)threadIdx.x, g = lane >> 4, c = lane & 15;
+  bool staged = false;  // wave-uniform
   constexpr int T = WIDTH / 16;     // tiles of 16 units
   constexpr int S0 = (IN + 3) / 4;  // steps of four inputs in the first layer
-  const float* Wp = a.cmlp + p * K;
   for (int v0 = 0; v0 < a.V; v0 += 16) {
     const int v = v0 + c;
     const bool vis = v < a.V && a.tile_counts[(int64_t)v * a.P + p] != 0;
     if (__ballot(vis) == 0) continue;  // wave-uniform
+    if (!staged) {
+      cmlp_stage<WIDTH, DEPTH, IN>(a.cmlp + p * Sh::K, sW, lane);
+      __syncthreads();
+      staged = true;
+    }
     float x[IN], dir[3], il;
     cmlp_input<IN>(a, p, v < a.V ? v : v0, x, dir, &il);  // lanes past the last view repeat a valid one
     float bx[S0];
@@ -511,16 +563,16 @@ __global__ void __launch_bounds__(256) cmlp_fwd_mfma_kernel(CmlpArgs a) {
 #pragma unroll
       for (int s = 0; s < S0; ++s) {
         const int k = 4 * s + g;
-        const float w = k < IN ? Wp[(16 * t + c) * IN + k] : 0.f;
+        const float w = k < IN ? sW[(16 * t + c) * IN + k] : 0.f;
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(w, bx[s], d, 0, 0, 0);
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) d[r] = fmaxf(d[r] + Wp[IN * WIDTH + 16 * t + 4 * g + r], 0.f);
+      for (int r = 0; r < 4; ++r) d[r] = fmaxf(d[r] + sW[IN * WIDTH + 16 * t + 4 * g + r], 0.f);
       h[t] = rows_to_regs(d);
     }
-    int off = IN * WIDTH + WIDTH;
 #pragma unroll
     for (int l = 1; l < DEPTH; ++l) {
+      const float* sL = sW + Sh::LH + (l - 1) * Sh::LHS;
       v4f nh[T];
 #pragma unroll
       for (int to = 0; to < T; ++to) {
@@ -529,15 +581,13 @@ __global__ void __launch_bounds__(256) cmlp_fwd_mfma_kernel(CmlpArgs a) {
         for (int t = 0; t < T; ++t)
 #pragma unroll
           for (int s = 0; s < 4; ++s)
-            d = __builtin_amdgcn_mfma_f32_16x16x4f32(Wp[off + (16 * to + c) * WIDTH + 16 * t + 4 * s + g], h[t][s], d,
-                                                     0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x4f32(sL[(16 * to + c) * Sh::WS + 16 * t + 4 * s + g], h[t][s], d, 0, 0, 0);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) d[r] = fmaxf(d[r] + Wp[off + WIDTH * WIDTH + 16 * to + 4 * g + r], 0.f);
+        for (int r = 0; r < 4; ++r) d[r] = fmaxf(d[r] + sL[WIDTH * Sh::WS + 16 * to + 4 * g + r], 0.f);
         nh[to] = rows_to_regs(d);
       }
 #pragma unroll
       for (int t = 0; t < T; ++t) h[t] = nh[t];
-      off += WIDTH * WIDTH + WIDTH;
     }
     // output layer: rows 0..2 of the tile (units c < 3 carry weights)
     v4f d = {0.f, 0.f, 0.f, 0.f};
@@ -545,14 +595,14 @@ __global__ void __launch_bounds__(256) cmlp_fwd_mfma_kernel(CmlpArgs a) {
     for (int t = 0; t < T; ++t)
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
-        const float w = c < 3 ? Wp[off + c * WIDTH + 16 * t + 4 * s + g] : 0.f;
+        const float w = c < 3 ? sW[Sh::LO + c * WIDTH + 16 * t + 4 * s + g] : 0.f;
         d = __builtin_amdgcn_mfma_f32_16x16x4f32(w, h[t][s], d, 0, 0, 0);
       }
     if (g == 0 && vis) {  // row group 0 holds outputs 0..3 of view c
       float out[3];
 #pragma unroll
       for (int o = 0; o < 3; ++o) {
-        out[o] = 1.0f / (1.0f + expf(-(d[o] + Wp[off + 3 * WIDTH + o])));
+        out[o] = 1.0f / (1.0f + expf(-(d[o] + sW[Sh::LO + 3 * WIDTH + o])));
         if (IN == 14) out[o] += a.colors[3 * p + o];  // relighting: c_dc + network
       }
       float* rec = a.records + ((int64_t)v * a.P + p) * kRecFloats;
@@ -568,41 +618,57 @@ __global__ void __launch_bounds__(256) cmlp_fwd_mfma_kernel(CmlpArgs a) {
 // (lane (g, c) = (lane / 16, lane % 16) holds units 16 t + 4 g + r of view c
 // in register r; rows_to_regs makes that the B operand of the next product).
 // The forward is recomputed; the deltas run back through the transposed
-// weights (operand A = W^T, the lanes along the rows of W: 64-byte runs);
-// the input gradient is one more such product.  The weights are read from
-// global memory (L1 and L2 after the first touch): an LDS copy would cost
-// more workgroups per CU than it saves.  Activations, deltas and inputs also
-// go to LDS as [view][unit], the operands of the weight gradients: products
-// over the views, each entry added to HBM by its one owning lane (no
-// atomics).  Views culled for the primitive carry zero deltas.
-template <int WIDTH, int DEPTH, int IN>
+// weights (operand A = W^T); the input gradient is one more such product.
+// The weights are read once, into LDS (cmlp_stage).  Activations, deltas and
+// inputs also go to LDS as [view][unit], the operands of the weight
+// gradients: products over the views, each entry written by its one owning
+// lane (no atomics).  Views culled for the primitive carry zero deltas.  LDS
+// holds rows for VR views of a chunk: with at most four views (VR = 4) the
+// rows of the other twelve would only cost workgroups per CU, and the weight
+// gradients take one product step per tile instead of four.
+// Bound by reading the weights and writing their gradients.  1M primitives,
+// 32 x 3, two views: 13.1 ms with the operands read from memory in their own
+// order (16 lines per load, evicted from L1 before their next use) and 16
+// rows, 7.4 ms with this copy and four rows; 200k,
+// 32 x 2: four views 1.39 -> 0.81, sixteen views (VR = 16) 1.46 -> 1.23 ms.
+template <int WIDTH, int DEPTH, int IN, int VR>
 __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
-  constexpr int K = CmlpShape<WIDTH, DEPTH, IN>::K;
+  using Sh = CmlpShape<WIDTH, DEPTH, IN>;
+  constexpr int K = Sh::K;
   constexpr int XI0 = IN - kXiDim;  // first xi input
   constexpr int VC = 16;            // views per chunk
   constexpr int T = WIDTH / 16;     // tiles of 16 units
   constexpr int S0 = (IN + 3) / 4;  // steps of four inputs in the first layer
   constexpr int LAST = IN * WIDTH + WIDTH + (DEPTH - 1) * (WIDTH * WIDTH + WIDTH);  // output layer offset
-  __shared__ float sX[VC][IN + 1];
-  __shared__ float sH[DEPTH][VC][WIDTH + 1];  // post-ReLU activations
-  __shared__ float sD[DEPTH][VC][WIDTH + 1];  // deltas of the hidden pre-activations
-  __shared__ float sDo[VC][4];                // deltas of the output pre-activations
-  __shared__ float sGx[VC][IN + 1];           // d loss / d input
+  __shared__ float sW[Sh::LDS];
+  __shared__ float sX[VR][IN + 1];
+  __shared__ float sH[DEPTH][VR][WIDTH + 1];  // post-ReLU activations
+  __shared__ float sD[DEPTH][VR][WIDTH + 1];  // deltas of the hidden pre-activations
+  __shared__ float sDo[VR][4];                // deltas of the output pre-activations
+  __shared__ float sGx[VR][IN + 1];           // d loss / d input
   const int64_t p = blockIdx.x;
   const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-  const float* Wg = a.cmlp + p * K;
+  const bool row = c < VR;  // a view with rows in LDS
+  bool staged = false;      // wave-uniform: a chunk with a visible view has been met
   float xi_acc = 0.f;  // lanes 0..7: sum over views of d loss / d xi[lane]
   float gc0 = 0.f, gc1 = 0.f, gc2 = 0.f;  // relighting: d loss / d x_B through the light direction
   for (int v0 = 0; v0 < a.V; v0 += VC) {
     const int v = v0 + c;
     const int64_t i = (int64_t)(v < a.V ? v : v0) * a.P + p;
     const bool act = v < a.V && a.tile_counts[i] != 0;
+    if (__ballot(act) == 0) continue;  // wave-uniform
+    const bool add = a.accumulate || staged;  // else the gradients are stored
+    if (!staged) {
+      cmlp_stage<WIDTH, DEPTH, IN>(a.cmlp + p * K, sW, lane);
+      __syncthreads();
+      staged = true;
+    }
     // ---- inputs (every lane of view c computes them; row 0 stores them)
     float x[IN], dir[3], il = 0.f;
 #pragma unroll
     for (int k = 0; k < IN; ++k) x[k] = 0.f;
     if (act) cmlp_input<IN>(a, p, v, x, dir, &il);
-    if (g == 0) {
+    if (g == 0 && row) {
 #pragma unroll
       for (int k = 0; k < IN; ++k) sX[c][k] = x[k];
     }
@@ -624,18 +690,18 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
       for (int s = 0; s < S0; ++s) {
         const int k = 4 * s + g;
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(k < IN ? Wg[(16 * t + c) * IN + k] : 0.f, bx[s], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(k < IN ? sW[(16 * t + c) * IN + k] : 0.f, bx[s], d, 0, 0, 0);
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        d[r] = fmaxf(d[r] + Wg[IN * WIDTH + 16 * t + 4 * g + r], 0.f);
-        sH[0][c][16 * t + 4 * g + r] = d[r];
+        d[r] = fmaxf(d[r] + sW[IN * WIDTH + 16 * t + 4 * g + r], 0.f);
+        if (row) sH[0][c][16 * t + 4 * g + r] = d[r];
       }
       hb[t] = rows_to_regs(d);
     }
 #pragma unroll
     for (int l = 1; l < DEPTH; ++l) {
-      const int off = IN * WIDTH + WIDTH + (l - 1) * (WIDTH * WIDTH + WIDTH);
+      const float* sL = sW + Sh::LH + (l - 1) * Sh::LHS;
       v4f nb[T];
 #pragma unroll
       for (int to = 0; to < T; ++to) {
@@ -644,12 +710,11 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
         for (int t = 0; t < T; ++t)
 #pragma unroll
           for (int s = 0; s < 4; ++s)
-            d = __builtin_amdgcn_mfma_f32_16x16x4f32(Wg[off + (16 * to + c) * WIDTH + 16 * t + 4 * s + g], hb[t][s], d,
-                                                     0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x4f32(sL[(16 * to + c) * Sh::WS + 16 * t + 4 * s + g], hb[t][s], d, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          d[r] = fmaxf(d[r] + Wg[off + WIDTH * WIDTH + 16 * to + 4 * g + r], 0.f);
-          sH[l][c][16 * to + 4 * g + r] = d[r];
+          d[r] = fmaxf(d[r] + sL[WIDTH * Sh::WS + 16 * to + 4 * g + r], 0.f);
+          if (row) sH[l][c][16 * to + 4 * g + r] = d[r];
         }
         nb[to] = rows_to_regs(d);
       }
@@ -665,17 +730,17 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
       for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          d = __builtin_amdgcn_mfma_f32_16x16x4f32(c < 3 ? Wg[LAST + c * WIDTH + 16 * t + 4 * s + g] : 0.f, hb[t][s],
+          d = __builtin_amdgcn_mfma_f32_16x16x4f32(c < 3 ? sW[Sh::LO + c * WIDTH + 16 * t + 4 * s + g] : 0.f, hb[t][s],
                                                    d, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float dv = 0.f;
         if (g == 0 && r < 3 && act) {
-          const float sg = 1.0f / (1.0f + expf(-(d[r] + Wg[LAST + 3 * WIDTH + r])));
+          const float sg = 1.0f / (1.0f + expf(-(d[r] + sW[Sh::LO + 3 * WIDTH + r])));
           dv = a.gview[i * kGViewFloats + 18 + r] * sg * (1.0f - sg);
         }
         dout[r] = dv;
-        if (g == 0) sDo[c][r] = dv;
+        if (g == 0 && row) sDo[c][r] = dv;
       }
     }
     // ---- deltas: last hidden layer from the output, then down the layers;
@@ -686,19 +751,19 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
       for (int t = 0; t < T; ++t) {
         v4f d = {0.f, 0.f, 0.f, 0.f};
-        d = __builtin_amdgcn_mfma_f32_16x16x4f32(g < 3 ? Wg[LAST + g * WIDTH + 16 * t + c] : 0.f, ob[0], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f32_16x16x4f32(g < 3 ? sW[Sh::LO + g * WIDTH + 16 * t + c] : 0.f, ob[0], d, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int u = 16 * t + 4 * g + r;
-          d[r] = sH[DEPTH - 1][c][u] > 0.f ? d[r] : 0.f;
-          sD[DEPTH - 1][c][u] = d[r];
+          d[r] = row && sH[DEPTH - 1][c][u] > 0.f ? d[r] : 0.f;
+          if (row) sD[DEPTH - 1][c][u] = d[r];
         }
         db[t] = rows_to_regs(d);
       }
     }
 #pragma unroll
     for (int l = DEPTH - 1; l >= 1; --l) {
-      const int off = IN * WIDTH + WIDTH + (l - 1) * (WIDTH * WIDTH + WIDTH);
+      const float* sL = sW + Sh::LH + (l - 1) * Sh::LHS;
       v4f nb[T];
 #pragma unroll
       for (int t = 0; t < T; ++t) {  // units of layer l - 1
@@ -707,13 +772,12 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
         for (int to = 0; to < T; ++to)  // units of layer l
 #pragma unroll
           for (int s = 0; s < 4; ++s)
-            d = __builtin_amdgcn_mfma_f32_16x16x4f32(Wg[off + (16 * to + 4 * s + g) * WIDTH + 16 * t + c], db[to][s], d,
-                                                     0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_16x16x4f32(sL[(16 * to + 4 * s + g) * Sh::WS + 16 * t + c], db[to][s], d, 0, 0, 0);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int u = 16 * t + 4 * g + r;
-          d[r] = sH[l - 1][c][u] > 0.f ? d[r] : 0.f;
-          sD[l - 1][c][u] = d[r];
+          d[r] = row && sH[l - 1][c][u] > 0.f ? d[r] : 0.f;
+          if (row) sD[l - 1][c][u] = d[r];
         }
         nb[t] = rows_to_regs(d);
       }
@@ -727,11 +791,11 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
       for (int to = 0; to < T; ++to)
 #pragma unroll
         for (int s = 0; s < 4; ++s)
-          d = __builtin_amdgcn_mfma_f32_16x16x4f32(c < IN ? Wg[(16 * to + 4 * s + g) * IN + c] : 0.f, db[to][s], d, 0,
+          d = __builtin_amdgcn_mfma_f32_16x16x4f32(c < IN ? sW[(16 * to + 4 * s + g) * IN + c] : 0.f, db[to][s], d, 0,
                                                    0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
-        if (4 * g + r < IN) sGx[c][4 * g + r] = d[r];
+        if (row && 4 * g + r < IN) sGx[c][4 * g + r] = d[r];
     }
     __syncthreads();
     if (g == 0 && act) {  // direction gradient for the chain to the centre
@@ -752,7 +816,7 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
     }
     if (lane < kXiDim) {
 #pragma unroll
-      for (int w = 0; w < VC; ++w) xi_acc += sGx[w][XI0 + lane];
+      for (int w = 0; w < VR; ++w) xi_acc += sGx[w][XI0 + lane];
     }
     // ---- weight gradients: sum over the chunk's 16 views of delta[o] x a[k]
     // on the matrix cores (K = views, four per step): lane (g, c) supplies
@@ -777,12 +841,12 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) old[t][r] = cw < IN ? G[(16 * t + 4 * gw + r) * IN + cw] : 0.f;
+          for (int r = 0; r < 4; ++r) old[t][r] = add && cw < IN ? G[(16 * t + 4 * gw + r) * IN + cw] : 0.f;
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t) {
           v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
+          for (int s = 0; s < VR / 4; ++s)
             d = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[0][4 * s + gw][16 * t + cw], cw < IN ? sX[4 * s + gw][cw] : 0.f,
                                                      d, 0, 0, 0);
           if (cw < IN) {
@@ -800,14 +864,14 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
           for (int t2 = 0; t2 < WIDTH / 16; ++t2)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) old[t][t2][r] = G[off + (16 * t + 4 * gw + r) * WIDTH + 16 * t2 + cw];
+            for (int r = 0; r < 4; ++r) old[t][t2][r] = add ? G[off + (16 * t + 4 * gw + r) * WIDTH + 16 * t2 + cw] : 0.f;
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t)
 #pragma unroll
           for (int t2 = 0; t2 < WIDTH / 16; ++t2) {
             v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int s = 0; s < VR / 4; ++s)
               d = __builtin_amdgcn_mfma_f32_16x16x4f32(sD[l][4 * s + gw][16 * t + cw], sH[l - 1][4 * s + gw][16 * t2 + cw],
                                                        d, 0, 0, 0);
 #pragma unroll
@@ -820,12 +884,12 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
         for (int t2 = 0; t2 < WIDTH / 16; ++t2)
 #pragma unroll
-          for (int r = 0; r < 3; ++r) old[t2][r] = gw == 0 ? G[LAST + r * WIDTH + 16 * t2 + cw] : 0.f;
+          for (int r = 0; r < 3; ++r) old[t2][r] = add && gw == 0 ? G[LAST + r * WIDTH + 16 * t2 + cw] : 0.f;
 #pragma unroll
         for (int t2 = 0; t2 < WIDTH / 16; ++t2) {
           v4f d = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
+          for (int s = 0; s < VR / 4; ++s)
             d = __builtin_amdgcn_mfma_f32_16x16x4f32(cw < 3 ? sDo[4 * s + gw][cw] : 0.f,
                                                      sH[DEPTH - 1][4 * s + gw][16 * t2 + cw], d, 0, 0, 0);
           if (gw == 0) {
@@ -841,20 +905,26 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
           const int boff = l == 0 ? IN * WIDTH : IN * WIDTH + WIDTH + (l - 1) * (WIDTH * WIDTH + WIDTH) + WIDTH * WIDTH;
           float sum = 0.f;
 #pragma unroll
-          for (int w = 0; w < VC; ++w) sum += sD[l][w][lane];
-          G[boff + lane] += sum;
+          for (int w = 0; w < VR; ++w) sum += sD[l][w][lane];
+          G[boff + lane] = add ? G[boff + lane] + sum : sum;
         }
       } else if (lane < WIDTH + 3) {
         const int o = lane - WIDTH;
         float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < VC; ++w) sum += sDo[w][o];
-        G[LAST + 3 * WIDTH + o] += sum;
+        for (int w = 0; w < VR; ++w) sum += sDo[w][o];
+        float* go = G + LAST + 3 * WIDTH + o;
+        *go = add ? *go + sum : sum;
       }
     }
     __syncthreads();
   }
-  if (a.g_xi && lane < kXiDim) a.g_xi[p * kXiDim + lane] += xi_acc;
+  if (!staged && a.g_cmlp && !a.accumulate)  // seen by no view
+    for (int k = lane; k < K; k += 64) a.g_cmlp[p * K + k] = 0.f;
+  if (a.g_xi && lane < kXiDim) {
+    float* gx = a.g_xi + p * kXiDim + lane;
+    *gx = a.accumulate ? *gx + xi_acc : xi_acc;
+  }
   if (IN == 14 && a.g_centers) {
     // the light-direction terms of the 16 view lanes (lanes 0..15, q = 0)
     gc0 += __shfl_xor(gc0, 1); gc1 += __shfl_xor(gc1, 1); gc2 += __shfl_xor(gc2, 1);
@@ -862,9 +932,10 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
     gc0 += __shfl_xor(gc0, 4); gc1 += __shfl_xor(gc1, 4); gc2 += __shfl_xor(gc2, 4);
     gc0 += __shfl_xor(gc0, 8); gc1 += __shfl_xor(gc1, 8); gc2 += __shfl_xor(gc2, 8);
     if (lane == 0) {
-      a.g_centers[3 * p] += gc0;
-      a.g_centers[3 * p + 1] += gc1;
-      a.g_centers[3 * p + 2] += gc2;
+      float* gx = a.g_centers + 3 * p;
+      gx[0] = a.accumulate ? gx[0] + gc0 : gc0;
+      gx[1] = a.accumulate ? gx[1] + gc1 : gc1;
+      gx[2] = a.accumulate ? gx[2] + gc2 : gc2;
     }
   }
 }
@@ -1115,25 +1186,25 @@ hipError_t launch_preprocess_views(const ViewArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-#define SNP_CMLP_DISPATCH_IN(KERNEL, IN, width, depth, grid, block, st, a)                                \
-  do {                                                                                                     \
-    if (width == 16 && depth == 1) hipLaunchKernelGGL((KERNEL<16, 1, IN>), grid, block, 0, st, a);         \
-    else if (width == 16 && depth == 2) hipLaunchKernelGGL((KERNEL<16, 2, IN>), grid, block, 0, st, a);    \
-    else if (width == 16 && depth == 3) hipLaunchKernelGGL((KERNEL<16, 3, IN>), grid, block, 0, st, a);    \
-    else if (width == 32 && depth == 1) hipLaunchKernelGGL((KERNEL<32, 1, IN>), grid, block, 0, st, a);    \
-    else if (width == 32 && depth == 2) hipLaunchKernelGGL((KERNEL<32, 2, IN>), grid, block, 0, st, a);    \
-    else if (width == 32 && depth == 3) hipLaunchKernelGGL((KERNEL<32, 3, IN>), grid, block, 0, st, a);    \
-    else return hipErrorInvalidValue;                                                                      \
+#define SNP_CMLP_DISPATCH_IN(KERNEL, IN, width, depth, grid, block, st, a, ...)                                         \
+  do {                                                                                                                  \
+    if (width == 16 && depth == 1) hipLaunchKernelGGL((KERNEL<16, 1, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a);      \
+    else if (width == 16 && depth == 2) hipLaunchKernelGGL((KERNEL<16, 2, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a); \
+    else if (width == 16 && depth == 3) hipLaunchKernelGGL((KERNEL<16, 3, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a); \
+    else if (width == 32 && depth == 1) hipLaunchKernelGGL((KERNEL<32, 1, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a); \
+    else if (width == 32 && depth == 2) hipLaunchKernelGGL((KERNEL<32, 2, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a); \
+    else if (width == 32 && depth == 3) hipLaunchKernelGGL((KERNEL<32, 3, IN __VA_OPT__(,) __VA_ARGS__>), grid, block, 0, st, a); \
+    else return hipErrorInvalidValue;                                                                                   \
   } while (0)
-#define SNP_CMLP_DISPATCH(KERNEL, width, depth, grid, block, st, a)                 \
-  do {                                                                               \
-    if (a.relight) SNP_CMLP_DISPATCH_IN(KERNEL, 14, width, depth, grid, block, st, a); \
-    else SNP_CMLP_DISPATCH_IN(KERNEL, 11, width, depth, grid, block, st, a);           \
+#define SNP_CMLP_DISPATCH(KERNEL, width, depth, grid, block, st, a, ...)                                          \
+  do {                                                                                                             \
+    if (a.relight) SNP_CMLP_DISPATCH_IN(KERNEL, 14, width, depth, grid, block, st, a __VA_OPT__(,) __VA_ARGS__);   \
+    else SNP_CMLP_DISPATCH_IN(KERNEL, 11, width, depth, grid, block, st, a __VA_OPT__(,) __VA_ARGS__);             \
   } while (0)
 
 hipError_t launch_cmlp_fwd(int width, int depth, CmlpArgs a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((a.P + 3) / 4)), block(256);
+  const dim3 grid((unsigned)a.P), block(64);
   SNP_CMLP_DISPATCH(cmlp_fwd_mfma_kernel, width, depth, grid, block, st, a);
   return hipGetLastError();
 }
@@ -1141,7 +1212,10 @@ hipError_t launch_cmlp_fwd(int width, int depth, CmlpArgs a, hipStream_t st) {
 hipError_t launch_cmlp_bwd(int width, int depth, CmlpArgs a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
   const dim3 grid((unsigned)a.P), block(64);
-  SNP_CMLP_DISPATCH(cmlp_bwd_kernel, width, depth, grid, block, st, a);
+  if (a.V <= 4)
+    SNP_CMLP_DISPATCH(cmlp_bwd_kernel, width, depth, grid, block, st, a, 4);
+  else
+    SNP_CMLP_DISPATCH(cmlp_bwd_kernel, width, depth, grid, block, st, a, 16);
   return hipGetLastError();
 }
 

@@ -182,6 +182,7 @@ struct CmlpArgs {
   float* g_cmlp;
   float* g_xi;
   float* g_centers;  // relighting: the light direction's chain to the centres
+  int32_t accumulate;  // 1: the gradients are added to what is there, 0: stored
 };
 
 constexpr int kShTime = 12;  // time-dependent zero-order SH: xi^1..4, cos(i xi), sin(i xi), i = 1..4
