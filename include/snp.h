@@ -292,8 +292,9 @@ snp_status snp_render_backward(const snp_config* cfg, const snp_prims* prims, in
                                void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
                                const snp_grads* grads, hipStream_t stream);
 
-/* One whole training step: zero `grads`, preprocess, bin, sort, forward,
- * L1 loss against `targets` (mean over n_norm elements), backward. */
+/* One whole training step: preprocess, bin, sort, forward,
+ * L1 loss against `targets` (mean over n_norm elements), backward.  Sets
+ * `grads`, whatever they held before. */
 snp_status snp_step(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams, void* ws,
                     const snp_layout* layout, float* images, float* final_T, const float* targets, double n_norm,
                     double* loss_out, float* dL_dimages, const snp_grads* grads, hipStream_t stream);

@@ -53,25 +53,22 @@ hipError_t launch_l1(const float* img, const float* tgt, int64_t n, double n_nor
   return hipGetLastError();
 }
 
-// zero a float buffer (a kernel rather than a memset, so it can sit in a graph)
-__global__ void zero_f32_kernel(float* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Zeroes a few buffers in one launch (a kernel rather than a memset, so it can
+// sit in a graph): 16-byte stores over each buffer in turn.
+__global__ void __launch_bounds__(256) zero_buffers_kernel(ZeroList z) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = 0.f;
+  for (int k = 0; k < z.count; ++k)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < z.n4[k]; i += stride)
+      z.p[k][i] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
-hipError_t zero_f32(float* p, int64_t n, hipStream_t st) {
-  if (!p || n <= 0) return hipSuccess;
-  int64_t blocks = (n + 255) / 256;
+hipError_t zero_buffers(const ZeroList& z, hipStream_t st) {
+  int64_t most = 0;
+  for (int k = 0; k < z.count; ++k) most = z.n4[k] > most ? z.n4[k] : most;
+  if (most <= 0) return hipSuccess;
+  int64_t blocks = (most + 255) / 256;
   if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL(zero_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, p, n);
-  return hipGetLastError();
-}
-
-__global__ void zero_one_u64_kernel(unsigned long long* p) { *p = 0ull; }
-
-hipError_t zero_counter(unsigned long long* p, hipStream_t st) {
-  hipLaunchKernelGGL(zero_one_u64_kernel, dim3(1), dim3(1), 0, st, p);
+  hipLaunchKernelGGL(zero_buffers_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z);
   return hipGetLastError();
 }
 

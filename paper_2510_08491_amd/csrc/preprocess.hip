@@ -629,8 +629,9 @@ __global__ void __launch_bounds__(64) cmlp_fwd_mfma_kernel(CmlpArgs a) {
 // Bound by reading the weights and writing their gradients.  1M primitives,
 // 32 x 3, two views: 13.1 ms with the operands read from memory in their own
 // order (16 lines per load, evicted from L1 before their next use) and 16
-// rows, 7.4 ms with this copy and four rows; 200k,
-// 32 x 2: four views 1.39 -> 0.81, sixteen views (VR = 16) 1.46 -> 1.23 ms.
+// rows, 7.4 ms with this copy and four rows, 5.35
+// ms where the gradients are stored rather than added; 200k,
+// 32 x 2: four views 1.39 -> 0.81 -> 0.62, sixteen views (VR = 16) 1.46 -> 1.23 ms.
 template <int WIDTH, int DEPTH, int IN, int VR>
 __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
   using Sh = CmlpShape<WIDTH, DEPTH, IN>;
@@ -906,25 +907,21 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
           float sum = 0.f;
 #pragma unroll
           for (int w = 0; w < VR; ++w) sum += sD[l][w][lane];
-          G[boff + lane] = add ? G[boff + lane] + sum : sum;
+          put_grad(G + boff + lane, sum, add);
         }
       } else if (lane < WIDTH + 3) {
         const int o = lane - WIDTH;
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < VR; ++w) sum += sDo[w][o];
-        float* go = G + LAST + 3 * WIDTH + o;
-        *go = add ? *go + sum : sum;
+        put_grad(G + LAST + 3 * WIDTH + o, sum, add);
       }
     }
     __syncthreads();
   }
   if (!staged && a.g_cmlp && !a.accumulate)  // seen by no view
     for (int k = lane; k < K; k += 64) a.g_cmlp[p * K + k] = 0.f;
-  if (a.g_xi && lane < kXiDim) {
-    float* gx = a.g_xi + p * kXiDim + lane;
-    *gx = a.accumulate ? *gx + xi_acc : xi_acc;
-  }
+  if (a.g_xi && lane < kXiDim) put_grad(a.g_xi + p * kXiDim + lane, xi_acc, a.accumulate);
   if (IN == 14 && a.g_centers) {
     // the light-direction terms of the 16 view lanes (lanes 0..15, q = 0)
     gc0 += __shfl_xor(gc0, 1); gc1 += __shfl_xor(gc1, 1); gc2 += __shfl_xor(gc2, 1);
@@ -932,10 +929,9 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
     gc0 += __shfl_xor(gc0, 4); gc1 += __shfl_xor(gc1, 4); gc2 += __shfl_xor(gc2, 4);
     gc0 += __shfl_xor(gc0, 8); gc1 += __shfl_xor(gc1, 8); gc2 += __shfl_xor(gc2, 8);
     if (lane == 0) {
-      float* gx = a.g_centers + 3 * p;
-      gx[0] = a.accumulate ? gx[0] + gc0 : gc0;
-      gx[1] = a.accumulate ? gx[1] + gc1 : gc1;
-      gx[2] = a.accumulate ? gx[2] + gc2 : gc2;
+      put_grad(a.g_centers + 3 * p, gc0, a.accumulate);
+      put_grad(a.g_centers + 3 * p + 1, gc1, a.accumulate);
+      put_grad(a.g_centers + 3 * p + 2, gc2, a.accumulate);
     }
   }
 }
@@ -957,7 +953,7 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 // Bound by its traffic (the gradient rows, W1, the gradients read and
 // written).  With a thread per primitive every load of the units touched 64
 // lines and a small scene ran on a dozen waves (1M primitives of 32 units,
-// two views: 5.55 ms, now 1.12; 3001 of 16, three views: 39 us, now 11).
+// two views: 5.55 ms, now 1.01; 3001 of 16, three views: 39 us, now 10).
 constexpr int kPreBwdPrims = 64;
 
 template <int N>
@@ -991,14 +987,14 @@ __global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwd
           for (int ii = 0; ii < 3; ++ii) {
             double acc = 0.0;
             for (int j = 0; j < 3; ++j) acc += gwt[j] * Rp[ii][j] * s[j];
-            a.g.w1[(p * N + k) * 3 + ii] += (float)(K * acc);
+            put_grad(a.g.w1 + (p * N + k) * 3 + ii, (float)(K * acc), a.accumulate);
           }
         }
-        if (a.g.b1) a.g.b1[p * N + k] += (float)((double)g4.w * a.omega0 / twopi);
-        if (a.g.wt) a.g.wt[p * N + k] += (float)((double)g4.w * a.time / twopi);
-        if (a.g.w2) a.g.w2[p * N + k] += (float)((double)gt[4 * N + k] / twopi);
+        if (a.g.b1) put_grad(a.g.b1 + p * N + k, (float)((double)g4.w * a.omega0 / twopi), a.accumulate);
+        if (a.g.wt) put_grad(a.g.wt + p * N + k, (float)((double)g4.w * a.time / twopi), a.accumulate);
+        if (a.g.w2) put_grad(a.g.w2 + p * N + k, (float)((double)gt[4 * N + k] / twopi), a.accumulate);
       }
-      if (a.g.b2 && q == 0) a.g.b2[p] += gt[5 * N];
+      if (a.g.b2 && q == 0) put_grad(a.g.b2 + p, gt[5 * N], a.accumulate);
       for (int ii = 0; ii < 3; ++ii)
         for (int j = 0; j < 3; ++j) {
           const double t = group_sum(T[ii][j]);
@@ -1150,13 +1146,13 @@ __global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwd
                  y * gR[1][2] + x * gR[2][0] + y * gR[2][1]);
   const double dq = gq[0] * w + gq[1] * x + gq[2] * y + gq[3] * z;
   if (a.g.quats)
-    for (int k = 0; k < 4; ++k) a.g.quats[4 * p + k] += (float)((gq[k] - qh[k] * dq) / qnorm);
+    for (int k = 0; k < 4; ++k) put_grad(a.g.quats + 4 * p + k, (float)((gq[k] - qh[k] * dq) / qnorm), a.accumulate);
   if (a.g.scales)
-    for (int k = 0; k < 3; ++k) a.g.scales[3 * p + k] += (float)gs[k];
+    for (int k = 0; k < 3; ++k) put_grad(a.g.scales + 3 * p + k, (float)gs[k], a.accumulate);
   if (a.g.centers)
-    for (int k = 0; k < 3; ++k) a.g.centers[3 * p + k] += (float)sums[9 + k];
+    for (int k = 0; k < 3; ++k) put_grad(a.g.centers + 3 * p + k, (float)sums[9 + k], a.accumulate_centers);
   if ((a.color_mode == 0 || a.color_mode == 3 || a.color_mode == 4) && a.g.colors)
-    for (int k = 0; k < 3; ++k) a.g.colors[3 * p + k] += (float)sums[12 + k];
+    for (int k = 0; k < 3; ++k) put_grad(a.g.colors + 3 * p + k, (float)sums[12 + k], a.accumulate);
 }
 
 // ---------------------------------------------------------------------------

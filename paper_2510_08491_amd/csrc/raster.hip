@@ -122,8 +122,15 @@ __device__ __forceinline__ int first_item(int cus) {
   return (k & 1) && (k + 1) * cus <= (int)gridDim.x ? (2 * k + 1) * cus - 1 - b : b;
 }
 
-__device__ __forceinline__ int next_item(unsigned long long* queue, int* s_item) {
-  if (threadIdx.x == 0) *s_item = (int)(atomicAdd(queue, 1ull) + gridDim.x);
+// A launch fetches exactly `total` times (total - gridDim.x items, and one
+// fetch past the end per workgroup), so the last fetch puts the queue back to
+// zero for the next launch: no launch of its own to clear it (4.6 us each).
+__device__ __forceinline__ int next_item(unsigned long long* queue, int total, int* s_item) {
+  if (threadIdx.x == 0) {
+    const unsigned long long k = atomicAdd(queue, 1ull);
+    if (k + 1 == (unsigned long long)total) atomicExch(queue, 0ull);
+    *s_item = (int)(k + gridDim.x);
+  }
   __syncthreads();
   const int item = *s_item;
   __syncthreads();
@@ -532,7 +539,7 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
       }
     }
     if (!PERSIST) break;
-    item = next_item(&a.counters[CNT_QUEUE_FWD], &s_item);
+    item = next_item(&a.counters[CNT_QUEUE_FWD], a.total_tiles, &s_item);
   }
   if (COUNT) {
     // one atomic per wave
@@ -650,7 +657,7 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_gauss_kernel(RasterA
       }
     }
     if (!PERSIST) break;
-    item = next_item(&a.counters[CNT_QUEUE_FWD], &s_item);
+    item = next_item(&a.counters[CNT_QUEUE_FWD], a.total_tiles, &s_item);
   }
   if (COUNT) {
     unsigned long long tot = npairs, live = nlive;
@@ -1405,7 +1412,7 @@ render_bwd_kernel(RasterArgs a) {
       if (__syncthreads_and(done)) break;
     }
     if (!PERSIST) break;
-    item = next_item(&a.counters[CNT_QUEUE_BWD], &s_item);
+    item = next_item(&a.counters[CNT_QUEUE_BWD], a.total_tiles, &s_item);
   }
 }
 

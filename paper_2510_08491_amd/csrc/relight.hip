@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(256) ray_bias_kernel(RayColourArgs a, int K) {
 // through the light direction.  The rotation and the scales need only the sums
 // P[i][j] = sum_k g_Au_k[j] W1p_k[i] and Q[i][j] = sum_k g_Ad_k[j] W1d_k[i].
 // Bound by its traffic (200k primitives of 16 units: 1.32 ms with a thread
-// per primitive, now 0.38).
+// per primitive, now 0.26).
 template <int W, int D>
 __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   using Lt = RayColourLayout<W, D>;
@@ -166,22 +166,22 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
         gd += gad[j] * Rp[ii][j] * s[j];
       }
       if (gc) {
-        gc[k * kRayIn + ii] += (float)(gp / m);
-        gc[k * kRayIn + 3 + ii] += (float)gd;
-        gc[k * kRayIn + 6 + ii] += (float)gwl[u][ii];
+        put_grad(gc + k * kRayIn + ii, (float)(gp / m), a.accumulate);
+        put_grad(gc + k * kRayIn + 3 + ii, (float)gd, a.accumulate);
+        put_grad(gc + k * kRayIn + 6 + ii, (float)gwl[u][ii], a.accumulate);
       }
     }
-    if (gc) gc[kRayIn * W + k] += (float)gb1[u];
+    if (gc) put_grad(gc + kRayIn * W + k, (float)gb1[u], a.accumulate);
   }
   if (gc) {
     int pos = kRayIn * W + W;
     if (D == 2) {
 #pragma unroll 4
-      for (int i = q; i < W * W + W; i += kGroup) gc[pos + i] += gt[Lt::WH + i];
+      for (int i = q; i < W * W + W; i += kGroup) put_grad(gc + pos + i, gt[Lt::WH + i], a.accumulate);
       pos += W * W + W;
     }
 #pragma unroll
-    for (int i = q; i < 3 * W + 3; i += kGroup) gc[pos + i] += gt[Lt::WO + i];
+    for (int i = q; i < 3 * W + 3; i += kGroup) put_grad(gc + pos + i, gt[Lt::WO + i], a.accumulate);
   }
   double gR[3][3], gs[3], gm = 0.0;
   for (int j = 0; j < 3; ++j) {
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   }
   if (q != 0) return;
   if (a.g_centers)
-    for (int ii = 0; ii < 3; ++ii) a.g_centers[3 * p + ii] += (float)gx[ii];
+    for (int ii = 0; ii < 3; ++ii) put_grad(a.g_centers + 3 * p + ii, (float)gx[ii], a.accumulate);
   float* ex = a.extra_rs + p * 12;
   for (int ii = 0; ii < 3; ++ii)
     for (int j = 0; j < 3; ++j) ex[3 * ii + j] = (float)gR[ii][j];

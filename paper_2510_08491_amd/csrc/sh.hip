@@ -160,14 +160,16 @@ __global__ void __launch_bounds__(128) sh_bwd_kernel(ShArgs a) {
 #pragma unroll
     for (int k = 0; k < 16; ++k)
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) a.g_sh[p * kShCoeffs + 3 * k + ch] += g[k][ch];
+      for (int ch = 0; ch < 3; ++ch) put_grad(a.g_sh + p * kShCoeffs + 3 * k + ch, g[k][ch], a.accumulate);
   }
   // the time coefficients: d S0(xi) / d sh_t[k][c] = tb_k
-  if (a.sh_t && a.g_sh_t) {
+  // (zero where the colour does not depend on the time)
+  if (a.g_sh_t && (a.sh_t || !a.accumulate)) {
 #pragma unroll
     for (int k = 0; k < kShTime; ++k)
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) a.g_sh_t[p * (kShTime * 3) + 3 * k + ch] += a.tb[k] * g[0][ch];
+      for (int ch = 0; ch < 3; ++ch)
+        put_grad(a.g_sh_t + p * (kShTime * 3) + 3 * k + ch, a.sh_t ? a.tb[k] * g[0][ch] : 0.f, a.accumulate);
   }
 }
 

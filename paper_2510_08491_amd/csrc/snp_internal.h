@@ -199,6 +199,7 @@ struct ShArgs {
   float* gview;
   float* g_sh;
   float* g_sh_t;
+  int32_t accumulate;  // as in CmlpArgs
 };
 
 // Lanes per primitive where a per-primitive kernel goes over the units of its
@@ -230,7 +231,12 @@ struct PreBwdArgs {
   const float* gtable;
   const float* extra_rs;  // per primitive 12 floats: further d loss / d R (9) and d loss / d s (3), or null
   snp_grads g;
+  int32_t accumulate;          // as in CmlpArgs
+  int32_t accumulate_centers;  // the same for the centres, which the colour networks' adjoints write first
 };
+
+// a gradient entry, added to what is there or stored
+__device__ __forceinline__ void put_grad(float* p, float g, bool add) { *p = add ? *p + g : g; }
 
 // per-ray relighting colour (colour mode 4): the preprocess side
 struct RayColourArgs {
@@ -246,6 +252,7 @@ struct RayColourArgs {
   float* g_cmlp;
   float* g_centers;
   float* extra_rs;      // backward: per primitive d loss / d R (9), d loss / d s (3) for the preprocess adjoint
+  int32_t accumulate;   // as in CmlpArgs
 };
 
 struct EmitArgs {
@@ -370,7 +377,17 @@ hipError_t launch_densify_apply(int64_t P, const int32_t* action, const uint32_t
 size_t loss_scratch_bytes();
 hipError_t launch_l1(const float* img, const float* tgt, int64_t n, double n_norm, float* grad, double* partials,
                      double* out, hipStream_t st);
-hipError_t zero_f32(float* p, int64_t n, hipStream_t st);
-hipError_t zero_counter(unsigned long long* p, hipStream_t st);
+// Workspace buffers to clear: 16-byte aligned, whole float4s.
+struct ZeroList {
+  static constexpr int kMax = 4;
+  float4* p[kMax];
+  int64_t n4[kMax];
+  int count;
+  void add(float* q, int64_t floats) {
+    p[count] = reinterpret_cast<float4*>(q);
+    n4[count++] = floats / 4;
+  }
+};
+hipError_t zero_buffers(const ZeroList& z, hipStream_t st);
 
 }  // namespace snp
