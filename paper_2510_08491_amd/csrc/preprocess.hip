@@ -842,7 +842,13 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) old[t][r] = add && cw < IN ? G[(16 * t + 4 * gw + r) * IN + cw] : 0.f;
+          for (int r = 0; r < 4; ++r) old[t][r] = 0.f;
+        if (add && cw < IN) {
+#pragma unroll
+          for (int t = 0; t < WIDTH / 16; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) old[t][r] = G[(16 * t + 4 * gw + r) * IN + cw];
+        }
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t) {
           v4f d = {0.f, 0.f, 0.f, 0.f};
@@ -865,7 +871,15 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
           for (int t2 = 0; t2 < WIDTH / 16; ++t2)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) old[t][t2][r] = add ? G[off + (16 * t + 4 * gw + r) * WIDTH + 16 * t2 + cw] : 0.f;
+            for (int r = 0; r < 4; ++r) old[t][t2][r] = 0.f;
+        if (add) {
+#pragma unroll
+          for (int t = 0; t < WIDTH / 16; ++t)
+#pragma unroll
+            for (int t2 = 0; t2 < WIDTH / 16; ++t2)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) old[t][t2][r] = G[off + (16 * t + 4 * gw + r) * WIDTH + 16 * t2 + cw];
+        }
 #pragma unroll
         for (int t = 0; t < WIDTH / 16; ++t)
 #pragma unroll
@@ -885,7 +899,13 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 #pragma unroll
         for (int t2 = 0; t2 < WIDTH / 16; ++t2)
 #pragma unroll
-          for (int r = 0; r < 3; ++r) old[t2][r] = add && gw == 0 ? G[LAST + r * WIDTH + 16 * t2 + cw] : 0.f;
+          for (int r = 0; r < 3; ++r) old[t2][r] = 0.f;
+        if (add && gw == 0) {
+#pragma unroll
+          for (int t2 = 0; t2 < WIDTH / 16; ++t2)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) old[t2][r] = G[LAST + r * WIDTH + 16 * t2 + cw];
+        }
 #pragma unroll
         for (int t2 = 0; t2 < WIDTH / 16; ++t2) {
           v4f d = {0.f, 0.f, 0.f, 0.f};
@@ -907,21 +927,21 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
           float sum = 0.f;
 #pragma unroll
           for (int w = 0; w < VR; ++w) sum += sD[l][w][lane];
-          put_grad(G + boff + lane, sum, add);
+          G[boff + lane] = (add ? G[boff + lane] : 0.f) + sum;
         }
       } else if (lane < WIDTH + 3) {
         const int o = lane - WIDTH;
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < VR; ++w) sum += sDo[w][o];
-        put_grad(G + LAST + 3 * WIDTH + o, sum, add);
+        G[LAST + 3 * WIDTH + o] = (add ? G[LAST + 3 * WIDTH + o] : 0.f) + sum;
       }
     }
     __syncthreads();
   }
   if (!staged && a.g_cmlp && !a.accumulate)  // seen by no view
     for (int k = lane; k < K; k += 64) a.g_cmlp[p * K + k] = 0.f;
-  if (a.g_xi && lane < kXiDim) put_grad(a.g_xi + p * kXiDim + lane, xi_acc, a.accumulate);
+  if (a.g_xi && lane < kXiDim) a.g_xi[p * kXiDim + lane] = (a.accumulate ? a.g_xi[p * kXiDim + lane] : 0.f) + xi_acc;
   if (IN == 14 && a.g_centers) {
     // the light-direction terms of the 16 view lanes (lanes 0..15, q = 0)
     gc0 += __shfl_xor(gc0, 1); gc1 += __shfl_xor(gc1, 1); gc2 += __shfl_xor(gc2, 1);
@@ -929,9 +949,13 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
     gc0 += __shfl_xor(gc0, 4); gc1 += __shfl_xor(gc1, 4); gc2 += __shfl_xor(gc2, 4);
     gc0 += __shfl_xor(gc0, 8); gc1 += __shfl_xor(gc1, 8); gc2 += __shfl_xor(gc2, 8);
     if (lane == 0) {
-      put_grad(a.g_centers + 3 * p, gc0, a.accumulate);
-      put_grad(a.g_centers + 3 * p + 1, gc1, a.accumulate);
-      put_grad(a.g_centers + 3 * p + 2, gc2, a.accumulate);
+      float c[3] = {0.f, 0.f, 0.f};
+      float* gx = a.g_centers + 3 * p;
+      if (a.accumulate)
+        for (int k = 0; k < 3; ++k) c[k] = gx[k];
+      gx[0] = c[0] + gc0;
+      gx[1] = c[1] + gc1;
+      gx[2] = c[2] + gc2;
     }
   }
 }
@@ -953,10 +977,10 @@ __global__ void __launch_bounds__(64) cmlp_bwd_kernel(CmlpArgs a) {
 // Bound by its traffic (the gradient rows, W1, the gradients read and
 // written).  With a thread per primitive every load of the units touched 64
 // lines and a small scene ran on a dozen waves (1M primitives of 32 units,
-// two views: 5.55 ms, now 1.01; 3001 of 16, three views: 39 us, now 10).
+// two views: 5.55 ms, now 0.86; 3001 of 16, three views: 39 us, now 10).
 constexpr int kPreBwdPrims = 64;
 
-template <int N>
+template <int N, bool ADD>
 __global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwdArgs a) {
   static_assert(kGroup == 4, "four waves of 64 primitives in every phase");
   constexpr int kSums = 15;  // of a wave's views: g_U (9), g_x_B (3), g_colour (3)
@@ -987,14 +1011,14 @@ __global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwd
           for (int ii = 0; ii < 3; ++ii) {
             double acc = 0.0;
             for (int j = 0; j < 3; ++j) acc += gwt[j] * Rp[ii][j] * s[j];
-            put_grad(a.g.w1 + (p * N + k) * 3 + ii, (float)(K * acc), a.accumulate);
+            put_grad<ADD>(a.g.w1 + (p * N + k) * 3 + ii, (float)(K * acc));
           }
         }
-        if (a.g.b1) put_grad(a.g.b1 + p * N + k, (float)((double)g4.w * a.omega0 / twopi), a.accumulate);
-        if (a.g.wt) put_grad(a.g.wt + p * N + k, (float)((double)g4.w * a.time / twopi), a.accumulate);
-        if (a.g.w2) put_grad(a.g.w2 + p * N + k, (float)((double)gt[4 * N + k] / twopi), a.accumulate);
+        if (a.g.b1) put_grad<ADD>(a.g.b1 + p * N + k, (float)((double)g4.w * a.omega0 / twopi));
+        if (a.g.wt) put_grad<ADD>(a.g.wt + p * N + k, (float)((double)g4.w * a.time / twopi));
+        if (a.g.w2) put_grad<ADD>(a.g.w2 + p * N + k, (float)((double)gt[4 * N + k] / twopi));
       }
-      if (a.g.b2 && q == 0) put_grad(a.g.b2 + p, gt[5 * N], a.accumulate);
+      if (a.g.b2 && q == 0) put_grad<ADD>(a.g.b2 + p, gt[5 * N]);
       for (int ii = 0; ii < 3; ++ii)
         for (int j = 0; j < 3; ++j) {
           const double t = group_sum(T[ii][j]);
@@ -1146,13 +1170,13 @@ __global__ void __launch_bounds__(4 * kPreBwdPrims) preprocess_bwd_kernel(PreBwd
                  y * gR[1][2] + x * gR[2][0] + y * gR[2][1]);
   const double dq = gq[0] * w + gq[1] * x + gq[2] * y + gq[3] * z;
   if (a.g.quats)
-    for (int k = 0; k < 4; ++k) put_grad(a.g.quats + 4 * p + k, (float)((gq[k] - qh[k] * dq) / qnorm), a.accumulate);
+    for (int k = 0; k < 4; ++k) put_grad<ADD>(a.g.quats + 4 * p + k, (float)((gq[k] - qh[k] * dq) / qnorm));
   if (a.g.scales)
-    for (int k = 0; k < 3; ++k) put_grad(a.g.scales + 3 * p + k, (float)gs[k], a.accumulate);
+    for (int k = 0; k < 3; ++k) put_grad<ADD>(a.g.scales + 3 * p + k, (float)gs[k]);
   if (a.g.centers)
-    for (int k = 0; k < 3; ++k) put_grad(a.g.centers + 3 * p + k, (float)sums[9 + k], a.accumulate_centers);
+    for (int k = 0; k < 3; ++k) a.g.centers[3 * p + k] = (a.accumulate_centers ? a.g.centers[3 * p + k] : 0.f) + (float)sums[9 + k];
   if ((a.color_mode == 0 || a.color_mode == 3 || a.color_mode == 4) && a.g.colors)
-    for (int k = 0; k < 3; ++k) put_grad(a.g.colors + 3 * p + k, (float)sums[12 + k], a.accumulate);
+    for (int k = 0; k < 3; ++k) put_grad<ADD>(a.g.colors + 3 * p + k, (float)sums[12 + k]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1224,13 +1248,21 @@ int cmlp_param_count(int width, int depth, bool relight) {
   return in * width + width + (depth - 1) * (width * width + width) + width * 3 + 3;
 }
 
-hipError_t launch_preprocess_bwd(const PreBwdArgs& a, hipStream_t st) {
+template <int N>
+static void preprocess_bwd(const PreBwdArgs& a, hipStream_t st) {
   const dim3 grid((unsigned)((a.P + kPreBwdPrims - 1) / kPreBwdPrims)), block(4 * kPreBwdPrims);
+  if (a.accumulate)
+    hipLaunchKernelGGL((preprocess_bwd_kernel<N, true>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((preprocess_bwd_kernel<N, false>), grid, block, 0, st, a);
+}
+
+hipError_t launch_preprocess_bwd(const PreBwdArgs& a, hipStream_t st) {
   switch (a.N) {
-    case 4: hipLaunchKernelGGL(preprocess_bwd_kernel<4>, grid, block, 0, st, a); break;
-    case 8: hipLaunchKernelGGL(preprocess_bwd_kernel<8>, grid, block, 0, st, a); break;
-    case 16: hipLaunchKernelGGL(preprocess_bwd_kernel<16>, grid, block, 0, st, a); break;
-    case 32: hipLaunchKernelGGL(preprocess_bwd_kernel<32>, grid, block, 0, st, a); break;
+    case 4: preprocess_bwd<4>(a, st); break;
+    case 8: preprocess_bwd<8>(a, st); break;
+    case 16: preprocess_bwd<16>(a, st); break;
+    case 32: preprocess_bwd<32>(a, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(256) ray_bias_kernel(RayColourArgs a, int K) {
 // P[i][j] = sum_k g_Au_k[j] W1p_k[i] and Q[i][j] = sum_k g_Ad_k[j] W1d_k[i].
 // Bound by its traffic (200k primitives of 16 units: 1.32 ms with a thread
 // per primitive, now 0.26).
-template <int W, int D>
+template <int W, int D, bool ADD>
 __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   using Lt = RayColourLayout<W, D>;
   constexpr int UPL = W / kGroup;  // units per lane
@@ -166,22 +166,22 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
         gd += gad[j] * Rp[ii][j] * s[j];
       }
       if (gc) {
-        put_grad(gc + k * kRayIn + ii, (float)(gp / m), a.accumulate);
-        put_grad(gc + k * kRayIn + 3 + ii, (float)gd, a.accumulate);
-        put_grad(gc + k * kRayIn + 6 + ii, (float)gwl[u][ii], a.accumulate);
+        put_grad<ADD>(gc + k * kRayIn + ii, (float)(gp / m));
+        put_grad<ADD>(gc + k * kRayIn + 3 + ii, (float)gd);
+        put_grad<ADD>(gc + k * kRayIn + 6 + ii, (float)gwl[u][ii]);
       }
     }
-    if (gc) put_grad(gc + kRayIn * W + k, (float)gb1[u], a.accumulate);
+    if (gc) put_grad<ADD>(gc + kRayIn * W + k, (float)gb1[u]);
   }
   if (gc) {
     int pos = kRayIn * W + W;
     if (D == 2) {
 #pragma unroll 4
-      for (int i = q; i < W * W + W; i += kGroup) put_grad(gc + pos + i, gt[Lt::WH + i], a.accumulate);
+      for (int i = q; i < W * W + W; i += kGroup) put_grad<ADD>(gc + pos + i, gt[Lt::WH + i]);
       pos += W * W + W;
     }
 #pragma unroll
-    for (int i = q; i < 3 * W + 3; i += kGroup) put_grad(gc + pos + i, gt[Lt::WO + i], a.accumulate);
+    for (int i = q; i < 3 * W + 3; i += kGroup) put_grad<ADD>(gc + pos + i, gt[Lt::WO + i]);
   }
   double gR[3][3], gs[3], gm = 0.0;
   for (int j = 0; j < 3; ++j) {
@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) ray_colour_bwd_kernel(RayColourArgs a) {
   }
   if (q != 0) return;
   if (a.g_centers)
-    for (int ii = 0; ii < 3; ++ii) put_grad(a.g_centers + 3 * p + ii, (float)gx[ii], a.accumulate);
+    for (int ii = 0; ii < 3; ++ii) put_grad<ADD>(a.g_centers + 3 * p + ii, (float)gx[ii]);
   float* ex = a.extra_rs + p * 12;
   for (int ii = 0; ii < 3; ++ii)
     for (int j = 0; j < 3; ++j) ex[3 * ii + j] = (float)gR[ii][j];
@@ -226,13 +226,21 @@ hipError_t launch_ray_colour_fwd(const RayColourArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int D>
+static void ray_colour_bwd(const RayColourArgs& a, hipStream_t st) {
+  const dim3 block(256), grid((unsigned)((a.P * kGroup + 255) / 256));
+  if (a.accumulate)
+    hipLaunchKernelGGL((ray_colour_bwd_kernel<16, D, true>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((ray_colour_bwd_kernel<16, D, false>), grid, block, 0, st, a);
+}
+
 hipError_t launch_ray_colour_bwd(const RayColourArgs& a, hipStream_t st) {
-  const dim3 block(256), gp((unsigned)((a.P * kGroup + 255) / 256));
   if (a.W != 16) return hipErrorInvalidValue;
   if (a.D == 1)
-    hipLaunchKernelGGL((ray_colour_bwd_kernel<16, 1>), gp, block, 0, st, a);
+    ray_colour_bwd<1>(a, st);
   else if (a.D == 2)
-    hipLaunchKernelGGL((ray_colour_bwd_kernel<16, 2>), gp, block, 0, st, a);
+    ray_colour_bwd<2>(a, st);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

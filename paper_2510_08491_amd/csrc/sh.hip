@@ -64,117 +64,175 @@ __device__ __forceinline__ void sh_weighted_grad(float x, float y, float z, cons
        kSh3e * (xx - yy) * w[14];
 }
 
-__device__ __forceinline__ void view_dir(const ShArgs& a, int v, int64_t p, float& x, float& y, float& z) {
+__device__ __forceinline__ void view_dir(const ShArgs& a, int v, const float (&xb)[3], float& x, float& y, float& z) {
   const CamDev& cam = a.cams[v];
-  const float dx = a.centers[3 * p] - cam.o_f[0];
-  const float dy = a.centers[3 * p + 1] - cam.o_f[1];
-  const float dz = a.centers[3 * p + 2] - cam.o_f[2];
+  const float dx = xb[0] - cam.o_f[0];
+  const float dy = xb[1] - cam.o_f[1];
+  const float dz = xb[2] - cam.o_f[2];
   const float il = 1.0f / sqrtf(dx * dx + dy * dy + dz * dz);
   x = dx * il;
   y = dy * il;
   z = dz * il;
 }
 
-// the zero-order coefficient of channel ch (time dependent with sh_t)
-__device__ __forceinline__ float zero_order(const ShArgs& a, int64_t p, const float* c, int ch) {
-  float s0 = c[ch];
-  if (a.sh_t) {
-    const float* t = a.sh_t + p * (kShTime * 3);
-#pragma unroll
-    for (int k = 0; k < kShTime; ++k) s0 = __builtin_fmaf(a.tb[k], t[3 * k + ch], s0);
-  }
-  return s0;
+// Four lanes per primitive (kGroup): lane q holds the coefficients 4 q .. 4 q
+// + 3 and the time coefficients 3 q .. 3 q + 2, a quarter of a row each, so
+// that a wave reads and writes whole runs of memory; the channels' sums meet
+// over the group.  Bound by that traffic (100k primitives; a thread per
+// primitive before: forward of one view 18 -> 8.9 us, of two views with the
+// time term 38 -> 15.6 us, adjoint 21 -> 16 us and 40 -> 23 us).
+static_assert(kGroup == 4 && kShTime == 12, "a quarter of the rows per lane");
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float group_sum_f32(float x) {
+  x += dpp_f32<0xB1>(x);         // quad_perm 1,0,3,2
+  return x + dpp_f32<0x4E>(x);   // quad_perm 2,3,0,1
 }
 
-// one thread per (view, primitive): colour into the record
-__global__ void __launch_bounds__(256) sh_fwd_kernel(ShArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)a.V * a.P || a.tile_counts[i] == 0) return;
-  const int v = (int)(i / a.P);
-  const int64_t p = i - (int64_t)v * a.P;
-  float x, y, z, Y[16];
-  view_dir(a, v, p, x, y, z);
-  sh_basis(x, y, z, Y);
-  const float* c = a.sh + p * kShCoeffs;
-  float col[3];
+// the value of lane q's quarter.  (By value, in registers: an index or a
+// select among the elements of an array would put it into scratch.)
+__device__ __forceinline__ float pick4(float a0, float a1, float a2, float a3, int q) {
+  asm("" : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3));
+  const float lo = q == 0 ? a0 : a1, hi = q == 2 ? a2 : a3;
+  return q < 2 ? lo : hi;
+}
+
+// this lane's four of the sixteen basis values
+__device__ __forceinline__ void own_basis(const float (&Y)[16], int q, float (&Yq)[4]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) Yq[i] = pick4(Y[i], Y[4 + i], Y[8 + i], Y[12 + i], q);
+}
+
+// this lane's k-th function of the time
+__device__ __forceinline__ float own_time(const ShArgs& a, int q, int k) {
+  return pick4(a.tb[k], a.tb[3 + k], a.tb[6 + k], a.tb[9 + k], q);
+}
+
+// this lane's coefficients, the time-dependent part of the zero-order
+// coefficient included (as a share of c[0], which only the sums over the
+// group make whole: lane 0 alone carries Y_0)
+__device__ __forceinline__ void own_coeffs(const ShArgs& a, int64_t p, int q, float (&c)[4][3], float (&t0)[3]) {
+  const float* r = a.sh + p * kShCoeffs + 12 * q;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) c[i][ch] = r[3 * i + ch];
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) t0[ch] = 0.f;
+  if (a.sh_t) {
+    const float* t = a.sh_t + p * (kShTime * 3) + 9 * q;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float tb = own_time(a, q, k);
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) t0[ch] = __builtin_fmaf(tb, t[3 * k + ch], t0[ch]);
+    }
+  }
+}
+
+// colour into the record, before the clamp at zero
+__device__ __forceinline__ void group_colour(const float (&c)[4][3], const float (&t0)[3], const float (&Yq)[4],
+                                             float (&s)[3]) {
 #pragma unroll
   for (int ch = 0; ch < 3; ++ch) {
-    float s = 0.5f;
+    float x = kSh0 * t0[ch];
 #pragma unroll
-    for (int k = 1; k < 16; ++k) s = __builtin_fmaf(Y[k], c[3 * k + ch], s);
-    s = __builtin_fmaf(Y[0], zero_order(a, p, c, ch), s);
-    col[ch] = fmaxf(s, 0.f);
+    for (int i = 0; i < 4; ++i) x = __builtin_fmaf(Yq[i], c[i][ch], x);
+    s[ch] = 0.5f + group_sum_f32(x);
   }
-  float* rec = a.records + i * kRecFloats;
-  rec[11] = col[0];
-  rec[15] = col[1];
-  rec[19] = col[2];
 }
 
-// one thread per primitive, its views in turn: coefficient gradients summed
+// one group per (view, primitive): colour into the record
+__global__ void __launch_bounds__(256) sh_fwd_kernel(ShArgs a) {
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int q = (int)(threadIdx.x % kGroup);
+  if (i >= (int64_t)a.V * a.P || a.tile_counts[i] == 0) return;  // whole groups
+  const int v = (int)(i / a.P);
+  const int64_t p = i - (int64_t)v * a.P;
+  float x, y, z, Y[16], Yq[4], c[4][3], t0[3], s[3];
+  const float xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
+  own_coeffs(a, p, q, c, t0);
+  view_dir(a, v, xb, x, y, z);
+  sh_basis(x, y, z, Y);
+  own_basis(Y, q, Yq);
+  group_colour(c, t0, Yq, s);
+  if (q < 3) a.records[i * kRecFloats + 11 + 4 * q] = fmaxf(q == 0 ? s[0] : q == 1 ? s[1] : s[2], 0.f);
+}
+
+// one group per primitive, its views in turn: coefficient gradients summed
 // over the views (kept in registers), the direction gradient of each view
 // written to the view's gradient record (slots 21..23) for the chain to the
 // centre; a clamped channel passes no gradient
-__global__ void __launch_bounds__(128) sh_bwd_kernel(ShArgs a) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+template <bool ADD>
+__global__ void __launch_bounds__(256) sh_bwd_kernel(ShArgs a) {
+  const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int q = (int)(threadIdx.x % kGroup);
   if (p >= a.P) return;
-  float c[16][3], g[16][3];
+  float c[4][3], g[4][3], t0[3], g0[3] = {0.f, 0.f, 0.f};
+  const float xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
+  own_coeffs(a, p, q, c, t0);
 #pragma unroll
-  for (int k = 0; k < 16; ++k)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      c[k][ch] = a.sh[p * kShCoeffs + 3 * k + ch];
-      g[k][ch] = 0.f;
-    }
-#pragma unroll
-  for (int ch = 0; ch < 3; ++ch) c[0][ch] = zero_order(a, p, a.sh + p * kShCoeffs, ch);
+    for (int ch = 0; ch < 3; ++ch) g[i][ch] = 0.f;
   for (int v = 0; v < a.V; ++v) {
     const int64_t i = (int64_t)v * a.P + p;
-    if (a.tile_counts[i] == 0) continue;
-    float x, y, z, Y[16];
-    view_dir(a, v, p, x, y, z);
-    sh_basis(x, y, z, Y);
     float* gv = a.gview + i * kGViewFloats;
-    float gc[3];
+    float gc[3] = {gv[18], gv[19], gv[20]};  // in flight together with the count
+    if (a.tile_counts[i] == 0) continue;
+    float x, y, z, Y[16], Yq[4], s[3];
+    view_dir(a, v, xb, x, y, z);
+    sh_basis(x, y, z, Y);
+    own_basis(Y, q, Yq);
+    group_colour(c, t0, Yq, s);
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
-      float s = 0.5f;
-#pragma unroll
-      for (int k = 0; k < 16; ++k) s = __builtin_fmaf(Y[k], c[k][ch], s);
-      gc[ch] = s > 0.f ? gv[18 + ch] : 0.f;
+      if (!(s[ch] > 0.f)) gc[ch] = 0.f;
+      g0[ch] = __builtin_fmaf(gc[ch], kSh0, g0[ch]);
     }
-    float w[16];
+    float wq[4], w[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 0; k < 4; ++k) {
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) g[k][ch] = __builtin_fmaf(gc[ch], Y[k], g[k][ch]);
-      w[k] = gc[0] * c[k][0] + gc[1] * c[k][1] + gc[2] * c[k][2];
+      for (int ch = 0; ch < 3; ++ch) g[k][ch] = __builtin_fmaf(gc[ch], Yq[k], g[k][ch]);
+      wq[k] = gc[0] * c[k][0] + gc[1] * c[k][1] + gc[2] * c[k][2];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {  // every lane gets all sixteen
+      w[k] = dpp_f32<0x00>(wq[k]);
+      w[4 + k] = dpp_f32<0x55>(wq[k]);
+      w[8 + k] = dpp_f32<0xAA>(wq[k]);
+      w[12 + k] = dpp_f32<0xFF>(wq[k]);
     }
     float gx, gy, gz;
     sh_weighted_grad(x, y, z, w, gx, gy, gz);
-    gv[21] = gx;
-    gv[22] = gy;
-    gv[23] = gz;
+    if (q < 3) gv[21 + q] = q == 0 ? gx : q == 1 ? gy : gz;
   }
   if (a.g_sh) {
+    float* r = a.g_sh + p * kShCoeffs + 12 * q;
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
+    for (int k = 0; k < 4; ++k)
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) put_grad(a.g_sh + p * kShCoeffs + 3 * k + ch, g[k][ch], a.accumulate);
+      for (int ch = 0; ch < 3; ++ch) put_grad<ADD>(r + 3 * k + ch, g[k][ch]);
   }
   // the time coefficients: d S0(xi) / d sh_t[k][c] = tb_k
   // (zero where the colour does not depend on the time)
-  if (a.g_sh_t && (a.sh_t || !a.accumulate)) {
+  if (a.g_sh_t && (a.sh_t || !ADD)) {
+    float* r = a.g_sh_t + p * (kShTime * 3) + 9 * q;
 #pragma unroll
-    for (int k = 0; k < kShTime; ++k)
+    for (int k = 0; k < 3; ++k) {
+      const float tb = own_time(a, q, k);
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch)
-        put_grad(a.g_sh_t + p * (kShTime * 3) + 3 * k + ch, a.sh_t ? a.tb[k] * g[0][ch] : 0.f, a.accumulate);
+      for (int ch = 0; ch < 3; ++ch) put_grad<ADD>(r + 3 * k + ch, a.sh_t ? tb * g0[ch] : 0.f);
+    }
   }
 }
 
 hipError_t launch_sh_fwd(const ShArgs& a, hipStream_t st) {
-  const int64_t n = (int64_t)a.V * a.P;
+  const int64_t n = (int64_t)a.V * a.P * kGroup;
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(sh_fwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
@@ -182,7 +240,11 @@ hipError_t launch_sh_fwd(const ShArgs& a, hipStream_t st) {
 
 hipError_t launch_sh_bwd(const ShArgs& a, hipStream_t st) {
   if (a.P <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sh_bwd_kernel, dim3((unsigned)((a.P + 127) / 128)), dim3(128), 0, st, a);
+  const dim3 grid((unsigned)((a.P * kGroup + 255) / 256)), block(256);
+  if (a.accumulate)
+    hipLaunchKernelGGL(sh_bwd_kernel<true>, grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL(sh_bwd_kernel<false>, grid, block, 0, st, a);
   return hipGetLastError();
 }
 

@@ -235,8 +235,13 @@ struct PreBwdArgs {
   int32_t accumulate_centers;  // the same for the centres, which the colour networks' adjoints write first
 };
 
-// a gradient entry, added to what is there or stored
-__device__ __forceinline__ void put_grad(float* p, float g, bool add) { *p = add ? *p + g : g; }
+// A gradient entry, added to what is there or stored.  The kernels take the
+// choice as a template argument: a flag would put a branch around every load,
+// and each would wait for the one before.
+template <bool ADD>
+__device__ __forceinline__ void put_grad(float* p, float g) {
+  *p = ADD ? *p + g : g;
+}
 
 // per-ray relighting colour (colour mode 4): the preprocess side
 struct RayColourArgs {
