@@ -77,19 +77,17 @@ __device__ __forceinline__ void view_dir(const ShArgs& a, int v, const float (&x
 
 // Four lanes per primitive (kGroup): lane q holds the coefficients 4 q .. 4 q
 // + 3 and the time coefficients 3 q .. 3 q + 2, a quarter of a row each, so
-// that a wave reads and writes whole runs of memory; the channels' sums meet
-// over the group.  Bound by that traffic (100k primitives; a thread per
-// primitive before: forward of one view 18 -> 8.9 us, of two views with the
-// time term 38 -> 15.6 us, adjoint 21 -> 16 us and 40 -> 23 us).
+// that a wave reads and writes whole runs of memory.  A channel's sum passes
+// from lane to lane, so that its terms are added in the order of k.  Bound by that traffic (100k primitives; a thread per
+// primitive before: forward of one view 18 -> 8.1 us, of two views with the
+// time term 38 -> 16.4 us, adjoint 21 -> 18 us and 40 -> 23.6 us; adding the
+// lanes' shares in a tree instead takes 1 us less and rounds differently).
 static_assert(kGroup == 4 && kShTime == 12, "a quarter of the rows per lane");
 
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float group_sum_f32(float x) {
-  x += dpp_f32<0xB1>(x);         // quad_perm 1,0,3,2
-  return x + dpp_f32<0x4E>(x);   // quad_perm 2,3,0,1
+// lane L's value of each group of four
+template <int L>
+__device__ __forceinline__ float group_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x55 * L, 0xF, 0xF, false));  // quad_perm L,L,L,L
 }
 
 // the value of lane q's quarter.  (By value, in registers: an index or a
@@ -111,37 +109,42 @@ __device__ __forceinline__ float own_time(const ShArgs& a, int q, int k) {
   return pick4(a.tb[k], a.tb[3 + k], a.tb[6 + k], a.tb[9 + k], q);
 }
 
-// this lane's coefficients, the time-dependent part of the zero-order
-// coefficient included (as a share of c[0], which only the sums over the
-// group make whole: lane 0 alone carries Y_0)
-__device__ __forceinline__ void own_coeffs(const ShArgs& a, int64_t p, int q, float (&c)[4][3], float (&t0)[3]) {
+// x[ch] = fma(f[i], r[i][ch], x[ch]) for i = FROM .. n - 1 with lane L's f
+// and r, the result in every lane
+template <int L, int FROM, int n>
+__device__ __forceinline__ void chain(const float (&f)[n], const float (&r)[n][3], float (&x)[3]) {
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) {
+    float y = x[ch];
+#pragma unroll
+    for (int i = FROM; i < n; ++i) y = __builtin_fmaf(f[i], r[i][ch], y);
+    x[ch] = group_lane<L>(y);
+  }
+}
+
+// this lane's coefficients and the zero-order coefficient of the primitive
+// (time dependent with sh_t)
+__device__ __forceinline__ void own_coeffs(const ShArgs& a, int64_t p, int q, float (&c)[4][3], float (&zo)[3]) {
   const float* r = a.sh + p * kShCoeffs + 12 * q;
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) c[i][ch] = r[3 * i + ch];
 #pragma unroll
-  for (int ch = 0; ch < 3; ++ch) t0[ch] = 0.f;
+  for (int ch = 0; ch < 3; ++ch) zo[ch] = group_lane<0>(c[0][ch]);
   if (a.sh_t) {
     const float* t = a.sh_t + p * (kShTime * 3) + 9 * q;
+    float f[3], tc[3][3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const float tb = own_time(a, q, k);
+      f[k] = own_time(a, q, k);
 #pragma unroll
-      for (int ch = 0; ch < 3; ++ch) t0[ch] = __builtin_fmaf(tb, t[3 * k + ch], t0[ch]);
+      for (int ch = 0; ch < 3; ++ch) tc[k][ch] = t[3 * k + ch];
     }
-  }
-}
-
-// colour into the record, before the clamp at zero
-__device__ __forceinline__ void group_colour(const float (&c)[4][3], const float (&t0)[3], const float (&Yq)[4],
-                                             float (&s)[3]) {
-#pragma unroll
-  for (int ch = 0; ch < 3; ++ch) {
-    float x = kSh0 * t0[ch];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x = __builtin_fmaf(Yq[i], c[i][ch], x);
-    s[ch] = 0.5f + group_sum_f32(x);
+    chain<0, 0>(f, tc, zo);
+    chain<1, 0>(f, tc, zo);
+    chain<2, 0>(f, tc, zo);
+    chain<3, 0>(f, tc, zo);
   }
 }
 
@@ -152,13 +155,18 @@ __global__ void __launch_bounds__(256) sh_fwd_kernel(ShArgs a) {
   if (i >= (int64_t)a.V * a.P || a.tile_counts[i] == 0) return;  // whole groups
   const int v = (int)(i / a.P);
   const int64_t p = i - (int64_t)v * a.P;
-  float x, y, z, Y[16], Yq[4], c[4][3], t0[3], s[3];
+  float x, y, z, Y[16], Yq[4], c[4][3], zo[3], s[3] = {0.5f, 0.5f, 0.5f};
   const float xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
-  own_coeffs(a, p, q, c, t0);
+  own_coeffs(a, p, q, c, zo);
   view_dir(a, v, xb, x, y, z);
   sh_basis(x, y, z, Y);
   own_basis(Y, q, Yq);
-  group_colour(c, t0, Yq, s);
+  chain<0, 1>(Yq, c, s);
+  chain<1, 0>(Yq, c, s);
+  chain<2, 0>(Yq, c, s);
+  chain<3, 0>(Yq, c, s);
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) s[ch] = __builtin_fmaf(Y[0], zo[ch], s[ch]);
   if (q < 3) a.records[i * kRecFloats + 11 + 4 * q] = fmaxf(q == 0 ? s[0] : q == 1 ? s[1] : s[2], 0.f);
 }
 
@@ -171,9 +179,9 @@ __global__ void __launch_bounds__(256) sh_bwd_kernel(ShArgs a) {
   const int64_t p = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
   const int q = (int)(threadIdx.x % kGroup);
   if (p >= a.P) return;
-  float c[4][3], g[4][3], t0[3], g0[3] = {0.f, 0.f, 0.f};
+  float c[4][3], g[4][3], zo[3], g0[3] = {0.f, 0.f, 0.f};
   const float xb[3] = {a.centers[3 * p], a.centers[3 * p + 1], a.centers[3 * p + 2]};
-  own_coeffs(a, p, q, c, t0);
+  own_coeffs(a, p, q, c, zo);
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -187,7 +195,12 @@ __global__ void __launch_bounds__(256) sh_bwd_kernel(ShArgs a) {
     view_dir(a, v, xb, x, y, z);
     sh_basis(x, y, z, Y);
     own_basis(Y, q, Yq);
-    group_colour(c, t0, Yq, s);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) s[ch] = __builtin_fmaf(Y[0], zo[ch], 0.5f);
+    chain<0, 1>(Yq, c, s);
+    chain<1, 0>(Yq, c, s);
+    chain<2, 0>(Yq, c, s);
+    chain<3, 0>(Yq, c, s);
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
       if (!(s[ch] > 0.f)) gc[ch] = 0.f;
@@ -202,10 +215,10 @@ __global__ void __launch_bounds__(256) sh_bwd_kernel(ShArgs a) {
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {  // every lane gets all sixteen
-      w[k] = dpp_f32<0x00>(wq[k]);
-      w[4 + k] = dpp_f32<0x55>(wq[k]);
-      w[8 + k] = dpp_f32<0xAA>(wq[k]);
-      w[12 + k] = dpp_f32<0xFF>(wq[k]);
+      w[k] = group_lane<0>(wq[k]);
+      w[4 + k] = group_lane<1>(wq[k]);
+      w[8 + k] = group_lane<2>(wq[k]);
+      w[12 + k] = group_lane<3>(wq[k]);
     }
     float gx, gy, gz;
     sh_weighted_grad(x, y, z, w, gx, gy, gz);
