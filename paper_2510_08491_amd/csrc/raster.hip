@@ -25,6 +25,8 @@
 // Per-pair gradients of the table entries and of the record coefficients are
 // summed over the wave with DPP and added to per-primitive / per-(view,
 // primitive) accumulators with one atomic per value per wave.
+#include <type_traits>
+
 #include "snp_internal.h"
 
 namespace snp {
@@ -71,10 +73,11 @@ struct PixelBlock {
   int pix[PPL];  // index into the packed image, -1 if outside
   int loc[PPL];  // index in the tile
   int wx0, wx1, wy0, wy1;  // pixel block of this thread's wave
-  __device__ void init(const CamDev& cam, int tx, int ty) {
+  // w: the 8 x 8 block of this thread's wave (kBlocks), by default its wave index
+  __device__ void init(const CamDev& cam, int tx, int ty, int w = (int)(threadIdx.x / 64)) {
     int lx, ly0;
     if constexpr (kBlocks) {
-      const int w = (int)(threadIdx.x / 64), l = (int)(threadIdx.x % 64);
+      const int l = (int)(threadIdx.x % 64);
       const int bx = w % (TW / 8), by = w / (TW / 8);
       lx = bx * 8 + l % 8;
       ly0 = by * 8 + l / 8;
@@ -160,16 +163,15 @@ struct ColourStage {
 
 // Stages one batch: instance ids and rectangles, records and tables (and,
 // with a colour stage, the colour tables and biases), gathered by primitive
-// id as float4.  The
-// threads that gather read the id from global memory themselves, so one
-// barrier (at the end) suffices.  The caller's previous barrier (the end of
-// the previous batch, or the work-queue fetch) guarantees nobody still
-// reads the stage.
+// id as float4.  The threads that gather (tid: this one among the NT) read
+// the id from global memory themselves, so one barrier, the caller's after the
+// call, suffices.  The caller's previous barrier (the end of the previous
+// batch, or the work-queue fetch) guarantees nobody still reads the stage.
 template <int N, int NT, int B, int CD = 0>
-__device__ __forceinline__ void stage_batch(Stage<N, B>& S, const RasterArgs& a, int v, uint32_t b0, int nb,
+__device__ __forceinline__ void stage_batch(Stage<N, B>& S, const RasterArgs& a, int v, uint32_t b0, int nb, int tid,
                                             ColourStage<(CD > 0 ? CD : 1), B>* cs = nullptr) {
   const int64_t vbase = (int64_t)v * a.P;
-  for (int t = threadIdx.x; t < nb; t += NT) {
+  for (int t = tid; t < nb; t += NT) {
     const uint32_t p = a.values[b0 + t];
     S.id[t] = p;
     S.rect[t] = reinterpret_cast<const int4*>(a.rects)[vbase + p];
@@ -178,7 +180,7 @@ __device__ __forceinline__ void stage_batch(Stage<N, B>& S, const RasterArgs& a,
   const float4* tab4 = reinterpret_cast<const float4*>(a.table);
   constexpr int F = Stage<N, B>::F;
   constexpr int T4 = Stage<N, B>::TS / 4;
-  for (int idx = threadIdx.x; idx < nb * F; idx += NT) {
+  for (int idx = tid; idx < nb * F; idx += NT) {
     const int j = idx / F, c = idx - j * F;
     const uint32_t p = a.values[b0 + j];
     if (c < 6)
@@ -190,7 +192,7 @@ __device__ __forceinline__ void stage_batch(Stage<N, B>& S, const RasterArgs& a,
     constexpr int C4 = ColourStage<CD, B>::T4;
     const float4* ct4 = reinterpret_cast<const float4*>(a.ctab);
     const float4* cb4 = reinterpret_cast<const float4*>(a.cbias);
-    for (int idx = threadIdx.x; idx < nb * (C4 + 4); idx += NT) {
+    for (int idx = tid; idx < nb * (C4 + 4); idx += NT) {
       const int j = idx / (C4 + 4), c = idx - j * (C4 + 4);
       const uint32_t p = a.values[b0 + j];
       if (c < C4)
@@ -199,7 +201,6 @@ __device__ __forceinline__ void stage_batch(Stage<N, B>& S, const RasterArgs& a,
         cs->b[j][c - C4] = cb4[(vbase + p) * 4 + (c - C4)];
     }
   }
-  __syncthreads();
 }
 
 // The per-ray colour network on one pair: the entry point u (unit-sphere
@@ -456,9 +457,10 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
     for (uint32_t b0 = start; b0 < end; b0 += FB) {
       const int nb = (int)min((uint32_t)FB, end - b0);
       if constexpr (CD > 0)
-        stage_batch<N, NT, FB, CD>(S, a, v, b0, nb, &CS);
+        stage_batch<N, NT, FB, CD>(S, a, v, b0, nb, threadIdx.x, &CS);
       else
-        stage_batch<N, NT, FB>(S, a, v, b0, nb);
+        stage_batch<N, NT, FB>(S, a, v, b0, nb, threadIdx.x);
+      __syncthreads();
 #pragma unroll 1
       for (unsigned long long m = meets_wave(S, pb, nb); m; m &= m - 1) {
         const int j = __builtin_ctzll(m);
@@ -552,6 +554,124 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
       atomicAdd(&a.counters[CNT_HIT_PAIRS], tot);
       atomicAdd(&a.counters[CNT_LIVE_PAIRS], live);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// forward for launches of few tiles: WIDE waves per 8 x 8 block of a 16 x 16 tile
+// ---------------------------------------------------------------------------
+// One wave alone on a SIMD issues an instruction every five cycles or so, two
+// to three times slower than the SIMD can with several waves, and a launch of
+// few tiles leaves SIMDs with one wave, or with none once the lighter tiles
+// have ended.  Here the waves of a block share its instances: each batch is
+// evaluated (geometry, density integral, alpha) by all waves, every wave
+// taking its share of the instances that meet its block, and the alphas go to
+// LDS; then the block's first wave blends them in depth order -- a tenth of
+// the work -- while the other waves stage the next batch.  The arithmetic per
+// pair and the blending order are render_fwd_kernel's, so the images are the
+// same bit for bit; a pixel that ends inside a batch is left out of the
+// evaluation from the next batch on.  Times and the choice: wide_fwd.
+template <int N>
+constexpr int wide_batch() { return N >= 32 ? 16 : 32; }
+
+template <int N, int WIDE>
+__global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs a) {
+  static_assert(WIDE == 2 || WIDE == 4, "waves per block");
+  constexpr int NPIX = 256, NT = NPIX * WIDE, NB4 = 4;
+  constexpr int FB = wide_batch<N>();
+  __shared__ Stage<N, FB> S;
+  __shared__ float s_al[FB][NPIX];       // alpha of each evaluated (instance, pixel), 0 where it does not blend
+  __shared__ float4 s_col[2][FB];        // colours of the batch being blended and of the one being staged
+  __shared__ uint32_t s_mask[NB4];       // bit j: some pixel of the block meets instance j
+  __shared__ unsigned long long s_done[NB4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = wave / NB4;
+  // the waves of a block sit on different SIMDs
+  const int blk = (wave + 2 * sub) & (NB4 - 1);
+  const bool blends = wave < NB4;
+  if (threadIdx.x < NB4) s_mask[threadIdx.x] = 0u;
+  // ids, rectangles, records, tables and colours of a batch, by NTH threads
+  auto stage = [&](auto nth, int v, uint32_t b0, int nb, int buf, int tid) {
+    constexpr int NTH = decltype(nth)::value;
+    stage_batch<N, NTH, FB>(S, a, v, b0, nb, tid);
+    for (int t = tid; t < nb; t += NTH) {
+      const float* rec = a.records + ((int64_t)v * a.P + a.values[b0 + t]) * kRecFloats;
+      s_col[buf][t] = make_float4(rec[11], rec[15], rec[19], 0.f);
+    }
+  };
+  const int tile = a.tile_order ? (int)a.tile_order[blockIdx.x] : (int)blockIdx.x;
+  const int v = view_of_tile(a.cams, a.V, tile);
+  const CamDev& cam = a.cams[v];
+  const int local = tile - cam.tile_base;
+  const int ty = local / cam.ntx, tx = local - ty * cam.ntx;
+  PixelBlock<16, 16, 1> pb;
+  pb.init(cam, tx, ty, blk);
+  const bool outside = pb.pix[0] < 0;
+  float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
+  bool done = outside;
+  unsigned long long dmask = __ballot(outside);  // pixels of the block that take no more primitives
+  const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
+  if (start < end) stage(std::integral_constant<int, NT>{}, v, start, (int)min((uint32_t)FB, end - start), 0, threadIdx.x);
+  __syncthreads();
+  int buf = 0;
+  for (uint32_t b0 = start; b0 < end; b0 += FB, buf ^= 1) {
+    const int nb = (int)min((uint32_t)FB, end - b0);
+    // ---- evaluation: this wave's share of the instances that meet its block
+    unsigned long long m = dmask != ~0ull ? meets_wave(S, pb, nb) : 0ull;
+    for (int t = 0; m; m &= m - 1, ++t) {
+      if ((t & (WIDE - 1)) != sub) continue;
+      const int j = __builtin_ctzll(m);
+      PairGeom g[1];
+      const bool gh = pair_geom(S.rec[j][0], S.rec[j][1], S.rec[j][2], S.rec[j][3], S.rec[j][4], S.rec[j][5],
+                                pb.pxc[0], pb.pyc[0], g[0], disc_coef_of(S, a, v, j));
+      const bool hit = gh && !((dmask >> lane) & 1ull);
+      if (__ballot(hit) == 0) continue;  // wave-uniform
+      float Q[1];
+      unit_sum<N, 1>(S.tab[j], g, Q);
+      const float b2 = reinterpret_cast<const float*>(S.tab[j])[5 * N];
+      const float ahat = 2.f * pb.L[0] * g[0].H * (Q[0] + b2);
+      if (a.ahat_cache && (int64_t)(b0 + j) < a.cache_instances)
+        a.ahat_cache[(int64_t)(b0 + j) * NPIX + pb.loc[0]] = ahat;
+      const float al0 = alpha_of(ahat, a.alpha_max);
+      s_al[j][blk * 64 + lane] = hit && !(a.alpha_min > 0.f && al0 < a.alpha_min) ? al0 : 0.f;
+      if (lane == 0) atomicOr(&s_mask[blk], 1u << j);
+    }
+    __syncthreads();
+    if (blends) {
+      // ---- blending, in depth order; the next alpha is read ahead
+      uint32_t h = s_mask[blk];
+      float al_next = h ? s_al[__builtin_ctz(h)][blk * 64 + lane] : 0.f;
+      while (h) {
+        const int j = __builtin_ctz(h);
+        h &= h - 1;
+        const float al = done ? 0.f : al_next;
+        const float4 col = s_col[buf][j];
+        if (h) al_next = s_al[__builtin_ctz(h)][blk * 64 + lane];
+        const float w = al * T;
+        C0 = __builtin_fmaf(col.x, w, C0);
+        C1 = __builtin_fmaf(col.y, w, C1);
+        C2 = __builtin_fmaf(col.z, w, C2);
+        T = T * (1.f - al);
+        done = done || T < a.t_eps;
+      }
+      const unsigned long long d = __ballot(done);
+      if (lane == 0) {
+        s_mask[blk] = 0u;
+        s_done[blk] = d;
+      }
+    } else if (b0 + FB < end) {
+      stage(std::integral_constant<int, NT - NPIX>{}, v, b0 + FB, (int)min((uint32_t)FB, end - b0 - FB), buf ^ 1,
+            threadIdx.x - NPIX);
+    }
+    __syncthreads();
+    dmask = s_done[blk];
+    if ((s_done[0] & s_done[1] & s_done[2] & s_done[3]) == ~0ull) break;
+  }
+  if (blends && !outside) {
+    const int64_t px = cam.pix_base + pb.pix[0];
+    a.images[3 * px + 0] = C0 + T * a.bg0;
+    a.images[3 * px + 1] = C1 + T * a.bg1;
+    a.images[3 * px + 2] = C2 + T * a.bg2;
+    a.final_T[px] = T;
   }
 }
 
@@ -952,6 +1072,11 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // registers spill at 5); 4 at N <= 8, where the spilled part is a larger share
 // of a chunk (4.10 against 4.30 ms).
 //
+// Launches of few tiles (WIDE > 1, see wide_bwd): WIDE - 1 further waves per
+// pixel wave take part in staging, phase 2 and the flush, and wait out phase
+// 1; with batches of 16 or 32 instances there are chunks for all of them (212
+// tiles, 16 waves: batches of 8 0.397 ms, 16 0.270, 32 0.220).
+//
 // With the per-ray colour network (CD > 0, colour mode 4) phase 1 evaluates
 // each pair's colour, lists every pair that blends (alpha > 0) with its
 // weight alpha T, and phase 2 adds the network's adjoint: the weight
@@ -959,10 +1084,11 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // (and the per-(view, primitive) bias gradient), the colour offset into the
 // record gradient, and the entry point's and direction's gradients into the
 // geometry chain.
-template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0>
-__global__ void __launch_bounds__(TW * TH) __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 ? 4 : 5)))
-render_bwd_kernel(RasterArgs a) {
+template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0, int WIDE = 1>
+__global__ void __launch_bounds__(TW * TH * WIDE)
+__attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) render_bwd_kernel(RasterArgs a) {
   constexpr int NT = TW * TH;
+  constexpr int NA = NT * WIDE;  // threads: one per pixel and the helpers of phase 2
   constexpr int NW = NT / 64;
   // chunks of phase 2 take rows of different instances (the per-ray colour
   // network's sums go to global memory once per chunk, so it takes one instance)
@@ -985,7 +1111,8 @@ render_bwd_kernel(RasterArgs a) {
   // selector bits and value index of the transposed row reductions
   const bool sel1 = lane & 4, sel2 = lane & 1, sel3 = lane & 2, sel4 = lane & 8;
   const int idx16 = 8 * ((lane >> 3) & 1) + 4 * ((lane >> 1) & 1) + 2 * (lane & 1) + ((lane >> 2) & 1);
-  for (int idx = threadIdx.x; idx < NB * ACC; idx += NT) (&s_acc[0][0])[idx] = 0.f;
+  const bool helper = WIDE > 1 && wave >= NW;
+  for (int idx = threadIdx.x; idx < NB * ACC; idx += NA) (&s_acc[0][0])[idx] = 0.f;
   int item = first_item(a.cus);
   while (true) {
     if (item >= a.total_tiles) break;
@@ -995,9 +1122,9 @@ render_bwd_kernel(RasterArgs a) {
     const int local = tile - cam.tile_base;
     const int ty = local / cam.ntx, tx = local - ty * cam.ntx;
     PixelBlock<TW, TH, 1> pb;
-    pb.init(cam, tx, ty);
+    pb.init(cam, tx, ty, wave % NW);
     float T = 1.f;
-    bool done = pb.pix[0] < 0;
+    bool done = helper || pb.pix[0] < 0;
     const int64_t pxi = cam.pix_base + (done ? 0 : pb.pix[0]);
     const float G0 = done ? 0.f : a.dL[3 * pxi + 0];
     const float G1 = done ? 0.f : a.dL[3 * pxi + 1];
@@ -1012,9 +1139,10 @@ render_bwd_kernel(RasterArgs a) {
       const int nb = (int)min((uint32_t)NB, end - b0);
       if (threadIdx.x < NB * NW) (&s_cnt[0][0])[threadIdx.x] = 0u;
       if constexpr (CD > 0)
-        stage_batch<N, NT, NB, CD>(S, a, v, b0, nb, &CS);
+        stage_batch<N, NA, NB, CD>(S, a, v, b0, nb, threadIdx.x, &CS);
       else
-        stage_batch<N, NT, NB>(S, a, v, b0, nb);
+        stage_batch<N, NA, NB>(S, a, v, b0, nb, threadIdx.x);
+      __syncthreads();
       // ---------------- phase 1: pixels ----------------
       // Blends instance j into this thread's pixel: T, the behind colour, the
       // colour gradient, and the pair's entry in the live list.  c: the pair's
@@ -1120,7 +1248,7 @@ render_bwd_kernel(RasterArgs a) {
           if (((m >> j) & 1u) && __ballot(pre[j] > 0.f && !done) != 0) pixel_step(j, true, pre[j]);
         }
       } else {
-        for (uint32_t m = (uint32_t)meets_wave(S, pb, nb); m; m &= m - 1) pixel_step(__builtin_ctz(m), false, 0.f);
+        for (uint32_t m = helper ? 0u : (uint32_t)meets_wave(S, pb, nb); m; m &= m - 1) pixel_step(__builtin_ctz(m), false, 0.f);
       }
       __syncthreads();
       // ---------------- phase 2: live pairs ----------------
@@ -1140,7 +1268,7 @@ render_bwd_kernel(RasterArgs a) {
       }
       // (lanes past the last instance repeat its end)
       const uint32_t total = __builtin_amdgcn_readlane(rsum, NB - 1);
-      for (uint32_t q0 = 4 * wave; q0 < total; q0 += 4 * NW) {
+      for (uint32_t q0 = 4 * wave; q0 < total; q0 += 4 * NW * WIDE) {
         {
           // this row's instance: the number of instances that end at or before
           // it, counted over the lanes for each of the chunk's rows (rows past
@@ -1395,7 +1523,7 @@ render_bwd_kernel(RasterArgs a) {
       // flush the batch's accumulators to HBM (one float atomic per nonzero
       // value, spread over the workgroup) and clear them
       __syncthreads();
-      for (int idx = threadIdx.x; idx < nb * ACC; idx += NT) {
+      for (int idx = threadIdx.x; idx < nb * ACC; idx += NA) {
         const int jj = idx / ACC, cc = idx - jj * ACC;
         float* slot = &s_acc[jj][cc];
         float val = *slot;
@@ -1461,10 +1589,38 @@ static int persistent_grid(K kernel, int threads, const RasterArgs& a) {
   return g < 1 ? 1 : g;
 }
 
+// Waves per 8 x 8 block (and per-pixel wave of the backward) by the launch's
+// tiles per CU; 1: the plain kernels.  A workgroup of 1024 threads has a CU
+// to itself, so it pays up to 2.5 tiles per CU, two of 512 up to 5 (forward)
+// or 6 (backward); beyond, the plain kernels keep the SIMDs full by
+// themselves and the waiting waves of the wide ones only take slots.  ms,
+// N = 16 unless noted, 256 CUs, plain / 2 waves / 4 waves (forward; backward):
+//   212 tiles (3001 primitives)   0.233 / 0.184 / 0.151;  0.460 / 0.279 / 0.220
+//   510 (100k)                    1.89 / 1.53 / 1.21;     4.67 / 2.92 / 2.25
+//   660 (20k)                     0.381 / 0.305 / 0.273;  0.939 / 0.598 / 0.604
+//   875 (20k, N = 8)              0.254 / 0.208 / 0.247;  0.645 / 0.443 / 0.529
+//   1200 (100k, N = 8)            1.14 / 0.946 / 1.32;    2.95 / 2.24 / 2.91
+//   1540 (100k, N = 8)            1.11 / 1.08 / 1.53;     2.90 / 2.60 / 3.37
+//   1900 (100k)                   1.58 / 1.81 / 2.60;     4.20 / 4.43 / 5.47
+static int wide_fwd(const RasterArgs& a) {
+  return 2 * (int64_t)a.total_tiles <= 5 * (int64_t)a.cus ? 4 : a.total_tiles <= 5 * (int64_t)a.cus ? 2 : 1;
+}
+static int wide_bwd(const RasterArgs& a) {
+  return 2 * (int64_t)a.total_tiles <= 5 * (int64_t)a.cus ? 4 : a.total_tiles <= 6 * (int64_t)a.cus ? 2 : 1;
+}
+
 template <int N, int TW, int TH, int PPL, int CD = 0>
 static hipError_t fwd_shape(const RasterArgs& a, bool persist, bool count, hipStream_t st) {
   constexpr int NT = TW * TH / PPL;
   if (a.total_tiles <= 0) return hipSuccess;
+  if constexpr (TW == 16 && TH == 16 && PPL == 1 && CD == 0) {
+    const int wide = count ? 1 : wide_fwd(a);
+    if (wide == 4)
+      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 4>), dim3(a.total_tiles), dim3(NT * 4), 0, st, a);
+    else if (wide == 2)
+      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 2>), dim3(a.total_tiles), dim3(NT * 2), 0, st, a);
+    if (wide > 1) return hipGetLastError();
+  }
   if (persist) {
     if (count) {
       auto k = render_fwd_kernel<N, TW, TH, PPL, true, true, CD>;
@@ -1510,6 +1666,15 @@ template <int N, int TW, int TH, int NB, int CD = 0>
 static hipError_t bwd_shape(const RasterArgs& a, bool persist, hipStream_t st) {
   constexpr int NT = TW * TH;
   if (a.total_tiles <= 0) return hipSuccess;
+  if constexpr (TW == 16 && TH == 16 && CD == 0) {
+    // (batches of their own: more rows for more waves)
+    const int wide = wide_bwd(a);
+    if (wide == 4)
+      hipLaunchKernelGGL((render_bwd_kernel<N, 16, 16, 32, false, 0, 4>), dim3(a.total_tiles), dim3(NT * 4), 0, st, a);
+    else if (wide == 2)
+      hipLaunchKernelGGL((render_bwd_kernel<N, 16, 16, 16, false, 0, 2>), dim3(a.total_tiles), dim3(NT * 2), 0, st, a);
+    if (wide > 1) return hipGetLastError();
+  }
   if (persist) {
     auto k = render_bwd_kernel<N, TW, TH, NB, true, CD>;
     hipLaunchKernelGGL(k, dim3(persistent_grid(k, NT, a)), dim3(NT), 0, st, a);
