@@ -135,7 +135,7 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   L.tile_counts = take(sizeof(uint32_t) * (size_t)VP);
   L.offsets = take(sizeof(uint32_t) * (size_t)VP);
   auto take_pairs = [&] {
-    const size_t dn = pl->depth_first ? (size_t)VP : 0, kn = order_small(VP) ? 0 : dn;
+    const size_t dn = pl->depth_first ? (size_t)VP : 0, kn = order_small(P, V) ? 0 : dn;
     for (int k = 0; k < 2; ++k) pl->dkeys[k] = take(sizeof(uint32_t) * kn);
     pl->dvals = take(sizeof(uint32_t) * kn);
     pl->order = take(sizeof(uint32_t) * dn);
@@ -172,7 +172,7 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
     pl->inst_rounds = rounds_of(cap);
     pl->pair_rounds = rounds_of(VP);
     size_t sort_bytes = sort_scratch_bytes(cap, pl->inst_rounds);
-    if (pl->depth_first && !order_small(VP))
+    if (pl->depth_first && !order_small(P, V))
       sort_bytes = std::max(sort_bytes, sort_scratch_bytes(VP, pl->pair_rounds));
     pl->sort_scratch = take(sort_bytes);
     if (off < end) off = end;
@@ -354,15 +354,15 @@ static snp_status do_bin(const snp_config* cfg, int64_t P, int32_t V, const Plan
     uint32_t* cs = wsp<uint32_t>(ws, pl.counts_sorted);
     uint32_t* od = wsp<uint32_t>(ws, pl.order);
     const uint32_t* depth = wsp<uint32_t>(ws, L.depth_bits);
-    if (order_small(VP))
-      SNP_HIP(launch_order_small(depth, counts, VP, od, cs, offsets, total, st));
+    if (order_small(P, V))
+      SNP_HIP(launch_order_small(depth, counts, P, V, od, cs, offsets, total, st));
     else
       SNP_HIP(order_pairs(depth, counts, VP, wsp<uint32_t>(ws, pl.dkeys[0]), wsp<uint32_t>(ws, pl.dkeys[1]),
                           wsp<uint32_t>(ws, pl.dvals), od, cs, pl.pair_rounds, wsp<void>(ws, pl.sort_scratch), st));
     order = od;
     counts = cs;
   }
-  if (!pl.depth_first || !order_small(VP))
+  if (!pl.depth_first || !order_small(P, V))
     SNP_HIP(scan_exclusive_u32(counts, offsets, VP, wsp<void>(ws, pl.scan_scratch),
                                reinterpret_cast<uint64_t*>(total), st));
   const bool odd = radix_passes(sort_bits(pl)) % 2 == 1;

@@ -195,19 +195,27 @@ __device__ __forceinline__ unsigned long long same_digit(uint32_t d, bool valid)
 }
 
 // ---------------------------------------------------------------------------
-// order of up to kOrderMax pairs, in one workgroup
+// order of the pairs of views of up to kOrderMax primitives, a workgroup per view
 // ---------------------------------------------------------------------------
-// Depth bits of the pairs -> their order (stable, ascending), the tile counts
-// in that order, the counts' exclusive scan and its total.  LSD radix with
-// four 8-bit passes: every wave owns 16 x 64 consecutive keys, a key's rank
-// among its wave's equal digits comes from ballots, a scan over (digit, wave)
-// gives the digits' places, and the keys change places through LDS.  Bound by
-// its own chain of barriers (one CU); against the twenty launches it stands
-// for: 3 x 3001 pairs 0.16 -> 0.04 ms, 256 pairs 0.08 -> 0.02 ms.
+// Depth bits of the pairs -> their order (view by view, ascending depth,
+// stable: the sort by tiles that follows needs no more), the tile counts in
+// that order, the counts' exclusive scan and its total.  LSD radix of 8-bit
+// passes over depth - least depth, three of them unless the depths span more
+// than a factor of four or so: every wave owns up to 16 x 64 consecutive
+// keys, a key's rank among its wave's equal digits comes from ballots, a scan
+// over (digit, wave) gives the digits' places, and the keys change places
+// through LDS.  A view's first place is the sum of the counts of the views
+// before it, which its workgroup adds up itself.  Bound by its own chain of
+// barriers and rounds (a CU per view).  3 x 3001 pairs: twenty launches of
+// passes over all pairs 0.16 ms, one workgroup for all views and four passes
+// 46 us, this 22; 2 x 7919 pairs 79 -> 39 us; 256 pairs 14 us.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderWaves = kOrderThreads / 64;
 constexpr int kOrderItems = 16;
 constexpr int kOrderMax = kOrderThreads * kOrderItems;  // 16384
+// pairs in all: the passes over all pairs cost 50 us from the start, and a
+// view's workgroup reads the counts of all views before it
+constexpr int64_t kOrderPairs = 131072;
 
 __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32_t* __restrict__ depth_bits,
                                                                     const uint32_t* __restrict__ counts, int n,
@@ -215,10 +223,12 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
                                                                     uint32_t* __restrict__ counts_sorted,
                                                                     uint32_t* __restrict__ offsets,
                                                                     unsigned long long* total_out) {
+  const int64_t v0 = (int64_t)blockIdx.x * n;  // the view's first pair
   __shared__ uint32_t s_key[kOrderMax];
   __shared__ uint16_t s_idx[kOrderMax];
   __shared__ uint16_t s_cnt[kOrderWaves][kRadix];  // count, then first place, of each (wave, digit)
   __shared__ uint64_t s_warp[kOrderWaves];
+  __shared__ uint32_t s_min, s_max;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   // rounds of 64 keys per wave: the waves share the keys evenly
   const int rounds = (n + kOrderThreads - 1) / kOrderThreads;
@@ -229,10 +239,36 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
 #pragma unroll
   for (int r = 0; r < kOrderItems; ++r) {
     const int i = first + 64 * r;
-    key[r] = r < rounds && i < n ? depth_bits[i] : 0u;
+    key[r] = r < rounds && i < n ? depth_bits[v0 + i] : 0u;
     idx[r] = (uint16_t)i;
   }
-  for (int shift = 0; shift < 32; shift += 8) {
+  // depths relative to the least (culled pairs, depth 0, stay first)
+  if (t == 0) {
+    s_min = ~0u;
+    s_max = 0u;
+  }
+  __syncthreads();
+  uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+  for (int r = 0; r < kOrderItems; ++r) {
+    lo = min(lo, key[r] - 1u);  // 0 wraps to the largest
+    hi = max(hi, key[r]);
+  }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, o));
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, o));
+  }
+  if (lane == 0) {
+    atomicMin(&s_min, lo);
+    atomicMax(&s_max, hi);
+  }
+  __syncthreads();
+  const uint32_t least = s_min, most = s_max;  // (least depth - 1: the differences start at 1)
+#pragma unroll
+  for (int r = 0; r < kOrderItems; ++r) key[r] = key[r] ? key[r] - least : 0u;
+  const int bits = most ? 32 - __builtin_clz(most - least) : 0;
+  for (int shift = 0; shift < bits; shift += 8) {
     for (int i = t; i < kRadix * kOrderWaves / 2; i += kOrderThreads) reinterpret_cast<uint32_t*>(s_cnt)[i] = 0u;
     __syncthreads();
     uint16_t rank[kOrderItems];
@@ -290,36 +326,39 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
   for (int r = 0; r < kOrderItems; ++r) {
     const int i = first + 64 * r;
     if (r < rounds && i < n) {
-      const uint32_t cnt = counts[idx[r]];
-      order[i] = idx[r];
-      counts_sorted[i] = cnt;
+      const uint32_t cnt = counts[v0 + idx[r]];
+      order[v0 + i] = (uint32_t)v0 + idx[r];
+      counts_sorted[v0 + i] = cnt;
       s_key[i] = cnt;
     }
   }
+  uint64_t sum = 0, before = 0;
+  for (int64_t i = t; i < v0; i += kOrderThreads) sum += counts[i];
+  if (v0) block_exclusive_scan<kOrderThreads>(sum, &before, s_warp);
   __syncthreads();
-  uint64_t sum = 0;
+  sum = 0;
   for (int k = 0; k < rounds; ++k) {
     const int i = t * rounds + k;
     sum += i < n ? s_key[i] : 0u;
   }
   uint64_t total;
-  uint64_t run = block_exclusive_scan<kOrderThreads>(sum, &total, s_warp);
+  uint64_t run = before + block_exclusive_scan<kOrderThreads>(sum, &total, s_warp);
   for (int k = 0; k < rounds; ++k) {
     const int i = t * rounds + k;
     if (i < n) {
-      offsets[i] = (uint32_t)run;
+      offsets[v0 + i] = (uint32_t)run;
       run += s_key[i];
     }
   }
-  if (t == 0) *total_out = total;
+  if (t == 0 && blockIdx.x == gridDim.x - 1) *total_out = before + total;
 }
 
-bool order_small(int64_t n) { return n <= kOrderMax; }
+bool order_small(int64_t P, int32_t V) { return P <= kOrderMax && P * V <= kOrderPairs; }
 
-hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t n, uint32_t* order,
+hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t P, int32_t V, uint32_t* order,
                               uint32_t* counts_sorted, uint32_t* offsets, unsigned long long* total_out,
                               hipStream_t st) {
-  hipLaunchKernelGGL(order_small_kernel, dim3(1), dim3(kOrderThreads), 0, st, depth_bits, counts, (int)n, order,
+  hipLaunchKernelGGL(order_small_kernel, dim3((unsigned)V), dim3(kOrderThreads), 0, st, depth_bits, counts, (int)P, order,
                      counts_sorted, offsets, total_out);
   return hipGetLastError();
 }
