@@ -292,6 +292,12 @@ snp_status snp_render_backward(const snp_config* cfg, const snp_prims* prims, in
                                void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
                                const snp_grads* grads, hipStream_t stream);
 
+/* snp_render_backward that sets `grads` instead of adding into it (every
+ * element of the tensors the colour mode uses, whatever they held before). */
+snp_status snp_render_backward_set(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
+                                   void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
+                                   const snp_grads* grads, hipStream_t stream);
+
 /* One whole training step: preprocess, bin, sort, forward,
  * L1 loss against `targets` (mean over n_norm elements), backward.  Sets
  * `grads`, whatever they held before. */

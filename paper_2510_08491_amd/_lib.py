@@ -87,6 +87,7 @@ def lib():
         "snp_render_forward": [cfg, prims, I32, cams, VP, lay, VP, VP, I32, VP],
         "snp_loss_l1": [cfg, I32, cams, VP, VP, D, VP, lay, VP, VP, VP],
         "snp_render_backward": [cfg, prims, I32, cams, VP, lay, VP, VP, grads, VP],
+        "snp_render_backward_set": [cfg, prims, I32, cams, VP, lay, VP, VP, grads, VP],
         "snp_step": [cfg, prims, I32, cams, VP, lay, VP, VP, VP, D, VP, VP, grads, VP],
         "snp_step_static": [cfg, prims, I32, cams, VP, VP, VP, D, VP, VP, grads, VP, VP],
         "snp_graph_create": [cfg, prims, I32, cams, VP, lay, VP, VP, VP, D, VP, VP, grads, VP, P(VP)],
@@ -118,7 +119,7 @@ def lib():
 
 
 EXPORTED = ["snp_workspace_layout", "snp_preprocess", "snp_bin", "snp_sort", "snp_render_forward", "snp_loss_l1",
-            "snp_render_backward", "snp_step", "snp_step_static", "snp_graph_create", "snp_graph_create_forward", "snp_graph_launch",
+            "snp_render_backward", "snp_render_backward_set", "snp_step", "snp_step_static", "snp_graph_create", "snp_graph_create_forward", "snp_graph_launch",
             "snp_graph_destroy",
             "snp_read_status", "snp_supported_tiles", "snp_status_string", "snp_selftest_wave_sum",
             "snp_read_counters", "snp_kernel_timing", "snp_kernel_timing_read", "snp_adam_step",

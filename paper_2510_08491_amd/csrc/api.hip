@@ -771,15 +771,27 @@ snp_status snp_loss_l1(const snp_config* cfg, int32_t V, const snp_camera* cams,
   return do_loss(pl, images, targets, n_norm, ws, loss_out, dL_dimages, stream);
 }
 
-snp_status snp_render_backward(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
-                               void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
-                               const snp_grads* grads, hipStream_t stream) {
+static snp_status render_backward(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
+                                  void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
+                                  const snp_grads* grads, bool accumulate, hipStream_t stream) {
   if (!cfg || !prims || !images || !dL_dimages || !grads) return SNP_ERR_INVALID;
   if (gaussian(cfg)) return SNP_ERR_UNSUPPORTED;
   Plan pl;
   SNP_TRY(plan_for(cfg, prims->P, V, cams, ws, layout, &pl));
   SNP_TRY(check_prims(cfg, prims));
-  return do_backward(cfg, prims, V, pl, ws, images, dL_dimages, grads, true, stream);
+  return do_backward(cfg, prims, V, pl, ws, images, dL_dimages, grads, accumulate, stream);
+}
+
+snp_status snp_render_backward(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
+                               void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
+                               const snp_grads* grads, hipStream_t stream) {
+  return render_backward(cfg, prims, V, cams, ws, layout, images, dL_dimages, grads, true, stream);
+}
+
+snp_status snp_render_backward_set(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
+                                   void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
+                                   const snp_grads* grads, hipStream_t stream) {
+  return render_backward(cfg, prims, V, cams, ws, layout, images, dL_dimages, grads, false, stream);
 }
 
 static snp_status do_step(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,

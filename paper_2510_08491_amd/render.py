@@ -16,6 +16,7 @@ from . import _lib as L
 PARAM_KEYS = ("centers", "scales", "quats", "w1", "b1", "w2", "b2", "colors", "cmlp", "xi", "sh", "opacity", "wt",
               "sh_t")
 XI_DIM = 8
+GRAD_KEYS = tuple(k for k, _ in L.SnpGrads._fields_)  # every parameter but the Gaussians' opacity
 
 
 @dataclasses.dataclass
@@ -97,7 +98,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle (torch.cuda.current_stream() builds a Stream
+    # around it first: 0.25 ms of host time in 25 calls, this 0.05 ms)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def params_to_device(scene: dict, device="cuda") -> Dict[str, torch.Tensor]:
@@ -207,6 +210,8 @@ class Rasterizer:
 
     # -- stages --------------------------------------------------------------------
     def _prims(self, params) -> L.SnpPrims:
+        if isinstance(params, L.SnpPrims):  # built by the caller for several stages
+            return params
         pr = L.SnpPrims()
         pr.P = self.P
         for k in PARAM_KEYS:
@@ -279,7 +284,7 @@ class Rasterizer:
 
     def grads_struct(self, grads: Dict[str, torch.Tensor]) -> L.SnpGrads:
         g = L.SnpGrads()
-        for k, _ in L.SnpGrads._fields_:
+        for k in GRAD_KEYS:
             setattr(g, k, _ptr(grads.get(k)))
         return g
 
@@ -289,6 +294,29 @@ class Rasterizer:
         L.check(L.lib().snp_render_backward(C.byref(self.ccfg), C.byref(self._prims(params)), self.V, self.ccams,
                                             self.ws_ptr, C.byref(self.layout), _ptr(images), _ptr(dL), C.byref(g),
                                             _stream()), "snp_render_backward")
+
+    def _gradients(self, params, images, dL) -> Dict[str, torch.Tensor]:
+        """d loss / d params in new tensors: set by the kernels where the
+        colour mode uses them, zero otherwise."""
+        N, mode = self.cfg.n_hidden, self.cfg.color_mode
+        width = {"centers": 3, "scales": 3, "quats": 4, "w1": 3 * N, "b1": N, "w2": N, "b2": 1, "wt": N}
+        if mode in (0, 3, 4):
+            width["colors"] = 3
+        if mode in (1, 3, 4):
+            width["cmlp"] = cmlp_param_count(self.cfg.cmlp_width, self.cfg.cmlp_depth, mode == 3, mode == 4)
+        if mode in (1, 3):
+            width["xi"] = XI_DIM
+        if mode == 2:
+            width.update(sh=48, sh_t=36)
+        grads = {}
+        for k, v in params.items():
+            if k in GRAD_KEYS:
+                grads[k] = torch.empty_like(v) if v.numel() == self.P * width.get(k, 0) else torch.zeros_like(v)
+        g = self.grads_struct(grads)
+        L.check(L.lib().snp_render_backward_set(C.byref(self.ccfg), C.byref(self._prims(params)), self.V, self.ccams,
+                                                self.ws_ptr, C.byref(self.layout), _ptr(images), _ptr(dL), C.byref(g),
+                                                _stream()), "snp_render_backward")
+        return grads
 
     def step(self, params, images, final_T, targets, n_norm, loss_out, dL, grads):
         self.generation += 1
@@ -342,8 +370,7 @@ def kernel_timing_read():
 def zeros_like_params(params: Dict[str, torch.Tensor]) -> Dict[str, torch.Tensor]:
     """Zeroed gradient tensors for the parameters the backward differentiates
     (every one but the Gaussians' opacity)."""
-    keys = {k for k, _ in L.SnpGrads._fields_}
-    return {k: torch.zeros_like(v) for k, v in params.items() if k in keys}
+    return {k: torch.zeros_like(v) for k, v in params.items() if k in GRAD_KEYS}
 
 
 class GraphStep:
@@ -436,9 +463,10 @@ class SplatRender(torch.autograd.Function):
     def forward(ctx, rast: Rasterizer, *tensors):
         params = {k: t for k, t in zip(PARAM_KEYS, tensors) if t is not None}
         params = {k: v.detach().contiguous() for k, v in params.items()}
-        rast.prepare(params)
+        prims = rast._prims(params)
+        rast.prepare(prims)
         images, final_T = rast.new_images()
-        rast.forward(params, images, final_T)
+        rast.forward(prims, images, final_T)
         ctx.rast = rast
         ctx.generation = rast.generation
         ctx.keys = [k for k, t in zip(PARAM_KEYS, tensors) if t is not None]
@@ -456,8 +484,7 @@ class SplatRender(torch.autograd.Function):
             again, T = rast.new_images()
             rast.forward(params, again, T)
             images = again
-        grads = zeros_like_params(params)
-        rast.backward(params, images, dL_dimages.contiguous(), grads)
+        grads = rast._gradients(params, images, dL_dimages.contiguous())
         out = [None]
         for k in PARAM_KEYS:
             out.append(grads.get(k) if k in params else None)
