@@ -682,7 +682,25 @@ __global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs 
 // blended like the neural primitives.  A batch is one instance per thread
 // (up to the workgroup size), staged as two float4, the blue channel and
 // the rectangle.
+//
+// Bound by the vector ALU: about twenty operations and an exponential per
+// (wave, instance).  So where a wave is one 8 x 8 block, its lanes first make
+// the mask of the pixels inside the rectangle for 64 instances at once, and
+// an instance is taken up only where that mask holds a pixel that has not
+// ended; its operands are read ahead from LDS.  With the rectangle tested by
+// every lane for every instance, and a wave's ended pixels left to the end of
+// the workgroup, 100k Gaussians at 800 x 800 (2.07e6 instances) took 178 us,
+// this 130.
 // ---------------------------------------------------------------------------
+// Pixels of an 8 x 8 block at (bx, by) inside an inclusive rectangle: bit 8 y + x
+__device__ __forceinline__ unsigned long long block_mask(const int4 rc, int bx, int by) {
+  const int x0 = max(rc.x - bx, 0), x1 = min(rc.y - bx, 7), y0 = max(rc.z - by, 0), y1 = min(rc.w - by, 7);
+  if (x0 > x1 || y0 > y1) return 0ull;
+  const uint32_t cols = (((2u << x1) - (1u << x0)) & 0xFFu) * 0x01010101u;
+  const unsigned long long rows = (~0ull >> (8 * (7 - y1))) & (~0ull << (8 * y0));
+  return (((unsigned long long)cols << 32) | cols) & rows;
+}
+
 template <int NT>
 struct GaussStage {
   float4 g0[NT];  // u, v, ka, red
@@ -732,28 +750,76 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_gauss_kernel(RasterA
         S.cb[threadIdx.x] = a.records[r * kRecFloats + 19];
       }
       __syncthreads();
+      if constexpr (PixelBlock<TW, TH, PPL>::kBlocks) {
+        const int lane = (int)(threadIdx.x & 63);
+        unsigned long long ended = __ballot(done[0]);
+        for (int j0 = 0; j0 < nb && ended != ~0ull; j0 += 64) {
+          const unsigned long long in = j0 + lane < nb ? block_mask(S.rect[j0 + lane], pb.wx0, pb.wy0) : 0ull;
+          const int lo = (int)(uint32_t)in, hi = (int)(uint32_t)(in >> 32);
+          unsigned long long m = __ballot(in != 0ull);
+          if (m == 0ull) continue;  // wave-uniform
+          int j = __builtin_ctzll(m);
+          float4 g0 = S.g0[j0 + j], g1 = S.g1[j0 + j];
+          float blue = S.cb[j0 + j];
+          while (true) {
+            const unsigned long long pixels =
+                ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(hi, j) << 32) |
+                (uint32_t)__builtin_amdgcn_readlane(lo, j);
+            const unsigned long long open = pixels & ~ended;
+            m &= m - 1;
+            const int jn = m ? __builtin_ctzll(m) : j;
+            const float4 n0 = S.g0[j0 + jn], n1 = S.g1[j0 + jn];
+            const float nblue = S.cb[j0 + jn];
+            if (open) {  // wave-uniform
+              const bool hit = __builtin_amdgcn_inverse_ballot_w64(open);
+              if (COUNT) tpairs += hit ? 1u : 0u;
+              const float dx = pb.pxc[0] - g0.x, dy = pb.pyc[0] - g0.y;
+              // log2 of the Gaussian factor; <= 0 for the positive definite conic
+              const float pw = fminf(__builtin_fmaf(dx, __builtin_fmaf(g1.x, dy, g0.z * dx), g1.y * dy * dy), 0.f);
+              const float al0 = fminf(g1.z * exp2_fast(pw), a.alpha_max);
+              const bool blend = hit && !(a.alpha_min > 0.f && al0 < a.alpha_min);
+              if (COUNT) nlive += blend ? 1 : 0;
+              if (blend) {
+                const float w = al0 * T[0];
+                C0[0] = __builtin_fmaf(g0.w, w, C0[0]);
+                C1[0] = __builtin_fmaf(g1.w, w, C1[0]);
+                C2[0] = __builtin_fmaf(blue, w, C2[0]);
+                T[0] = T[0] * (1.f - al0);
+                if (T[0] < a.t_eps) done[0] = true;
+              }
+              ended = __ballot(done[0]);
+            }
+            if (!m) break;
+            j = jn;
+            g0 = n0;
+            g1 = n1;
+            blue = nblue;
+          }
+        }
+      } else {
 #pragma unroll 4
-      for (int j = 0; j < nb; ++j) {
-        const int4 rc = S.rect[j];
-        if (rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1) continue;  // wave-uniform
-        const float4 g0 = S.g0[j], g1 = S.g1[j];
-        const float blue = S.cb[j];
+        for (int j = 0; j < nb; ++j) {
+          const int4 rc = S.rect[j];
+          if (rc.y < pb.wx0 || rc.x > pb.wx1 || rc.w < pb.wy0 || rc.z > pb.wy1) continue;  // wave-uniform
+          const float4 g0 = S.g0[j], g1 = S.g1[j];
+          const float blue = S.cb[j];
 #pragma unroll
-        for (int q = 0; q < PPL; ++q) {
-          const bool hit = !done[q] && px[q] >= rc.x && px[q] <= rc.y && py[q] >= rc.z && py[q] <= rc.w;
-          if (COUNT) tpairs += hit ? 1u : 0u;
-          const float dx = pb.pxc[q] - g0.x, dy = pb.pyc[q] - g0.y;
-          // log2 of the Gaussian factor; <= 0 for the positive definite conic
-          const float pw = fminf(__builtin_fmaf(dx, __builtin_fmaf(g1.x, dy, g0.z * dx), g1.y * dy * dy), 0.f);
-          const float al = fminf(g1.z * exp2_fast(pw), a.alpha_max);
-          if (hit && !(a.alpha_min > 0.f && al < a.alpha_min)) {
-            if (COUNT) nlive += 1;
-            const float w = al * T[q];
-            C0[q] = __builtin_fmaf(g0.w, w, C0[q]);
-            C1[q] = __builtin_fmaf(g1.w, w, C1[q]);
-            C2[q] = __builtin_fmaf(blue, w, C2[q]);
-            T[q] = T[q] * (1.f - al);
-            if (T[q] < a.t_eps) done[q] = true;
+          for (int q = 0; q < PPL; ++q) {
+            const bool hit = !done[q] && px[q] >= rc.x && px[q] <= rc.y && py[q] >= rc.z && py[q] <= rc.w;
+            if (COUNT) tpairs += hit ? 1u : 0u;
+            const float dx = pb.pxc[q] - g0.x, dy = pb.pyc[q] - g0.y;
+            // log2 of the Gaussian factor; <= 0 for the positive definite conic
+            const float pw = fminf(__builtin_fmaf(dx, __builtin_fmaf(g1.x, dy, g0.z * dx), g1.y * dy * dy), 0.f);
+            const float al = fminf(g1.z * exp2_fast(pw), a.alpha_max);
+            if (hit && !(a.alpha_min > 0.f && al < a.alpha_min)) {
+              if (COUNT) nlive += 1;
+              const float w = al * T[q];
+              C0[q] = __builtin_fmaf(g0.w, w, C0[q]);
+              C1[q] = __builtin_fmaf(g1.w, w, C1[q]);
+              C2[q] = __builtin_fmaf(blue, w, C2[q]);
+              T[q] = T[q] * (1.f - al);
+              if (T[q] < a.t_eps) done[q] = true;
+            }
           }
         }
       }
