@@ -978,37 +978,42 @@ __device__ __forceinline__ float row_level_ror8(float a, float b) {
 constexpr float kDsnC1n = (kTwoPi * kTwoPi) / 3.0f;
 constexpr float kDsnC3n = -(kTwoPi * kTwoPi * kTwoPi * kTwoPi) / 30.0f;
 
-// Sum over the wave of 16 values: lane l < 16 ends with the sum of value
-// 8 b3 + 4 b1 + 2 b0 + b2 (b = the bits of l).
-__device__ __forceinline__ float wave_sum16(const float* v, bool sel1, bool sel2, bool sel3, bool sel4) {
-  float x4[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    x4[q] = tb_level<kDppXor1>(tb_level<kDppHalfMirror>(v[4 * q], v[4 * q + 1], sel1),
-                               tb_level<kDppHalfMirror>(v[4 * q + 2], v[4 * q + 3], sel1), sel2);
-  return cross_rows_sum(tb_level<kDppRor8>(tb_level<kDppXor2>(x4[0], x4[1], sel3),
-                                           tb_level<kDppXor2>(x4[2], x4[3], sel3), sel4));
+// Sums over each row of 16 values (which it overwrites), or with `across` over
+// the wave: a row's lane l ends with the sum of value 8 b1 + 4 b0 + 2 b3 + b2
+// (b = the bits of l).
+__device__ __forceinline__ float row_sum16(float* v, bool sel2, bool sel3, bool across) {
+  row_levels_16(v);  // v[0], v[4], v[8], v[12]: four sums each
+  const float z = tb_level<kDppXor2>(tb_level<kDppXor1>(v[0], v[4], sel2), tb_level<kDppXor1>(v[8], v[12], sel2), sel3);
+  return across ? cross_rows_sum(z) : z;
+}
+
+// The same of three values: a row's lanes 0, 4 and 8 end with one each.
+__device__ __forceinline__ float row_sum3(float a, float b, float c, bool across) {
+  const float z = nb_level<kDppXor2>(nb_level<kDppXor1>(row_levels_3(a, b, c)));
+  return across ? cross_rows_sum(z) : z;
 }
 
 // Adjoint of the per-ray colour network on the wave's 64 pairs (every lane
 // takes part; a lane without a pair passes gc = 0).  gc: d loss / d colour
-// of the lane's pair.  The weight gradients summed over the wave go to the
-// primitive's table gradient gt and the (view, primitive) bias gradient gb
-// (global), the offset c_dc's to acc_col (LDS); returns d loss / d u and
-// d loss / d n of the lane's pair.
+// of the lane's pair.  The weight gradients summed over each row -- over the
+// wave where its rows hold one instance (same) -- go to the row's primitive's
+// table gradient gt and (view, primitive) bias gradient gb (global), the
+// offset c_dc's to acc_col (LDS); returns d loss / d u and d loss / d n of the
+// lane's pair.
 template <int CD>
 __device__ __forceinline__ void ray_net_adjoint(const float* ct, const float* cb, float u0, float u1, float u2,
                                                 float n0, float n1, float n2, float gc0, float gc1, float gc2,
                                                 float* gt, float* gb, float* acc_col, int lane, int idx16,
-                                                bool sel1, bool sel2, bool sel3, bool sel4, float* gu, float* gn) {
+                                                bool sel2, bool sel3, bool same, float* gu, float* gn) {
   using Lt = RayColourLayout<16, CD>;
   RayAct<CD> ra;
   ray_net<CD>(ct, cb, u0, u1, u2, n0, n1, n2, ra);
   const float go[3] = {gc0 * ra.sg[0] * (1.f - ra.sg[0]), gc1 * ra.sg[1] * (1.f - ra.sg[1]),
                        gc2 * ra.sg[2] * (1.f - ra.sg[2])};
-  auto flush16 = [&](float* base, const float* v16) {
-    const float z = wave_sum16(v16, sel1, sel2, sel3, sel4);
-    if (lane < 16 && z != 0.f) atomic_add_f32(base + idx16, z);
+  const bool adds = !same || lane < 16;
+  auto flush16 = [&](float* base, float* v16) {
+    const float z = row_sum16(v16, sel2, sel3, same);
+    if (adds && z != 0.f) atomic_add_f32(base + idx16, z);
     asm volatile("" ::: "memory");  // one block of 16 sums in registers at a time
   };
   const float* hl = CD == 2 ? ra.h2 : ra.h1;
@@ -1021,20 +1026,11 @@ __device__ __forceinline__ void ray_net_adjoint(const float* ct, const float* cb
   }
   {
     // output bias and the colour offset
-#pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = 0.f;
-    v[0] = go[0];
-    v[1] = go[1];
-    v[2] = go[2];
-    v[3] = gc0;
-    v[4] = gc1;
-    v[5] = gc2;
-    const float z = wave_sum16(v, sel1, sel2, sel3, sel4);
-    if (lane < 16 && z != 0.f) {
-      if (idx16 < 3)
-        atomic_add_f32(gt + Lt::BO + idx16, z);
-      else if (idx16 < 6)
-        atomicAdd(acc_col + idx16 - 3, z);
+    const float zo = row_sum3(go[0], go[1], go[2], same), zc = row_sum3(gc0, gc1, gc2, same);
+    const int c = (lane & 15) >> 2;
+    if (adds && c < 3 && (lane & 3) == 0) {
+      if (zo != 0.f) atomic_add_f32(gt + Lt::BO + c, zo);
+      if (zc != 0.f) atomicAdd(acc_col + c, zc);
     }
   }
   // d loss / d pre-activation of the last hidden layer
@@ -1054,7 +1050,9 @@ __device__ __forceinline__ void ray_net_adjoint(const float* ct, const float* cb
       for (int i = 0; i < 16; ++i) v[i] = gh[r] * ra.h1[i];
       flush16(gt + Lt::WH + 16 * r, v);
     }
-    flush16(gt + Lt::BH, gh);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = gh[i];
+    flush16(gt + Lt::BH, v);
     float g1[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -1081,7 +1079,9 @@ __device__ __forceinline__ void ray_net_adjoint(const float* ct, const float* cb
     for (int t = 0; t < 16; ++t) v[t] = gh[(16 * b + t) / 3] * nn[(16 * b + t) % 3];
     flush16(gt + Lt::AD + 16 * b, v);
   }
-  flush16(gb, gh);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = gh[i];
+  flush16(gb, v);
   z = zero_after(gh[15]);
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
@@ -1146,19 +1146,20 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // With the per-ray colour network (CD > 0, colour mode 4) phase 1 evaluates
 // each pair's colour, lists every pair that blends (alpha > 0) with its
 // weight alpha T, and phase 2 adds the network's adjoint: the weight
-// gradients summed over the 64 pairs into the per-primitive table gradient
-// (and the per-(view, primitive) bias gradient), the colour offset into the
-// record gradient, and the entry point's and direction's gradients into the
-// geometry chain.
+// gradients summed over a row, or over a chunk of one instance, into the
+// per-primitive table gradient (and the per-(view, primitive) bias gradient),
+// the colour offset into the record gradient, and the entry point's and
+// direction's gradients into the geometry chain.  Its 166 sums per pair set
+// the time: with levels that take selects and an instance per chunk 26.6 ms
+// (1280 x 720, 200k, N = 16), with the row levels' DPP adds 25.3, with rows of
+// several instances too 25.2; 100k at 640 x 360 (an instance's 26 pairs) 2.23,
+// 2.12, 1.81 ms.
 template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0, int WIDE = 1>
 __global__ void __launch_bounds__(TW * TH * WIDE)
 __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) render_bwd_kernel(RasterArgs a) {
   constexpr int NT = TW * TH;
   constexpr int NA = NT * WIDE;  // threads: one per pixel and the helpers of phase 2
   constexpr int NW = NT / 64;
-  // chunks of phase 2 take rows of different instances (the per-ray colour
-  // network's sums go to global memory once per chunk, so it takes one instance)
-  constexpr bool PACK = CD == 0;
   constexpr int TS = 5 * N + 4;
   constexpr int ACC = TS + kGViewFloats;  // per instance: table grads, then record grads
   __shared__ Stage<N, NB> S;
@@ -1175,8 +1176,8 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
   __shared__ int s_item;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // selector bits and value index of the transposed row reductions
-  const bool sel1 = lane & 4, sel2 = lane & 1, sel3 = lane & 2, sel4 = lane & 8;
-  const int idx16 = 8 * ((lane >> 3) & 1) + 4 * ((lane >> 1) & 1) + 2 * (lane & 1) + ((lane >> 2) & 1);
+  const bool sel2 = lane & 1, sel3 = lane & 2;
+  const int idx16 = 8 * ((lane >> 1) & 1) + 4 * (lane & 1) + 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);
   const bool helper = WIDE > 1 && wave >= NW;
   for (int idx = threadIdx.x; idx < NB * ACC; idx += NA) (&s_acc[0][0])[idx] = 0.f;
   int item = first_item(a.cus);
@@ -1324,7 +1325,7 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
       if (lane < NB) {
 #pragma unroll
         for (int w = 0; w < NW; ++w) rows += s_cnt[lane][w];
-        rows = PACK ? (rows + 15) / 16 : (rows + 63) / 64 * 4;
+        rows = (rows + 15) / 16;
       }
       uint32_t rsum = rows;
 #pragma unroll
@@ -1339,11 +1340,11 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
           // this row's instance: the number of instances that end at or before
           // it, counted over the lanes for each of the chunk's rows (rows past
           // the last one repeat it, without pairs)
-          const int myrow = PACK ? lane >> 4 : 0;
+          const int myrow = lane >> 4;
           int j = 0;
           uint32_t rbase = 0;
 #pragma unroll
-          for (int r = 0; r < (PACK ? 4 : 1); ++r) {
+          for (int r = 0; r < 4; ++r) {
             const uint32_t row = q0 + r < total ? q0 + r : total - 1;
             const int jr = __builtin_popcountll(__ballot(lane < NB && rsum <= row));
             const uint32_t br = jr > 0 ? __builtin_amdgcn_readlane(rsum, jr - 1) : 0u;
@@ -1351,9 +1352,9 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
             rbase = myrow >= r ? br : rbase;
           }
           const uint32_t row = q0 + myrow;
-          const uint32_t e = 16 * (row - rbase) + (PACK ? lane & 15 : lane);
+          const uint32_t e = 16 * (row - rbase) + (lane & 15);
           // one instance in the whole chunk: its sums are finished across the rows
-          const bool same = !PACK || __builtin_amdgcn_readfirstlane(j) == __builtin_amdgcn_readlane(j, 63);
+          const bool same = __builtin_amdgcn_readfirstlane(j) == __builtin_amdgcn_readlane(j, 63);
           // the list is the waves' regions in order: entry e lies in region w
           // with wstart[w] <= e < wstart[w + 1], at slot 64 w + e - wstart[w]
           uint32_t wstart[NW + 1];
@@ -1491,13 +1492,13 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
             // first pixel, which lies in the image, and carry wtp = 0)
             const int64_t gpx =
                 cam.pix_base + (int64_t)(ty * TH + pix / TW) * cam.width + (tx * TW + pix % TW);
-            const uint32_t pid = __builtin_amdgcn_readfirstlane(S.id[j]);
+            const uint32_t pid = S.id[j];
             ray_net_adjoint<CD>(reinterpret_cast<const float*>(CS.t[j]), reinterpret_cast<const float*>(CS.b[j]),
                                 G.p0 - G.e0, G.p1 - G.e1, G.p2 - G.e2, n0, n1, n2, a.dL[3 * gpx + 0] * wtp,
                                 a.dL[3 * gpx + 1] * wtp, a.dL[3 * gpx + 2] * wtp,
                                 a.gctab + (int64_t)pid * RayColourLayout<16, CD>::CTS,
-                                a.gcbias + ((int64_t)v * a.P + pid) * 16, acc + TS + 18, lane, idx16, sel1, sel2,
-                                sel3, sel4, gu, gn);
+                                a.gcbias + ((int64_t)v * a.P + pid) * 16, acc + TS + 18, lane, idx16, sel2, sel3, same,
+                                gu, gn);
             zz = zero_after(gu[0] + gn[0]);
           }
           // chain p', e', H -> d', m' -> record coefficients.  d' and m' are
@@ -1573,14 +1574,13 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
             float z = tb_level<kDppXor2>(tb_level<kDppXor1>(R[0], R[4], sel2),
                                          tb_level<kDppXor1>(R[8], R[12], sel2), sel3);
             float t4 = nb_level<kDppXor2>(nb_level<kDppXor1>(row_levels_3(R[16], R[17], wq)));
-            const int zl = 8 * ((lane >> 1) & 1) + 4 * (lane & 1) + 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);
             const int i4 = (lane >> 2) & 3;  // 0, 1: coefficients 16, 17; 2: b2
             if (same) {
               z = cross_rows_sum(z);
               t4 = cross_rows_sum(t4);
             }
             if (!same || lane < 16) {
-              atomicAdd(acc + TS + zl, z);
+              atomicAdd(acc + TS + idx16, z);
               if ((lane & 3) == 0 && i4 < 3) atomicAdd(i4 == 2 ? acc + 5 * N : acc + TS + 16 + i4, t4);
             }
           }
