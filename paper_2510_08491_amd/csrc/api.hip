@@ -81,6 +81,13 @@ static snp_status check_cams(int32_t V, const snp_camera* cams) {
   return SNP_OK;
 }
 
+constexpr int kDepthBits = 31;  // positive float32 depth: the sign bit is zero
+
+// key bits the instance sort orders: the tile bits only when the instances
+// are emitted in depth order, else depth and tile bits
+static int sort_lo(const Plan& pl) { return pl.depth_first ? kDepthBits : 0; }
+static int sort_bits(const Plan& pl) { return pl.depth_first ? pl.tile_bits : kDepthBits + pl.tile_bits; }
+
 static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const snp_camera* cams, int64_t cap,
                             Plan* pl) {
   snp_status s = check_cfg(cfg);
@@ -149,10 +156,13 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   L.ranges = take(sizeof(uint32_t) * 2 * (size_t)tiles);
   L.tile_pairs = take(sizeof(uint32_t) * (size_t)tiles);
   // the tile order lies in the sort's spare keys, which are free once it has
-  // run; with less room than tiles, persistent launches have an array of
-  // their own and the others take the tiles in id order
-  const bool spare = tiles <= 2 * cap;
-  pl->tile_order_on = spare || cfg->persistent;
+  // run over an even number of passes; over an odd one they hold its input,
+  // which a second sort reads again, and the order has an array of its own.
+  // With less room than tiles, only persistent launches have one, and the
+  // others take the tiles in id order.
+  const bool even = radix_passes(sort_bits(*pl)) % 2 == 0;
+  const bool room_for_tiles = tiles <= 2 * cap, spare = room_for_tiles && even;
+  pl->tile_order_on = room_for_tiles || cfg->persistent;
   pl->tile_order = spare ? pl->keys_alt : take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
   L.gview = take(gs ? 0 : sizeof(float) * (size_t)VP * kGViewFloats);
   L.gtable = take(sizeof(float) * (size_t)P * TS);
@@ -332,13 +342,6 @@ static snp_status do_preprocess(const snp_config* cfg, const snp_prims* pr, int3
   if (cfg->color_mode == 4) SNP_HIP(launch_ray_colour_fwd(ray_colour_args(cfg, pr, V, pl, ws), st));
   return SNP_OK;
 }
-
-constexpr int kDepthBits = 31;  // positive float32 depth: the sign bit is zero
-
-// key bits the instance sort orders: the tile bits only when the instances
-// are emitted in depth order, else depth and tile bits
-static int sort_lo(const Plan& pl) { return pl.depth_first ? kDepthBits : 0; }
-static int sort_bits(const Plan& pl) { return pl.depth_first ? pl.tile_bits : kDepthBits + pl.tile_bits; }
 
 // Instance offsets and instances, in primitive order or (depth_first) in the
 // depth order of the (view, primitive) pairs.
