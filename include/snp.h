@@ -114,7 +114,9 @@ typedef struct {
  *             tiles do not form the tail.
  *  bwd_batch  instances per batch of the backward rasterizer (0 = the
  *             default for the tile shape); the tile shape is shared with the
- *             forward, and the backward runs one pixel per thread.
+ *             forward, and the backward runs one pixel per thread.  Launches
+ *             of few 16 x 16 tiles (up to six per compute unit) take batches
+ *             of their own.
  *  fwd_cache  1 = the forward stores the integral (alpha-hat, Eq. 8-9) of
  *             every (pixel, instance) pair it evaluates, capacity x tile_w x
  *             tile_h floats in the workspace, and the backward reads it back

@@ -112,7 +112,7 @@ __device__ __forceinline__ void quat_rot_f64(const float* qf, double Rp[3][3], d
 // the group), so that the rows of the parameters and of the table are read
 // and written as whole runs of memory: bound by that traffic.  With a thread
 // per primitive every load touched 64 lines (1M primitives of 32 units: 2.28
-// ms, now 0.55; 200k of 16: 0.21 ms, now 0.07).
+// ms, now 0.51; 200k of 16: 0.21 ms, now 0.05).
 template <int N>
 __global__ void __launch_bounds__(256) prim_table_kernel(int64_t P, float omega0, const float* __restrict__ scales,
                                                          const float* __restrict__ quats,
