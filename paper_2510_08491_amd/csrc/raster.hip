@@ -558,37 +558,38 @@ __global__ void __launch_bounds__(TW * TH / PPL) render_fwd_kernel(RasterArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// forward for launches of few tiles: WIDE waves per 8 x 8 block of a 16 x 16 tile
+// forward for launches of few tiles: a workgroup of WIDE waves per 8 x 8 block
 // ---------------------------------------------------------------------------
 // One wave alone on a SIMD issues an instruction every five cycles or so, two
 // to three times slower than the SIMD can with several waves, and a launch of
 // few tiles leaves SIMDs with one wave, or with none once the lighter tiles
-// have ended.  Here the waves of a block share its instances: each batch is
-// evaluated (geometry, density integral, alpha) by all waves, every wave
-// taking its share of the instances that meet its block, and the alphas go to
-// LDS; then the block's first wave blends them in depth order -- a tenth of
-// the work -- while the other waves stage the next batch.  The arithmetic per
-// pair and the blending order are render_fwd_kernel's, so the images are the
-// same bit for bit; a pixel that ends inside a batch is left out of the
-// evaluation from the next batch on.  Times and the choice: wide_fwd.
+// have ended.  Here each 8 x 8 block of a 16 x 16 tile has a workgroup, so
+// that a heavy tile's work spreads over four CUs, and its waves share the
+// block's instances: each batch is evaluated (geometry, density integral,
+// alpha) by all waves, every wave taking its share of the instances that meet
+// the block, and the alphas go to LDS; then the first wave blends them in
+// depth order -- a tenth of the work -- while the other waves stage the next
+// batch.  The arithmetic per pair and the blending order are
+// render_fwd_kernel's, so the images are the same bit for bit; a pixel that
+// ends inside a batch is left out of the evaluation from the next batch on.
+// (A tile's four blocks in one workgroup took up to twice as long: 212 tiles
+// 0.151 ms with 16 waves, this 0.080 with eight per block.)  Times and the
+// choice: wide_fwd.
 template <int N>
 constexpr int wide_batch() { return N >= 32 ? 16 : 32; }
 
 template <int N, int WIDE>
-__global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs a) {
-  static_assert(WIDE == 2 || WIDE == 4, "waves per block");
-  constexpr int NPIX = 256, NT = NPIX * WIDE, NB4 = 4;
+__global__ void __launch_bounds__(64 * WIDE) render_fwd_wide_kernel(RasterArgs a) {
+  static_assert(WIDE == 4 || WIDE == 8, "waves per block");
+  constexpr int NPIX = 64, NT = NPIX * WIDE;
   constexpr int FB = wide_batch<N>();
   __shared__ Stage<N, FB> S;
   __shared__ float s_al[FB][NPIX];       // alpha of each evaluated (instance, pixel), 0 where it does not blend
   __shared__ float4 s_col[2][FB];        // colours of the batch being blended and of the one being staged
-  __shared__ uint32_t s_mask[NB4];       // bit j: some pixel of the block meets instance j
-  __shared__ unsigned long long s_done[NB4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = wave / NB4;
-  // the waves of a block sit on different SIMDs
-  const int blk = (wave + 2 * sub) & (NB4 - 1);
-  const bool blends = wave < NB4;
-  if (threadIdx.x < NB4) s_mask[threadIdx.x] = 0u;
+  __shared__ uint32_t s_mask;            // bit j: some pixel of the block meets instance j
+  __shared__ unsigned long long s_done;  // the block's pixels that have ended
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) s_mask = 0u;
   // ids, rectangles, records, tables and colours of a batch, by NTH threads
   auto stage = [&](auto nth, int v, uint32_t b0, int nb, int buf, int tid) {
     constexpr int NTH = decltype(nth)::value;
@@ -598,13 +599,14 @@ __global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs 
       s_col[buf][t] = make_float4(rec[11], rec[15], rec[19], 0.f);
     }
   };
-  const int tile = a.tile_order ? (int)a.tile_order[blockIdx.x] : (int)blockIdx.x;
+  const int item = (int)blockIdx.x / 4;
+  const int tile = a.tile_order ? (int)a.tile_order[item] : item;
   const int v = view_of_tile(a.cams, a.V, tile);
   const CamDev& cam = a.cams[v];
   const int local = tile - cam.tile_base;
   const int ty = local / cam.ntx, tx = local - ty * cam.ntx;
   PixelBlock<16, 16, 1> pb;
-  pb.init(cam, tx, ty, blk);
+  pb.init(cam, tx, ty, (int)blockIdx.x & 3);
   const bool outside = pb.pix[0] < 0;
   float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
   bool done = outside;
@@ -616,9 +618,9 @@ __global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs 
   for (uint32_t b0 = start; b0 < end; b0 += FB, buf ^= 1) {
     const int nb = (int)min((uint32_t)FB, end - b0);
     // ---- evaluation: this wave's share of the instances that meet its block
-    unsigned long long m = dmask != ~0ull ? meets_wave(S, pb, nb) : 0ull;
+    unsigned long long m = meets_wave(S, pb, nb);
     for (int t = 0; m; m &= m - 1, ++t) {
-      if ((t & (WIDE - 1)) != sub) continue;
+      if ((t & (WIDE - 1)) != wave) continue;
       const int j = __builtin_ctzll(m);
       PairGeom g[1];
       const bool gh = pair_geom(S.rec[j][0], S.rec[j][1], S.rec[j][2], S.rec[j][3], S.rec[j][4], S.rec[j][5],
@@ -630,22 +632,22 @@ __global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs 
       const float b2 = reinterpret_cast<const float*>(S.tab[j])[5 * N];
       const float ahat = 2.f * pb.L[0] * g[0].H * (Q[0] + b2);
       if (a.ahat_cache && (int64_t)(b0 + j) < a.cache_instances)
-        a.ahat_cache[(int64_t)(b0 + j) * NPIX + pb.loc[0]] = ahat;
+        a.ahat_cache[(int64_t)(b0 + j) * 256 + pb.loc[0]] = ahat;
       const float al0 = alpha_of(ahat, a.alpha_max);
-      s_al[j][blk * 64 + lane] = hit && !(a.alpha_min > 0.f && al0 < a.alpha_min) ? al0 : 0.f;
-      if (lane == 0) atomicOr(&s_mask[blk], 1u << j);
+      s_al[j][lane] = hit && !(a.alpha_min > 0.f && al0 < a.alpha_min) ? al0 : 0.f;
+      if (lane == 0) atomicOr(&s_mask, 1u << j);
     }
     __syncthreads();
-    if (blends) {
+    if (wave == 0) {
       // ---- blending, in depth order; the next alpha is read ahead
-      uint32_t h = s_mask[blk];
-      float al_next = h ? s_al[__builtin_ctz(h)][blk * 64 + lane] : 0.f;
+      uint32_t h = s_mask;
+      float al_next = h ? s_al[__builtin_ctz(h)][lane] : 0.f;
       while (h) {
         const int j = __builtin_ctz(h);
         h &= h - 1;
         const float al = done ? 0.f : al_next;
         const float4 col = s_col[buf][j];
-        if (h) al_next = s_al[__builtin_ctz(h)][blk * 64 + lane];
+        if (h) al_next = s_al[__builtin_ctz(h)][lane];
         const float w = al * T;
         C0 = __builtin_fmaf(col.x, w, C0);
         C1 = __builtin_fmaf(col.y, w, C1);
@@ -655,18 +657,18 @@ __global__ void __launch_bounds__(256 * WIDE) render_fwd_wide_kernel(RasterArgs 
       }
       const unsigned long long d = __ballot(done);
       if (lane == 0) {
-        s_mask[blk] = 0u;
-        s_done[blk] = d;
+        s_mask = 0u;
+        s_done = d;
       }
     } else if (b0 + FB < end) {
       stage(std::integral_constant<int, NT - NPIX>{}, v, b0 + FB, (int)min((uint32_t)FB, end - b0 - FB), buf ^ 1,
             threadIdx.x - NPIX);
     }
     __syncthreads();
-    dmask = s_done[blk];
-    if ((s_done[0] & s_done[1] & s_done[2] & s_done[3]) == ~0ull) break;
+    dmask = s_done;
+    if (dmask == ~0ull) break;
   }
-  if (blends && !outside) {
+  if (wave == 0 && !outside) {
     const int64_t px = cam.pix_base + pb.pix[0];
     a.images[3 * px + 0] = C0 + T * a.bg0;
     a.images[3 * px + 1] = C1 + T * a.bg1;
@@ -1655,22 +1657,30 @@ static int persistent_grid(K kernel, int threads, const RasterArgs& a) {
   return g < 1 ? 1 : g;
 }
 
-// Waves per 8 x 8 block (and per-pixel wave of the backward) by the launch's
-// tiles per CU; 1: the plain kernels.  A workgroup of 1024 threads has a CU
-// to itself, so it pays up to 2.5 tiles per CU, two of 512 up to 5 (forward)
-// or 6 (backward); beyond, the plain kernels keep the SIMDs full by
-// themselves and the waiting waves of the wide ones only take slots.  ms,
-// N = 16 unless noted, 256 CUs, plain / 2 waves / 4 waves (forward; backward):
-//   212 tiles (3001 primitives)   0.233 / 0.184 / 0.151;  0.460 / 0.279 / 0.220
-//   510 (100k)                    1.89 / 1.53 / 1.21;     4.67 / 2.92 / 2.25
-//   660 (20k)                     0.381 / 0.305 / 0.273;  0.939 / 0.598 / 0.604
-//   875 (20k, N = 8)              0.254 / 0.208 / 0.247;  0.645 / 0.443 / 0.529
-//   1200 (100k, N = 8)            1.14 / 0.946 / 1.32;    2.95 / 2.24 / 2.91
-//   1540 (100k, N = 8)            1.11 / 1.08 / 1.53;     2.90 / 2.60 / 3.37
-//   1900 (100k)                   1.58 / 1.81 / 2.60;     4.20 / 4.43 / 5.47
+// Waves per 8 x 8 block by the launch's tiles per CU; 1: the plain kernel,
+// which keeps the SIMDs full by itself where there are tiles enough.  ms,
+// N = 16 unless noted, 256 CUs, plain / 4 waves / 8 waves:
+//   212 tiles (3001 primitives)   0.233 / 0.116 / 0.080
+//   361 (20k)                     0.525 / 0.258 / 0.168
+//   510 (100k)                    1.89  / 0.969 / 0.936
+//   660 (20k)                     0.381 / 0.193 / 0.212
+//   1024 (100k)                   1.83  / 1.01  / 1.07
+//   1540 (100k, N = 8)            1.11  / 0.952;   1540 (20k) 0.325 / 0.312
+//   1900 (100k)                   1.58  / 1.77
 static int wide_fwd(const RasterArgs& a) {
-  return 2 * (int64_t)a.total_tiles <= 5 * (int64_t)a.cus ? 4 : a.total_tiles <= 5 * (int64_t)a.cus ? 2 : 1;
+  return a.total_tiles <= 2 * (int64_t)a.cus ? 8 : a.total_tiles <= 6 * (int64_t)a.cus ? 4 : 1;
 }
+
+// Waves per pixel wave of the backward: a workgroup of 1024 threads has a CU
+// to itself, so it pays up to 2.5 tiles per CU, two of 512 up to 6; beyond,
+// the helpers only take slots.  ms, plain / 2 / 4 waves per pixel wave:
+//   212 tiles (3001 primitives)   0.460 / 0.279 / 0.220
+//   510 (100k)                    4.67 / 2.92 / 2.25
+//   660 (20k)                     0.939 / 0.598 / 0.604
+//   875 (20k, N = 8)              0.645 / 0.443 / 0.529
+//   1200 (100k, N = 8)            2.95 / 2.24 / 2.91
+//   1540 (100k, N = 8)            2.90 / 2.60 / 3.37
+//   1900 (100k)                   4.20 / 4.43 / 5.47
 static int wide_bwd(const RasterArgs& a) {
   return 2 * (int64_t)a.total_tiles <= 5 * (int64_t)a.cus ? 4 : a.total_tiles <= 6 * (int64_t)a.cus ? 2 : 1;
 }
@@ -1681,10 +1691,10 @@ static hipError_t fwd_shape(const RasterArgs& a, bool persist, bool count, hipSt
   if (a.total_tiles <= 0) return hipSuccess;
   if constexpr (TW == 16 && TH == 16 && PPL == 1 && CD == 0) {
     const int wide = count ? 1 : wide_fwd(a);
-    if (wide == 4)
-      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 4>), dim3(a.total_tiles), dim3(NT * 4), 0, st, a);
-    else if (wide == 2)
-      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 2>), dim3(a.total_tiles), dim3(NT * 2), 0, st, a);
+    if (wide == 8)
+      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 8>), dim3(a.total_tiles * 4), dim3(64 * 8), 0, st, a);
+    else if (wide == 4)
+      hipLaunchKernelGGL((render_fwd_wide_kernel<N, 4>), dim3(a.total_tiles * 4), dim3(64 * 4), 0, st, a);
     if (wide > 1) return hipGetLastError();
   }
   if (persist) {
