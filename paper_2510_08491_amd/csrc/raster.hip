@@ -611,6 +611,7 @@ __global__ void __launch_bounds__(64 * WIDE) render_fwd_wide_kernel(RasterArgs a
   float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f;
   bool done = outside;
   unsigned long long dmask = __ballot(outside);  // pixels of the block that take no more primitives
+  if (dmask == ~0ull) return;  // the block lies outside the image
   const uint32_t start = a.ranges[2 * tile], end = a.ranges[2 * tile + 1];
   if (start < end) stage(std::integral_constant<int, NT>{}, v, start, (int)min((uint32_t)FB, end - start), 0, threadIdx.x);
   __syncthreads();
@@ -1142,7 +1143,7 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 //
 // Launches of few tiles (WIDE > 1, see wide_bwd): WIDE - 1 further waves per
 // pixel wave take part in staging, phase 2 and the flush, and wait out phase
-// 1; with batches of 16 or 32 instances there are chunks for all of them (212
+// 1 (BLOCK: the workgroup is one 8 x 8 block of the tile with its waves); with batches of 16 or 32 instances there are chunks for all of them (212
 // tiles, 16 waves: batches of 8 0.397 ms, 16 0.270, 32 0.220).
 //
 // With the per-ray colour network (CD > 0, colour mode 4) phase 1 evaluates
@@ -1156,10 +1157,11 @@ __device__ __forceinline__ float ray_length(const CamDev& cam, float pxc, float 
 // (1280 x 720, 200k, N = 16), with the row levels' DPP adds 25.3, with rows of
 // several instances too 25.2; 100k at 640 x 360 (an instance's 26 pairs) 2.23,
 // 2.12, 1.81 ms.
-template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0, int WIDE = 1>
-__global__ void __launch_bounds__(TW * TH * WIDE)
+template <int N, int TW, int TH, int NB, bool PERSIST, int CD = 0, int WIDE = 1, bool BLOCK = false>
+__global__ void __launch_bounds__((BLOCK ? 64 : TW * TH) * WIDE)
 __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) render_bwd_kernel(RasterArgs a) {
-  constexpr int NT = TW * TH;
+  constexpr int TP = TW * TH;             // pixels of a tile
+  constexpr int NT = BLOCK ? 64 : TP;     // pixels of this workgroup
   constexpr int NA = NT * WIDE;  // threads: one per pixel and the helpers of phase 2
   constexpr int NW = NT / 64;
   constexpr int TS = 5 * N + 4;
@@ -1182,7 +1184,7 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
   const int idx16 = 8 * ((lane >> 1) & 1) + 4 * (lane & 1) + 2 * ((lane >> 3) & 1) + ((lane >> 2) & 1);
   const bool helper = WIDE > 1 && wave >= NW;
   for (int idx = threadIdx.x; idx < NB * ACC; idx += NA) (&s_acc[0][0])[idx] = 0.f;
-  int item = first_item(a.cus);
+  int item = BLOCK ? (int)blockIdx.x / 4 : first_item(a.cus);
   while (true) {
     if (item >= a.total_tiles) break;
     const int tile = a.tile_order ? (int)a.tile_order[item] : item;
@@ -1191,7 +1193,7 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
     const int local = tile - cam.tile_base;
     const int ty = local / cam.ntx, tx = local - ty * cam.ntx;
     PixelBlock<TW, TH, 1> pb;
-    pb.init(cam, tx, ty, wave % NW);
+    pb.init(cam, tx, ty, BLOCK ? (int)blockIdx.x & 3 : wave % NW);
     float T = 1.f;
     bool done = helper || pb.pix[0] < 0;
     const int64_t pxi = cam.pix_base + (done ? 0 : pb.pix[0]);
@@ -1300,14 +1302,14 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
       };
       // the batch's integrals come from the forward's store
       const bool cached = a.ahat_cache && (int64_t)(b0 + nb) <= a.cache_instances;
-      const float* cp = a.ahat_cache + (int64_t)b0 * NT + pb.loc[0];
+      const float* cp = a.ahat_cache + (int64_t)b0 * TP + pb.loc[0];
       if (cached) {
         // the forward's integrals of this batch, fetched together (only for
         // instances whose rectangle meets this wave's pixels)
         float pre[NB];
         const uint32_t m = __ballot(!done) != 0 ? (uint32_t)meets_wave(S, pb, nb) : 0u;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) pre[j] = (m >> j) & 1u ? cp[(int64_t)j * NT] : 0.f;
+        for (int j = 0; j < NB; ++j) pre[j] = (m >> j) & 1u ? cp[(int64_t)j * TP] : 0.f;
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
           // a pair without a positive integral changes nothing (alpha 0, no
@@ -1671,18 +1673,22 @@ static int wide_fwd(const RasterArgs& a) {
   return a.total_tiles <= 2 * (int64_t)a.cus ? 8 : a.total_tiles <= 6 * (int64_t)a.cus ? 4 : 1;
 }
 
-// Waves per pixel wave of the backward: a workgroup of 1024 threads has a CU
-// to itself, so it pays up to 2.5 tiles per CU, two of 512 up to 6; beyond,
-// the helpers only take slots.  ms, plain / 2 / 4 waves per pixel wave:
-//   212 tiles (3001 primitives)   0.460 / 0.279 / 0.220
-//   510 (100k)                    4.67 / 2.92 / 2.25
-//   660 (20k)                     0.939 / 0.598 / 0.604
+// Waves per pixel wave of the backward; 8: a workgroup per 8 x 8 block, which
+// spreads a heavy tile over four CUs but halves the pairs that a row finds
+// together and flushes four times, so it pays up to 1.5 tiles per CU only.  A
+// workgroup of 1024 threads has a CU to itself, so it pays up to 2.5, two of
+// 512 up to 6; beyond, the helpers only take slots.  ms, plain / 2 / 4 / 8:
+//   212 tiles (3001 primitives)   0.460 / 0.279 / 0.220 / 0.184
+//   361 (20k)                     1.18  / 0.732 / 0.576 / 0.425
+//   510 (100k)                    4.67  / 2.92  / 2.25  / 3.08
+//   660 (20k)                     0.939 / 0.598 / 0.604 / 0.697
 //   875 (20k, N = 8)              0.645 / 0.443 / 0.529
-//   1200 (100k, N = 8)            2.95 / 2.24 / 2.91
-//   1540 (100k, N = 8)            2.90 / 2.60 / 3.37
-//   1900 (100k)                   4.20 / 4.43 / 5.47
+//   1200 (100k, N = 8)            2.95  / 2.24  / 2.91
+//   1540 (100k, N = 8)            2.90  / 2.60  / 3.37
+//   1900 (100k)                   4.20  / 4.43  / 5.47
 static int wide_bwd(const RasterArgs& a) {
-  return 2 * (int64_t)a.total_tiles <= 5 * (int64_t)a.cus ? 4 : a.total_tiles <= 6 * (int64_t)a.cus ? 2 : 1;
+  const int64_t twice = 2 * (int64_t)a.total_tiles, cus = a.cus;
+  return twice <= 3 * cus ? 8 : twice <= 5 * cus ? 4 : twice <= 12 * cus ? 2 : 1;
 }
 
 template <int N, int TW, int TH, int PPL, int CD = 0>
@@ -1745,7 +1751,10 @@ static hipError_t bwd_shape(const RasterArgs& a, bool persist, hipStream_t st) {
   if constexpr (TW == 16 && TH == 16 && CD == 0) {
     // (batches of their own: more rows for more waves)
     const int wide = wide_bwd(a);
-    if (wide == 4)
+    if (wide == 8)
+      hipLaunchKernelGGL((render_bwd_kernel<N, 16, 16, 32, false, 0, 8, true>), dim3(a.total_tiles * 4), dim3(64 * 8), 0,
+                         st, a);
+    else if (wide == 4)
       hipLaunchKernelGGL((render_bwd_kernel<N, 16, 16, 32, false, 0, 4>), dim3(a.total_tiles), dim3(NT * 4), 0, st, a);
     else if (wide == 2)
       hipLaunchKernelGGL((render_bwd_kernel<N, 16, 16, 16, false, 0, 2>), dim3(a.total_tiles), dim3(NT * 2), 0, st, a);
