@@ -379,7 +379,7 @@ hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts
 constexpr int kEmitPairs = 64;
 
 __global__ void __launch_bounds__(256) emit_kernel(EmitArgs a) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (pair_block() == 0 && threadIdx.x == 0) {
     if (a.counters[CNT_INSTANCES] > (unsigned long long)a.capacity) a.counters[CNT_OVERFLOW] = 1ull;
     a.counters[CNT_DEPTH_SORT] = (unsigned long long)a.depth_sorted;
   }
@@ -387,7 +387,8 @@ __global__ void __launch_bounds__(256) emit_kernel(EmitArgs a) {
   __shared__ int32_t s_tx0[kEmitPairs], s_nx[kEmitPairs], s_tile0[kEmitPairs], s_ntx[kEmitPairs];
   __shared__ uint32_t s_p[kEmitPairs], s_d[kEmitPairs];
   const int64_t n = a.P * a.V;
-  const int64_t j0 = (int64_t)blockIdx.x * kEmitPairs;
+  const int64_t j0 = pair_block() * kEmitPairs;
+  if (j0 >= n) return;
   const int last = (int)min((int64_t)(kEmitPairs - 1), n - 1 - j0);
   // uint32 arithmetic: the differences stay exact if the scan wrapped
   const uint32_t base = a.offsets[j0];
@@ -433,7 +434,7 @@ __global__ void __launch_bounds__(256) emit_kernel(EmitArgs a) {
 
 hipError_t launch_emit(const EmitArgs& a, hipStream_t st) {
   const int64_t n = a.P * a.V;
-  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)((n + kEmitPairs - 1) / kEmitPairs)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(emit_kernel, pair_grid((n + kEmitPairs - 1) / kEmitPairs), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

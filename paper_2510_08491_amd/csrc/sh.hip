@@ -150,7 +150,7 @@ __device__ __forceinline__ void own_coeffs(const ShArgs& a, int64_t p, int q, fl
 
 // one group per (view, primitive): colour into the record
 __global__ void __launch_bounds__(256) sh_fwd_kernel(ShArgs a) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
+  const int64_t i = (pair_block() * 256 + threadIdx.x) / kGroup;
   const int q = (int)(threadIdx.x % kGroup);
   if (i >= (int64_t)a.V * a.P || a.tile_counts[i] == 0) return;  // whole groups
   const int v = (int)(i / a.P);
@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(256) sh_bwd_kernel(ShArgs a) {
 hipError_t launch_sh_fwd(const ShArgs& a, hipStream_t st) {
   const int64_t n = (int64_t)a.V * a.P * kGroup;
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sh_fwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(sh_fwd_kernel, pair_grid((n + 255) / 256), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 

@@ -206,6 +206,16 @@ struct ShArgs {
 // rows (density table, adjoints): a group reads whole runs of a row.
 constexpr int kGroup = 4;
 
+// Grid and workgroup index of a launch with several threads per (view,
+// primitive) pair.  HIP refuses 2^32 threads in a dimension and there may be
+// that many pairs, so the workgroups beyond 2^20 lie in further rows of the
+// grid (the last one may pass the end).
+constexpr int64_t kGridRow = (int64_t)1 << 20;
+inline dim3 pair_grid(int64_t blocks) {
+  return dim3((unsigned)(blocks < kGridRow ? blocks : kGridRow), (unsigned)((blocks + kGridRow - 1) / kGridRow));
+}
+__device__ __forceinline__ int64_t pair_block() { return (int64_t)blockIdx.y * kGridRow + blockIdx.x; }
+
 // Sum over aligned groups of four lanes, the same value in every lane of the
 // group (whose lanes are active together).
 template <int CTRL>
