@@ -150,20 +150,21 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   };
   if (own_buffers) take_pairs();
   L.keys = take(sizeof(unsigned long long) * (size_t)cap);
-  pl->keys_alt = take(sizeof(unsigned long long) * (size_t)cap);
+  // the tile order lies in the sort's spare keys, which are free once it has
+  // run over an even number of passes; over an odd one they hold its input,
+  // which a second sort reads again, and the order has an array of its own.
+  // With room for fewer tiles, only persistent launches have one (and the
+  // spare keys room for it), and the others take the tiles in id order.
+  // (Size and capacity grow together: static_plan relies on it.)
+  pl->tile_order_on = tiles <= 2 * cap || cfg->persistent;
+  const bool spare = pl->tile_order_on && radix_passes(sort_bits(*pl)) % 2 == 0;
+  pl->keys_alt = take(std::max(sizeof(unsigned long long) * (size_t)cap, spare ? sizeof(uint32_t) * (size_t)tiles : 0));
+  if (spare) pl->tile_order = pl->keys_alt;
   L.values = take(sizeof(uint32_t) * (size_t)cap);
   pl->values_alt = take(sizeof(uint32_t) * (size_t)cap);
   L.ranges = take(sizeof(uint32_t) * 2 * (size_t)tiles);
   L.tile_pairs = take(sizeof(uint32_t) * (size_t)tiles);
-  // the tile order lies in the sort's spare keys, which are free once it has
-  // run over an even number of passes; over an odd one they hold its input,
-  // which a second sort reads again, and the order has an array of its own.
-  // With less room than tiles, only persistent launches have one, and the
-  // others take the tiles in id order.
-  const bool even = radix_passes(sort_bits(*pl)) % 2 == 0;
-  const bool room_for_tiles = tiles <= 2 * cap, spare = room_for_tiles && even;
-  pl->tile_order_on = room_for_tiles || cfg->persistent;
-  pl->tile_order = spare ? pl->keys_alt : take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
+  if (!spare) pl->tile_order = take(pl->tile_order_on ? sizeof(uint32_t) * (size_t)tiles : 0);
   L.gview = take(gs ? 0 : sizeof(float) * (size_t)VP * kGViewFloats);
   L.gtable = take(sizeof(float) * (size_t)P * TS);
   {
