@@ -143,8 +143,8 @@ typedef struct {
  *             pairs are sorted by depth first, instances are emitted in that
  *             order and sorted by their tile bits only (fewer passes over
  *             the instances); 2 = instances emitted in primitive order and
- *             sorted by the whole key; 0 = as 1, but when V * P < 2^16 with
- *             the workspace size and counters of 2.
+ *             sorted by the whole key; 0 = 1 when V * P >= 2^16, else the
+ *             layout, offsets and counters of 2 (by whichever way is faster).
  *  time       xi_t in [0, 1] of the dynamic-scene application: with
  *             prims.wt the phase of hidden unit k is omega0 (W1_k x + b1_k) +
  *             time * wt_k (the time term added unscaled, as the paper prints

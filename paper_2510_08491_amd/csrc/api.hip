@@ -17,17 +17,21 @@ struct Plan {
   size_t scan_scratch, sort_scratch, loss_partials, cams_bytes;
   size_t keys_alt, values_alt;
   // depth order of the (view, primitive) pairs: scratch keys and indices, the
-  // order and the tile counts in it
-  size_t dkeys[2], dvals, order, counts_sorted;
+  // order, the tile counts in it and (unseen) their scan
+  size_t dkeys[2], dvals, order, counts_sorted, offsets_sorted;
   size_t tile_order, tile_steps;  // tiles by instance count
   bool tile_order_on;
   int inst_rounds, pair_rounds;   // block sizes of the radix passes over instances and pairs
-  int64_t depth_reported;         // pairs the depth sort reports in its counter
   std::vector<int32_t> tile_base;
   std::vector<int64_t> pix_base;
   int64_t total_pixels;
   int tile_bits;  // significant bits of the global tile id
   bool depth_first;  // depth sort of the pairs, then the instances by tile bits only
+  // bin_order 0 of few pairs: they are put in depth order all the same, which
+  // is faster, but what the caller sees (layout, offsets, counters) is what
+  // bin_order 2 gives
+  bool unseen;
+  bool one_launch;  // unseen, and a workgroup per view orders its pairs
   // colour mode 4: the colour network's table and biases, their gradients,
   // and the rotation / scale gradients handed to the preprocess adjoint
   size_t ctab, cbias, gctab, gcbias, extra_rs;
@@ -111,12 +115,13 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   int tb = 1;
   while (((int64_t)1 << tb) < tiles) ++tb;
   pl->tile_bits = tb;
-  // bin_order 0: with few pairs the depth order takes no buffers of its own
-  // (and is not reported); the arrays it leads to are those of bin_order 2
   const bool few = (int64_t)V * P < ((int64_t)1 << 16);
   const bool own_buffers = cfg->bin_order == 1 || (cfg->bin_order == 0 && !few);
   pl->depth_first = cfg->bin_order != 2;
-  pl->depth_reported = own_buffers ? (int64_t)V * P : 0;
+  pl->unseen = cfg->bin_order == 0 && few;
+  const bool as_unseen = few && cfg->bin_order != 1;  // the same layout for bin_order 0 and 2
+  const bool as_one = as_unseen && order_small(P);
+  pl->one_launch = pl->unseen && as_one;
   // Gaussians have no density table, float64 discriminants, backward arrays
   // or pair cache
   const bool gs = gaussian(cfg);
@@ -142,11 +147,12 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   L.tile_counts = take(sizeof(uint32_t) * (size_t)VP);
   L.offsets = take(sizeof(uint32_t) * (size_t)VP);
   auto take_pairs = [&] {
-    const size_t dn = pl->depth_first ? (size_t)VP : 0, kn = order_small(P, V) ? 0 : dn;
+    const size_t dn = pl->depth_first || as_unseen ? (size_t)VP : 0, kn = as_one ? 0 : dn;
     for (int k = 0; k < 2; ++k) pl->dkeys[k] = take(sizeof(uint32_t) * kn);
     pl->dvals = take(sizeof(uint32_t) * kn);
     pl->order = take(sizeof(uint32_t) * dn);
     pl->counts_sorted = take(sizeof(uint32_t) * dn);
+    pl->offsets_sorted = take(as_unseen ? sizeof(uint32_t) * dn : 0);
   };
   if (own_buffers) take_pairs();
   L.keys = take(sizeof(unsigned long long) * (size_t)cap);
@@ -157,7 +163,9 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   // spare keys room for it), and the others take the tiles in id order.
   // (Size and capacity grow together: static_plan relies on it.)
   pl->tile_order_on = tiles <= 2 * cap || cfg->persistent;
-  const bool spare = pl->tile_order_on && radix_passes(sort_bits(*pl)) % 2 == 0;
+  const bool even = as_unseen ? radix_passes(tb) % 2 == 0 && radix_passes(kDepthBits + tb) % 2 == 0
+                              : radix_passes(sort_bits(*pl)) % 2 == 0;
+  const bool spare = pl->tile_order_on && even;
   pl->keys_alt = take(std::max(sizeof(unsigned long long) * (size_t)cap, spare ? sizeof(uint32_t) * (size_t)tiles : 0));
   if (spare) pl->tile_order = pl->keys_alt;
   L.values = take(sizeof(uint32_t) * (size_t)cap);
@@ -173,7 +181,7 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
     const size_t end = off, room = gs ? 0 : end;
     if (!gs) off = L.gview;
     if (!own_buffers) take_pairs();
-    pl->scan_scratch = take(scan_scratch_bytes(VP));
+    pl->scan_scratch = take(scan_scratch_bytes(VP, as_unseen ? 2 : 1));
     pl->tile_steps = take(pl->tile_order_on ? tile_order_scratch_bytes(tiles) : 0);
     // smaller blocks take four times the scratch: only where it adds nothing
     auto rounds_of = [&](int64_t n) {
@@ -183,7 +191,7 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
     pl->inst_rounds = rounds_of(cap);
     pl->pair_rounds = rounds_of(VP);
     size_t sort_bytes = sort_scratch_bytes(cap, pl->inst_rounds);
-    if (pl->depth_first && !order_small(P, V))
+    if ((pl->depth_first || as_unseen) && !as_one)
       sort_bytes = std::max(sort_bytes, sort_scratch_bytes(VP, pl->pair_rounds));
     pl->sort_scratch = take(sort_bytes);
     if (off < end) off = end;
@@ -352,23 +360,24 @@ static snp_status do_bin(const snp_config* cfg, int64_t P, int32_t V, const Plan
   const int64_t VP = (int64_t)V * P;
   const uint32_t* order = nullptr;  // identity: primitive order
   const uint32_t* counts = wsp<uint32_t>(ws, L.tile_counts);
-  uint32_t* offsets = wsp<uint32_t>(ws, L.offsets);
+  uint32_t* offsets = wsp<uint32_t>(ws, pl.unseen ? pl.offsets_sorted : L.offsets);
+  uint32_t* plain = pl.unseen ? wsp<uint32_t>(ws, L.offsets) : nullptr;
   unsigned long long* total = counters + CNT_INSTANCES;
   if (pl.depth_first) {
     uint32_t* cs = wsp<uint32_t>(ws, pl.counts_sorted);
     uint32_t* od = wsp<uint32_t>(ws, pl.order);
     const uint32_t* depth = wsp<uint32_t>(ws, L.depth_bits);
-    if (order_small(P, V))
-      SNP_HIP(launch_order_small(depth, counts, P, V, od, cs, offsets, total, st));
+    if (pl.one_launch)
+      SNP_HIP(launch_order_small(depth, counts, P, V, od, cs, offsets, plain, total, st));
     else
       SNP_HIP(order_pairs(depth, counts, VP, wsp<uint32_t>(ws, pl.dkeys[0]), wsp<uint32_t>(ws, pl.dkeys[1]),
                           wsp<uint32_t>(ws, pl.dvals), od, cs, pl.pair_rounds, wsp<void>(ws, pl.sort_scratch), st));
     order = od;
     counts = cs;
   }
-  if (!pl.depth_first || !order_small(P, V))
-    SNP_HIP(scan_exclusive_u32(counts, offsets, VP, wsp<void>(ws, pl.scan_scratch),
-                               reinterpret_cast<uint64_t*>(total), st));
+  if (!pl.one_launch)
+    SNP_HIP(scan_exclusive_u32(counts, offsets, VP, wsp<void>(ws, pl.scan_scratch), reinterpret_cast<uint64_t*>(total),
+                               st, plain ? wsp<uint32_t>(ws, L.tile_counts) : nullptr, plain));
   const bool odd = radix_passes(sort_bits(pl)) % 2 == 1;
   EmitArgs ea;
   ea.P = P;
@@ -379,11 +388,11 @@ static snp_status do_bin(const snp_config* cfg, int64_t P, int32_t V, const Plan
   ea.depth_bits = wsp<uint32_t>(ws, L.depth_bits);
   ea.tile_counts = wsp<uint32_t>(ws, L.tile_counts);
   ea.order = order;
-  ea.offsets = wsp<uint32_t>(ws, L.offsets);
+  ea.offsets = offsets;
   ea.keys = wsp<unsigned long long>(ws, odd ? pl.keys_alt : L.keys);
   ea.values = wsp<uint32_t>(ws, odd ? pl.values_alt : L.values);
   ea.counters = counters;
-  ea.depth_sorted = pl.depth_reported;
+  ea.depth_sorted = pl.depth_first && !pl.unseen ? VP : 0;
   SNP_HIP(launch_emit(ea, st));
   (void)cfg;
   return SNP_OK;

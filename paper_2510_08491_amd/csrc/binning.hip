@@ -21,8 +21,8 @@
 //   ranges : [start, end) of every global tile in the sorted array
 //
 // At the sizes of one view every kernel here is a few microseconds, most of
-// it launch and drain, so the launches are counted: up to kOrderMax pairs are
-// ordered, counted and scanned by one workgroup in LDS, a pass takes three
+// it launch and drain, so the launches are counted: with few pairs those of a
+// view are ordered, counted and scanned by one workgroup in LDS, a pass takes three
 // kernels at any size, a scan one or two, and what a neighbour can do on the
 // way (first keys, last gather, clears, checks) has no launch of its own.
 //
@@ -94,9 +94,16 @@ __device__ __forceinline__ T block_exclusive_scan(T x, T* total, T* s_warp) {
   return base + inc - x;
 }
 
-__global__ void __launch_bounds__(kScanThreads) scan_totals_kernel(const uint32_t* __restrict__ in, int64_t n,
-                                                                   uint64_t* __restrict__ totals) {
+// (the row of the grid picks the array)
+struct ScanArrays {
+  const uint32_t* in[2];
+  uint32_t* out[2];
+};
+
+__global__ void __launch_bounds__(kScanThreads) scan_totals_kernel(ScanArrays a, int64_t n, uint64_t* totals) {
   __shared__ uint64_t s_warp[kScanThreads / 64];
+  const uint32_t* __restrict__ in = a.in[blockIdx.y];
+  totals += (int64_t)blockIdx.y * gridDim.x;
   const int64_t base = (int64_t)blockIdx.x * kScanChunk;
   uint64_t sum = 0;
 #pragma unroll
@@ -111,11 +118,12 @@ __global__ void __launch_bounds__(kScanThreads) scan_totals_kernel(const uint32_
 
 // One block's chunk, after the totals of the blocks before it: summed here
 // (prefixed = 0), or already in totals as exclusive prefixes.
-__global__ void __launch_bounds__(kScanThreads) scan_chunk_kernel(const uint32_t* __restrict__ in,
-                                                                  uint32_t* __restrict__ out, int64_t n,
-                                                                  const uint64_t* __restrict__ totals, int prefixed,
-                                                                  uint64_t* total_out) {
+__global__ void __launch_bounds__(kScanThreads) scan_chunk_kernel(ScanArrays a, int64_t n, const uint64_t* totals,
+                                                                  int prefixed, uint64_t* total_out) {
   __shared__ uint64_t s_warp[kScanThreads / 64];
+  const uint32_t* __restrict__ in = a.in[blockIdx.y];
+  uint32_t* __restrict__ out = a.out[blockIdx.y];
+  totals += (int64_t)blockIdx.y * gridDim.x;
   uint64_t before = 0;
   if (prefixed) {
     before = totals[blockIdx.x];
@@ -141,13 +149,14 @@ __global__ void __launch_bounds__(kScanThreads) scan_chunk_kernel(const uint32_t
     if (i < n) out[i] = (uint32_t)run;
     run += v[k];
   }
-  if (total_out && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total_out = before + total;
+  if (total_out && blockIdx.y == 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total_out = before + total;
 }
 
 // totals -> exclusive prefixes in place, one workgroup (more blocks than
 // kScanBlocksMax: 2^25 values and up)
 __global__ void __launch_bounds__(1024) scan_prefix_kernel(uint64_t* totals, int64_t n) {
   __shared__ uint64_t s_warp[16];
+  totals += (int64_t)blockIdx.y * n;
   uint64_t carry = 0;
   for (int64_t i0 = 0; i0 < n; i0 += 1024) {
     const int64_t i = i0 + threadIdx.x;
@@ -159,23 +168,26 @@ __global__ void __launch_bounds__(1024) scan_prefix_kernel(uint64_t* totals, int
   }
 }
 
-// Scratch needed by scan_exclusive_u32 for n elements (bytes).
-size_t scan_scratch_bytes(int64_t n) {
+// Scratch needed by scan_exclusive_u32 for n elements of one or two arrays (bytes).
+size_t scan_scratch_bytes(int64_t n, int arrays) {
   const int64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  return ((size_t)nb * 8 + 255) / 256 * 256 + 256;
+  return ((size_t)nb * arrays * 8 + 255) / 256 * 256 + 256;
 }
 
 // Exclusive scan of n uint32 values into out (wrapping) and the exact total
-// into *total_out (uint64, device) if non-null.
+// into *total_out (uint64, device) if non-null; with in2, of a second array
+// into out2 in the same launches.
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint64_t* total_out,
-                              hipStream_t st) {
+                              hipStream_t st, const uint32_t* in2, uint32_t* out2) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = (n + kScanChunk - 1) / kScanChunk;
   uint64_t* totals = reinterpret_cast<uint64_t*>(scratch);
+  const ScanArrays a = {{in, in2}, {out, out2}};
+  const unsigned rows = in2 ? 2 : 1;
   const bool prefixed = nb > kScanBlocksMax;
-  if (nb > 1) hipLaunchKernelGGL(scan_totals_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, n, totals);
-  if (prefixed) hipLaunchKernelGGL(scan_prefix_kernel, dim3(1), dim3(1024), 0, st, totals, nb);
-  hipLaunchKernelGGL(scan_chunk_kernel, dim3((unsigned)nb), dim3(kScanThreads), 0, st, in, out, n, totals,
+  if (nb > 1) hipLaunchKernelGGL(scan_totals_kernel, dim3((unsigned)nb, rows), dim3(kScanThreads), 0, st, a, n, totals);
+  if (prefixed) hipLaunchKernelGGL(scan_prefix_kernel, dim3(1, rows), dim3(1024), 0, st, totals, nb);
+  hipLaunchKernelGGL(scan_chunk_kernel, dim3((unsigned)nb, rows), dim3(kScanThreads), 0, st, a, n, totals,
                      prefixed ? 1 : 0, total_out);
   return hipGetLastError();
 }
@@ -208,20 +220,19 @@ __device__ __forceinline__ unsigned long long same_digit(uint32_t d, bool valid)
 // before it, which its workgroup adds up itself.  Bound by its own chain of
 // barriers and rounds (a CU per view).  3 x 3001 pairs: twenty launches of
 // passes over all pairs 0.16 ms, one workgroup for all views and four passes
-// 46 us, this 22; 2 x 7919 pairs 79 -> 39 us; 256 pairs 14 us.
+// 46 us, this 22; 2 x 7919 pairs 79 -> 39 us; 256 pairs 14 us.  A second
+// row of workgroups, beside the first, scans the counts in primitive order.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderWaves = kOrderThreads / 64;
 constexpr int kOrderItems = 16;
 constexpr int kOrderMax = kOrderThreads * kOrderItems;  // 16384
-// pairs in all: the passes over all pairs cost 50 us from the start, and a
-// view's workgroup reads the counts of all views before it
-constexpr int64_t kOrderPairs = 131072;
 
 __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32_t* __restrict__ depth_bits,
                                                                     const uint32_t* __restrict__ counts, int n,
                                                                     uint32_t* __restrict__ order,
                                                                     uint32_t* __restrict__ counts_sorted,
                                                                     uint32_t* __restrict__ offsets,
+                                                                    uint32_t* __restrict__ plain,
                                                                     unsigned long long* total_out) {
   const int64_t v0 = (int64_t)blockIdx.x * n;  // the view's first pair
   __shared__ uint32_t s_key[kOrderMax];
@@ -232,6 +243,20 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   // rounds of 64 keys per wave: the waves share the keys evenly
   const int rounds = (n + kOrderThreads - 1) / kOrderThreads;
+  if (blockIdx.y == 1) {  // the scan in primitive order: `rounds` consecutive counts per thread, read twice
+    const int end = min((t + 1) * rounds, n);
+    uint64_t sum = 0, before = 0, total;
+    for (int64_t i = t; i < v0; i += kOrderThreads) before += counts[i];
+    for (int i = t * rounds; i < end; ++i) sum += counts[v0 + i];
+    block_exclusive_scan<kOrderThreads>(before, &total, s_warp);
+    uint64_t run = total;
+    run += block_exclusive_scan<kOrderThreads>(sum, &total, s_warp);
+    for (int i = t * rounds; i < end; ++i) {
+      plain[v0 + i] = (uint32_t)run;
+      run += counts[v0 + i];
+    }
+    return;
+  }
   const int first = w * rounds * 64 + lane;
   const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   uint32_t key[kOrderItems];
@@ -353,13 +378,13 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
   if (t == 0 && blockIdx.x == gridDim.x - 1) *total_out = before + total;
 }
 
-bool order_small(int64_t P, int32_t V) { return P <= kOrderMax && P * V <= kOrderPairs; }
+bool order_small(int64_t P) { return P <= kOrderMax; }
 
 hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t P, int32_t V, uint32_t* order,
-                              uint32_t* counts_sorted, uint32_t* offsets, unsigned long long* total_out,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(order_small_kernel, dim3((unsigned)V), dim3(kOrderThreads), 0, st, depth_bits, counts, (int)P, order,
-                     counts_sorted, offsets, total_out);
+                              uint32_t* counts_sorted, uint32_t* offsets, uint32_t* plain,
+                              unsigned long long* total_out, hipStream_t st) {
+  hipLaunchKernelGGL(order_small_kernel, dim3((unsigned)V, 2), dim3(kOrderThreads), 0, st, depth_bits, counts, (int)P,
+                     order, counts_sorted, offsets, plain, total_out);
   return hipGetLastError();
 }
 

@@ -79,7 +79,7 @@ enum Counter {
   CNT_QUEUE_FWD = 4,
   CNT_QUEUE_BWD = 5,
   CNT_LIVE_PAIRS = 6,
-  CNT_DEPTH_SORT = 7,  // number of (view, primitive) pairs, the length of the depth sort
+  CNT_DEPTH_SORT = 7,  // number of (view, primitive) pairs, the length of the depth sort (0 where Plan::unseen)
   CNT_COUNT = 8
 };
 
@@ -279,7 +279,7 @@ struct EmitArgs {
   const uint32_t* depth_bits;
   const uint32_t* tile_counts;
   const uint32_t* order;    // (view, primitive) pair indices in depth order
-  const uint32_t* offsets;  // first instance of each pair, in depth order
+  const uint32_t* offsets;  // first instance of each pair, in that order
   unsigned long long* keys;
   uint32_t* values;
   unsigned long long* counters;
@@ -338,13 +338,13 @@ hipError_t launch_ray_colour_fwd(const RayColourArgs& a, hipStream_t st);
 hipError_t launch_ray_colour_bwd(const RayColourArgs& a, hipStream_t st);
 // binning.hip
 hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
-size_t scan_scratch_bytes(int64_t n);
+size_t scan_scratch_bytes(int64_t n, int arrays = 1);
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint64_t* total_out,
-                              hipStream_t st);
-bool order_small(int64_t P, int32_t V);
+                              hipStream_t st, const uint32_t* in2 = nullptr, uint32_t* out2 = nullptr);
+bool order_small(int64_t P);
 hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t P, int32_t V, uint32_t* order,
-                              uint32_t* counts_sorted, uint32_t* offsets, unsigned long long* total_out,
-                              hipStream_t st);
+                              uint32_t* counts_sorted, uint32_t* offsets, uint32_t* plain,
+                              unsigned long long* total_out, hipStream_t st);
 hipError_t order_pairs(const uint32_t* depth_bits, const uint32_t* counts, int64_t n, uint32_t* ka, uint32_t* kb,
                        uint32_t* va, uint32_t* order, uint32_t* counts_sorted, int rounds, void* scratch,
                        hipStream_t st);
