@@ -120,7 +120,7 @@ static snp_status make_plan(const snp_config* cfg, int64_t P, int32_t V, const s
   pl->depth_first = cfg->bin_order != 2;
   pl->unseen = cfg->bin_order == 0 && few;
   const bool as_unseen = few && cfg->bin_order != 1;  // the same layout for bin_order 0 and 2
-  const bool as_one = as_unseen && order_small(P);
+  const bool as_one = as_unseen && order_small(P, V);
   pl->one_launch = pl->unseen && as_one;
   // Gaussians have no density table, float64 discriminants, backward arrays
   // or pair cache

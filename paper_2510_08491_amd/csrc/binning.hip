@@ -378,7 +378,14 @@ __global__ void __launch_bounds__(kOrderThreads) order_small_kernel(const uint32
   if (t == 0 && blockIdx.x == gridDim.x - 1) *total_out = before + total;
 }
 
-bool order_small(int64_t P) { return P <= kOrderMax; }
+// A workgroup holds a CU, and reads the counts of all views before its own, so
+// with many views the passes over all pairs win.  Binning and sorting, a
+// workgroup per view / passes: 64 views of 1023 primitives 52 / 86 us, 256 of
+// 255 63 / 88, 512 of 127 86 / 90, 512 of 15 69 / 85, 1024 of 63 133 / 95,
+// 1024 of 15 111 / 93, 4096 of 15 389 / 94.
+constexpr int kOrderViews = 512;
+
+bool order_small(int64_t P, int32_t V) { return P <= kOrderMax && V <= kOrderViews; }
 
 hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t P, int32_t V, uint32_t* order,
                               uint32_t* counts_sorted, uint32_t* offsets, uint32_t* plain,

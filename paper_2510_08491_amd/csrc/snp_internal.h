@@ -341,7 +341,7 @@ hipError_t fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t st);
 size_t scan_scratch_bytes(int64_t n, int arrays = 1);
 hipError_t scan_exclusive_u32(const uint32_t* in, uint32_t* out, int64_t n, void* scratch, uint64_t* total_out,
                               hipStream_t st, const uint32_t* in2 = nullptr, uint32_t* out2 = nullptr);
-bool order_small(int64_t P);
+bool order_small(int64_t P, int32_t V);
 hipError_t launch_order_small(const uint32_t* depth_bits, const uint32_t* counts, int64_t P, int32_t V, uint32_t* order,
                               uint32_t* counts_sorted, uint32_t* offsets, uint32_t* plain,
                               unsigned long long* total_out, hipStream_t st);
