@@ -924,7 +924,9 @@ __device__ __forceinline__ float cross_rows_pair(float a, float b) {
 // and 2, level 2 the partners lane ^ 8 (row_ror:8) and banks 0 and 1.  The
 // instructions write part of their destination, which the compiler's DPP
 // builtins cannot express for an add; the waits before the first DPP read are
-// the two states the hardware asks for after a VALU write.
+// the two states the hardware asks for after a VALU write.  The outputs are
+// early-clobber: they are written before the last input is read, so no input
+// may share their register, not even one of the same value.
 #define SNP_HM(a, b)                                                             \
   "v_add_f32_dpp " a ", " a ", " a " row_half_mirror row_mask:0xf bank_mask:0x5\n\t" \
   "v_add_f32_dpp " a ", " b ", " b " row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
@@ -939,7 +941,7 @@ __device__ __forceinline__ void row_levels_pair(float (&v8)[8], float (&v2)[2]) 
   asm("s_nop 1\n\t"  //
       SNP_HM("%0", "%5") SNP_HM("%1", "%6") SNP_HM("%2", "%7") SNP_HM("%3", "%8") SNP_HM("%4", "%9")
       SNP_R8("%0", "%1") SNP_R8("%2", "%3") "s_nop 0"
-      : "+v"(v8[0]), "+v"(v8[2]), "+v"(v8[4]), "+v"(v8[6]), "+v"(v2[0])
+      : "+&v"(v8[0]), "+&v"(v8[2]), "+&v"(v8[4]), "+&v"(v8[6]), "+&v"(v2[0])
       : "v"(v8[1]), "v"(v8[3]), "v"(v8[5]), "v"(v8[7]), "v"(v2[1]));
 }
 
@@ -949,7 +951,7 @@ __device__ __forceinline__ void row_levels_16(float* R) {
       SNP_HM("%0", "%8") SNP_HM("%1", "%9") SNP_HM("%2", "%10") SNP_HM("%3", "%11")
       SNP_HM("%4", "%12") SNP_HM("%5", "%13") SNP_HM("%6", "%14") SNP_HM("%7", "%15")
       SNP_R8("%0", "%1") SNP_R8("%2", "%3") SNP_R8("%4", "%5") SNP_R8("%6", "%7") "s_nop 1"
-      : "+v"(R[0]), "+v"(R[2]), "+v"(R[4]), "+v"(R[6]), "+v"(R[8]), "+v"(R[10]), "+v"(R[12]), "+v"(R[14])
+      : "+&v"(R[0]), "+&v"(R[2]), "+&v"(R[4]), "+&v"(R[6]), "+&v"(R[8]), "+&v"(R[10]), "+&v"(R[12]), "+&v"(R[14])
       : "v"(R[1]), "v"(R[3]), "v"(R[5]), "v"(R[7]), "v"(R[9]), "v"(R[11]), "v"(R[13]), "v"(R[15]));
 }
 
@@ -960,7 +962,7 @@ __device__ __forceinline__ float row_levels_3(float a, float b, float c) {
       SNP_HM("%0", "%2")
       "s_nop 1\n\t"
       SNP_R8("%0", "%1") "s_nop 1"
-      : "+v"(a), "+v"(c)
+      : "+&v"(a), "+&v"(c)
       : "v"(b));
   return a;
 }
@@ -968,7 +970,7 @@ __device__ __forceinline__ float row_levels_3(float a, float b, float c) {
 __device__ __forceinline__ float row_level_ror8(float a, float b) {
   asm("s_nop 1\n\t"  //
       SNP_R8("%0", "%1") "s_nop 1"
-      : "+v"(a)
+      : "+&v"(a)
       : "v"(b));
   return a;
 }
