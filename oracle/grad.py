@@ -6,7 +6,9 @@ Route 1 re-implements the renderer of oracle.render in torch.float64 on the
 CPU and differentiates it with autograd.  It is written separately from the
 numpy renderer: the chord integral uses the antiderivative literally,
 S(t_out) - S(t_in) (Eq. 7-8), instead of the midpoint form, so agreement of
-the two renderers also checks both integral forms.  Discrete decisions
+the two renderers also checks both integral forms (but where the phase hardly
+changes along the chord, where the difference and its derivative lose their
+digits).  Discrete decisions
 (culling, rectangles, depth order, termination) are taken from the numpy key
 path and carry no gradient.
 
@@ -152,15 +154,22 @@ def render_view_torch(params, meta, cam, opts: RenderOptions = RenderOptions(), 
         c = ((o - xb) @ params["w1"][p].T) / m + params["b1"][p]
         w2 = params["w2"][p]
         tph = float(meta.get("time", 0.0)) * params["wt"][p] if params.get("wt") is not None else 0.0
-        tiny = a.abs() < 1e-9
-        a_safe = torch.where(tiny, torch.ones_like(a), a)
+        # the difference of the antiderivatives divides by the phase gradient a,
+        # its derivative by a^2: where the phase changes by less than 0.2 along
+        # the chord, the midpoint form instead, with the series of sin(h)/h
+        # (h = omega a (t_out - t_in) / 2 < 0.1; the next term is below 1e-17)
+        dt = (t_out - t_in)[..., None]
+        h2 = (0.5 * om * a * dt) ** 2
+        flat = h2 < 0.01
+        a_safe = torch.where(flat, torch.ones_like(a), a)
 
         def S(t):
             return (w2 * torch.sin(om * (a_safe * t[..., None] + c) + tph) / (om * a_safe))
 
         lit = S(t_out) - S(t_in)
-        lim = w2 * torch.cos(om * (a * (0.5 * (t_in + t_out))[..., None] + c) + tph) * (t_out - t_in)[..., None]
-        integral = torch.where(tiny, lim, lit).sum(-1) + params["b2"][p] * (t_out - t_in)
+        sinc = 1.0 - h2 / 6.0 * (1.0 - h2 / 20.0 * (1.0 - h2 / 42.0 * (1.0 - h2 / 72.0)))
+        mid = w2 * torch.cos(om * (a * (0.5 * (t_in + t_out))[..., None] + c) + tph) * dt * sinc
+        integral = torch.where(flat, mid, lit).sum(-1) + params["b2"][p] * (t_out - t_in)
         alpha = 1.0 - torch.exp(-torch.clamp(integral, min=0.0))
         alpha = torch.clamp(alpha, max=opts.alpha_max)
         use = hit
