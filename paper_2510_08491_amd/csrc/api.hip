@@ -439,10 +439,7 @@ static RasterArgs raster_args(const snp_config* cfg, int64_t P, int32_t V, const
   a.values = wsp<uint32_t>(ws, L.values);
   a.ranges = wsp<uint32_t>(ws, L.ranges);
   a.tile_order = pl.tile_order_on ? wsp<uint32_t>(ws, pl.tile_order) : nullptr;
-  int dev = 0, cus = 0;
-  (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  a.cus = cus > 0 ? cus : 1;
+  a.cus = device_cus();
   a.rects = wsp<int32_t>(ws, L.rects);
   a.gview = wsp<float>(ws, L.gview);
   a.gtable = wsp<float>(ws, L.gtable);

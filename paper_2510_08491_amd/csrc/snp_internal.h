@@ -360,6 +360,14 @@ hipError_t launch_ranges(const unsigned long long* keys, const unsigned long lon
 size_t tile_order_scratch_bytes(int64_t n_tiles);
 hipError_t launch_tile_order(const uint32_t* ranges, int64_t n_tiles, uint32_t* order, uint32_t* scratch,
                              hipStream_t st);
+// compute units of the current device
+inline int device_cus() {
+  int dev = 0, cus = 0;
+  (void)hipGetDevice(&dev);
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  return cus > 0 ? cus : 1;
+}
+
 // raster.hip
 int supported_tiles(int32_t* triples, int32_t max);
 bool tile_supported(int tw, int th, int ppl);

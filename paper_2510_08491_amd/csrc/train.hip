@@ -77,14 +77,15 @@ hipError_t launch_adam(const snp_adam_group* groups, int ng, int64_t step, doubl
   for (int k = ng; k <= SNP_MAX_ADAM_GROUPS; ++k) a.start[k] = total;
   if (total == 0) return hipSuccess;
   int64_t blocks = (total + 255) / 256;
-  // Bound by memory.  2048 workgroups are what 256 CUs hold at once (32 waves
-  // each), so none waits for another and all walk the arrays abreast.  Same
-  // card, 2048 against the 8192 before, of 1639 floats per primitive: 10k
-  // primitives 97 / 106 us, 20k 211 / 220, 35k 372 / 385, 50k 534 / 536, 100k
-  // 1032 / 1065 (4.45 TB/s); half as many leave the memory idle (1406 us at
-  // 100k), 32768 are slower at most sizes (117 us at 10k).  Non-temporal loads
-  // win at 20k and 100k (201, 991 us) and lose elsewhere (5k: 66, 75k: 1122).
-  if (blocks > 2048) blocks = 2048;
+  // Bound by memory.  Eight workgroups (32 waves) are what a CU holds at once, so
+  // none waits for another and all walk the arrays abreast.  256 CUs, 2048
+  // workgroups against 8192, timed in turn on the same buffers of 1639 floats per
+  // primitive: 1k primitives 11.5 / 15.9 us, 5k 43.2 / 45.7, 10k 99.6 / 111, 20k
+  // 211 / 222, 50k 541 / 556, 75k 828 / 833, 100k 1034 / 1050 (4.44 TB/s); half
+  // as many leave the memory idle (1406 us at 100k).  Non-temporal loads win at
+  // 20k and 100k (201, 991 us) and lose elsewhere (5k: 66, 75k: 1122).
+  const int64_t resident = 8 * (int64_t)device_cus();
+  if (blocks > resident) blocks = resident;
   hipLaunchKernelGGL(adam_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
   return hipGetLastError();
 }
