@@ -111,12 +111,16 @@ typedef struct {
  *  persistent 1 = one persistent launch over all (view, tile) work items
  *             with a device work queue; 0 = one workgroup per tile.  Both
  *             take the tiles with the most instances first, so the heaviest
- *             tiles do not form the tail.
+ *             tiles do not form the tail.  Not read where a launch has few
+ *             16 x 16 tiles (up to six per compute unit; neural primitives,
+ *             colour modes 0 to 3; the forward with one pixel per thread and
+ *             without counting pairs): such a launch gives every tile several
+ *             workgroups or further waves, and uses no queue.
  *  bwd_batch  instances per batch of the backward rasterizer (0 = the
  *             default for the tile shape); the tile shape is shared with the
  *             forward, and the backward runs one pixel per thread.  Launches
- *             of few 16 x 16 tiles (up to six per compute unit) take batches
- *             of their own.
+ *             of few 16 x 16 tiles (as under persistent) take batches of
+ *             their own; colour mode 4 keeps this one.
  *  fwd_cache  1 = the forward stores the integral (alpha-hat, Eq. 8-9) of
  *             every (pixel, instance) pair it evaluates, capacity x tile_w x
  *             tile_h floats in the workspace, and the backward reads it back
@@ -183,9 +187,12 @@ typedef struct {
                            c_1..c_4 of sin(i xi_t); channel), added to sh[p][0][c]; or NULL */
 } snp_prims;
 
-/* Gradient outputs, same shapes as the parameters.  The backward ADDS into
- * them (the caller zeroes them first); NULL skips a tensor (gradients of xi
- * are only produced when non-NULL). */
+/* Gradient outputs, same shapes as the parameters.  snp_render_backward ADDS
+ * into them (the caller zeroes them first); snp_render_backward_set, snp_step,
+ * snp_step_static and a captured step SET them, whatever they held before.
+ * NULL skips a tensor.  A tensor that the colour mode does not use (colors
+ * outside modes 0, 3 and 4; cmlp outside 1, 3 and 4; xi outside 1 and 3; sh and
+ * sh_t outside 2) is left as it is by all of them. */
 typedef struct {
   float *centers, *scales, *quats, *w1, *b1, *w2, *b2, *colors, *cmlp, *xi, *sh;
   float *wt;   /* P x N, with prims.wt */
@@ -202,12 +209,12 @@ typedef struct {
   size_t rects;           /* per-(view, primitive) pixel rectangles, int32 x0,x1,y0,y1 */
   size_t depth_bits;      /* per-(view, primitive) uint32 depth key (0 = culled) */
   size_t tile_counts;     /* per-(view, primitive) uint32 number of tiles */
-  size_t offsets;         /* uint32 exclusive scan of tile_counts over the (view, primitive) pairs (in depth order with bin_order 1) */
+  size_t offsets;         /* uint32 exclusive scan of tile_counts over the (view, primitive) pairs (in depth order with bin_order 1, also where 0 is 1) */
   size_t keys;            /* uint64 sorted keys (tile << 31 | depth bits), capacity entries */
   size_t values;          /* uint32 sorted primitive ids, capacity entries */
   size_t ranges;          /* per global tile uint32 [start, end) */
   size_t counters;        /* uint64: [0] instances, [1] overflow flag, [2] hit pairs, [3] range flag */
-  size_t gview;           /* backward: per-(view, primitive) gradient records */
+  size_t gview;           /* backward: per-(view, primitive) gradient records (snp_bin and snp_sort use gview and gtable as scratch) */
   size_t gtable;          /* backward: per-primitive table gradients */
   size_t loss;            /* loss partial sums (float64) */
   size_t disc_coef;       /* per-(view, primitive) 6 float64 coefficients of the ray discriminant */
@@ -294,15 +301,16 @@ snp_status snp_render_backward(const snp_config* cfg, const snp_prims* prims, in
                                void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
                                const snp_grads* grads, hipStream_t stream);
 
-/* snp_render_backward that sets `grads` instead of adding into it (every
- * element of the tensors the colour mode uses, whatever they held before). */
+/* snp_render_backward that sets `grads` instead of adding into it: every
+ * element of the tensors the colour mode uses, whatever they held before. */
 snp_status snp_render_backward_set(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams,
                                    void* ws, const snp_layout* layout, const float* images, const float* dL_dimages,
                                    const snp_grads* grads, hipStream_t stream);
 
 /* One whole training step: preprocess, bin, sort, forward,
  * L1 loss against `targets` (mean over n_norm elements), backward.  Sets
- * `grads`, whatever they held before. */
+ * every element of the tensors of `grads` that the colour mode uses, whatever
+ * they held before. */
 snp_status snp_step(const snp_config* cfg, const snp_prims* prims, int32_t V, const snp_camera* cams, void* ws,
                     const snp_layout* layout, float* images, float* final_T, const float* targets, double n_norm,
                     double* loss_out, float* dL_dimages, const snp_grads* grads, hipStream_t stream);
@@ -358,7 +366,8 @@ snp_status snp_read_status(void* ws, const snp_layout* layout, int64_t* instance
 /* Synchronises `stream` and copies the 8 device counters of the workspace:
  * [0] instances, [1] overflow flag, [2] hit pairs and [6] pairs with a
  * positive, unclamped integral (both counted by snp_render_forward with
- * count_pairs != 0), [3] phase-range flag, [4], [5] work-queue heads,
+ * count_pairs != 0), [3] phase-range flag, [4], [5] work-queue heads (zero
+ * between launches),
  * [7] the number of (view, primitive) pairs the depth sort ordered. */
 snp_status snp_read_counters(void* ws, const snp_layout* layout, int64_t* out8, hipStream_t stream);
 

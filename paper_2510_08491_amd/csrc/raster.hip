@@ -1339,7 +1339,7 @@ __attribute__((amdgpu_waves_per_eu(CD > 0 || N <= 8 || WIDE > 1 ? 4 : 5))) rende
         const uint32_t y = __shfl_up(rsum, o);
         if (lane >= o) rsum += y;
       }
-      // (lanes past the last instance repeat its end)
+      // (of the first NB lanes, those past the last instance repeat its end)
       const uint32_t total = __builtin_amdgcn_readlane(rsum, NB - 1);
       for (uint32_t q0 = 4 * wave; q0 < total; q0 += 4 * NW * WIDE) {
         {
