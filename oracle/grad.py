@@ -158,18 +158,22 @@ def render_view_torch(params, meta, cam, opts: RenderOptions = RenderOptions(), 
         # its derivative by a^2: where the phase changes by less than 0.2 along
         # the chord, the midpoint form instead, with the series of sin(h)/h
         # (h = omega a (t_out - t_in) / 2 < 0.1; the next term is below 1e-17)
-        dt = (t_out - t_in)[..., None]
-        h2 = (0.5 * om * a * dt) ** 2
-        flat = h2 < 0.01
+        dt, tm = (t_out - t_in)[..., None], (0.5 * (t_in + t_out))[..., None]
+        flat = (0.5 * om * a * dt).detach().abs() < 0.1
         a_safe = torch.where(flat, torch.ones_like(a), a)
 
         def S(t):
             return (w2 * torch.sin(om * (a_safe * t[..., None] + c) + tph) / (om * a_safe))
 
-        lit = S(t_out) - S(t_in)
-        sinc = 1.0 - h2 / 6.0 * (1.0 - h2 / 20.0 * (1.0 - h2 / 42.0 * (1.0 - h2 / 72.0)))
-        mid = w2 * torch.cos(om * (a * (0.5 * (t_in + t_out))[..., None] + c) + tph) * dt * sinc
-        integral = torch.where(flat, mid, lit).sum(-1) + params["b2"][p] * (t_out - t_in)
+        units = S(t_out) - S(t_in)
+        if bool(flat.any()):
+            at = flat.nonzero(as_tuple=True)
+            af, dtf, tmf = a[at], dt.expand_as(a)[at], tm.expand_as(a)[at]
+            phase = om * (af * tmf + c[at[-1]]) + (tph + torch.zeros_like(c))[at[-1]]
+            h2 = (0.5 * om * af * dtf) ** 2
+            sinc = 1.0 - h2 / 6.0 * (1.0 - h2 / 20.0 * (1.0 - h2 / 42.0 * (1.0 - h2 / 72.0)))
+            units = units.index_put(at, w2[at[-1]] * torch.cos(phase) * dtf * sinc)
+        integral = units.sum(-1) + params["b2"][p] * (t_out - t_in)
         alpha = 1.0 - torch.exp(-torch.clamp(integral, min=0.0))
         alpha = torch.clamp(alpha, max=opts.alpha_max)
         use = hit
